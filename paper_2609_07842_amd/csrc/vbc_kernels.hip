@@ -98,12 +98,12 @@ __device__ __forceinline__ double omega_dd64(double x, double x1, double x2)
     return -4.0 * u * (1.0 - u * u) / w;
 }
 
+// Smooth step of eq. (omega) over the unit-width switching window [x1, x1 + 1] of
+// eq. (Psidelta), in the pair-arithmetic precision.
 template <class Real>
-__device__ __forceinline__ Real omega_r(Real x, Real x1, Real x2)
+__device__ __forceinline__ Real omega_win(Real x, Real x1)
 {
-    Real u = (x - x1) / (x2 - x1);
-    u = u < Real(0) ? Real(0) : (u > Real(1) ? Real(1) : u);
-    Real q = Real(1) - u * u;
+    const Real u = clamp01(x - x1), q = fma(-u, u, Real(1));
     return q * q;
 }
 
@@ -1200,13 +1200,56 @@ __device__ __forceinline__ typename V4<Real>::t local_pos(const RepDev &R, const
     return p;
 }
 
+// Type pair (i, j) of the general pair path as three records of four, so that a list entry
+// takes three LDS reads of its pair instead of one per constant: the lanes of a wave read at
+// most 16 different records, which lie in different banks.  Absent interactions are zero
+// coefficients (no attraction: c_a = E_a = 0; j not counted by i: the mask bit in cnt.x), so
+// that the pair terms need no branch.  The general force pass is bound by VALU issue: with one
+// read per constant, a division per switching factor and branches that nearly every wave took
+// both sides of, it ran at 118.7 us on a melt of 250,000 beads (density 0.85, two types); this
+// form takes 61.7 us, and the dU/dn pass with its gathers in phases 12.4 us instead of 14.7.
+template <class Real>
+struct PairM {
+    typename V4<Real>::t core;  // c_r, k_r, c_a, x1
+    typename V4<Real>::t geo;   // 1/w, -m/w, 1/(r_h - r_l), -r_l/(r_h - r_l)
+    typename V4<Real>::t cnt;   // c_c [i counts j], c_c [j counts i], E_r / c_r^2, E_a
+};
+
+template <class Real>
+__device__ __forceinline__ PairM<Real> pair_m(const RepDev &R, int a, int c)
+{
+    const PairDev &p = R.pair[a * MAXT + c];
+    PairM<Real> q;
+    q.core.x = (Real)p.c_r;
+    q.core.y = (Real)(-p.c_r * p.inv_rr2);
+    q.core.z = p.attract ? (Real)p.c_a : Real(0);
+    q.core.w = (Real)p.x1;
+    q.geo.x = (Real)p.inv_w;
+    q.geo.y = (Real)(-p.m * p.inv_w);
+    q.geo.z = (Real)p.inv_dw;
+    q.geo.w = (Real)(-p.r_l * p.inv_dw);
+    q.cnt.x = ((R.mask[a] >> c) & 1u) ? (Real)p.c_c : Real(0);
+    q.cnt.y = ((R.mask[c] >> a) & 1u) ? (Real)p.c_c : Real(0);
+    q.cnt.z = p.E_r > 0.0 ? (Real)(p.E_r / (p.c_r * p.c_r)) : Real(0);
+    q.cnt.w = p.attract ? (Real)p.E_a : Real(0);
+    return q;
+}
+
+// One thread per type pair writes its record (the general path), or thread 0 the constants of
+// the only one.
 template <class Real>
 __device__ __forceinline__ void load_pairs(const RepDev &R, PairR<Real> *pt)
 {
+    if (threadIdx.x == 0) pt[0] = pair_r<Real>(R.pair[0], R.rc2);
+}
+
+template <class Real>
+__device__ __forceinline__ void load_pairs_m(const RepDev &R, PairM<Real> *pm, int tid)
+{
     const int nt = R.ntypes;
-    if ((int)threadIdx.x < nt * nt) {
-        int a = threadIdx.x / nt, c = threadIdx.x % nt;
-        pt[a * MAXT + c] = pair_r<Real>(R.pair[a * MAXT + c], R.rc2);
+    if (tid < nt * nt) {
+        const int a = tid / nt, c = tid % nt;
+        pm[a * MAXT + c] = pair_m<Real>(R, a, c);
     }
 }
 
@@ -1324,7 +1367,8 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
     extern __shared__ __align__(32) unsigned char smem[];
     __shared__ int nwin;  // own particles inside a switching window
     __shared__ unsigned long long ev_sum;
-    __shared__ PairR<Real> pt[MAXT * MAXT];
+    __shared__ PairR<Real> pt[1];
+    __shared__ PairM<Real> pm[MULTI ? MAXT * MAXT : 1];
     int b;
     if (!brick_of_block(P, B, b)) return;
     const MapFirst mf = map_prefetch(B, b, P.stage_cap);
@@ -1343,6 +1387,7 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
     float *sza = (float *)(sxy + P.stage_cap + 1);
     const int64_t S_ = P.nslots;
     load_pairs<Real>(R, pt);
+    if (MULTI) load_pairs_m<Real>(R, pm, threadIdx.x);
     if (threadIdx.x == 0) {
         nwin = 0;
         ev_sum = 0ull;
@@ -1434,11 +1479,13 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
             if (STATS) inside += (r2 < p0.rc2) ? 1 : 0;
             Real rr = sqrt_r(r2);
             if (MULTI) {
-                int tj = (int)pj.w;
-                const PairR<Real> &q = pt[ti * MAXT + tj];
-                Real uu = clamp01((rr - q.r_l) * q.inv_dw);
-                Real qq = Real(1) - uu * uu;
-                chunk += (((R.mask[ti] >> tj) & 1u) && !ex) ? qq * qq : Real(0);
+                const PairM<Real> &q = pm[ti * MAXT + (int)pj.w];
+                const R4 g = q.geo;
+                Real uu = clamp01(fma(rr, g.z, g.w));
+                Real qq = fma(-uu, uu, Real(1));
+                // c_c is not zero where i counts j
+                qq = (q.cnt.x == Real(0) || ex) ? Real(0) : qq;
+                chunk = fma(qq, qq, chunk);
             } else {
                 Real uu = clamp01(fma(rr, p0.inv_dw, p0.nrl_dw));
                 Real qq = fma(-uu, uu, Real(1));
@@ -1513,9 +1560,10 @@ constexpr int EMBED_WAVES = 4;
 // group if already read, else -1.
 template <int LPP, class Real, bool MULTI>
 __device__ __forceinline__ void embed_brick(const Buffers &B, const Launch &P, const RepDev &R,
-                                            const PairR<Real> *pt, int b, int64_t base, int nw,
+                                            const PairM<Real> *pm, int b, int64_t base, int nw,
                                             int lane, int g, int ng, int t_first, int cur)
 {
+    using R4 = typename V4<Real>::t;
     // LPP lanes per window particle, EP entries of each list chunk per lane; neighbours are
     // gathered from global memory through the brick's staging map
     using R2 = typename V2<Real>::t;
@@ -1526,6 +1574,7 @@ __device__ __forceinline__ void embed_brick(const Buffers &B, const Launch &P, c
     const int32_t *sm = B.smap + (size_t)b * P.stage_cap;
     const uint8_t *wm = B.wmap + (size_t)b * P.stage_cap;
     const PairR<Real> p0 = pair_r<Real>(R.pair[0], R.rc2);
+    const bool xr = R.excl_span > 0;
     const int e = lane % LPP;
     for (int k = g; k < nw; k += ng) {
         int t = (k == g && t_first >= 0) ? t_first : B.wlst[base + k];
@@ -1535,7 +1584,7 @@ __device__ __forceinline__ void embed_brick(const Buffers &B, const Launch &P, c
         const double xi0 = X[3 * i], xi1 = X[3 * i + 1], xi2 = X[3 * i + 2];
         int nch = (B.nn[i] + CHUNK - 1) / CHUNK;
         double acc = 0.0;
-        if (!MULTI) {
+        {
             // four chunks at a time in phases (chunk words, staging map, positions, terms)
             // with no branch between the loads, so that the gathers of all four go out together;
             // rows past the list and the padding slot read valid memory and are masked.  The
@@ -1557,8 +1606,13 @@ __device__ __forceinline__ void embed_brick(const Buffers &B, const Launch &P, c
                     const int jc = j / EP, x = e + LPP * (j % EP);  // chunk, entry
                     const uint4 q = qc[jc];
                     const uint32_t wd = (x < 2) ? q.x : (x < 4) ? q.y : (x < 6) ? q.z : q.w;
-                    const int u = (int)((wd >> (16 * (x & 1))) & 0xffffu);
-                    vj[j] = c0 + jc < nch && u != P.stage_cap;
+                    int u = (int)((wd >> (16 * (x & 1))) & 0xffffu);
+                    bool ok = c0 + jc < nch;
+                    if (MULTI && xr) {
+                        ok = ok && !(u >> 15);  // excluded pair: no attraction between them
+                        u &= 0x7fff;
+                    }
+                    vj[j] = ok && u != P.stage_cap;
                     uj[j] = vj[j] ? u : 0;
                 }
 #pragma unroll
@@ -1571,44 +1625,35 @@ __device__ __forceinline__ void embed_brick(const Buffers &B, const Launch &P, c
                 for (int j = 0; j < 4; ++j)
                     for (int a = 0; a < 3; ++a) xj[j][a] = X[3 * sj[j] + a];
                 Real sjv[4];
+                int tj[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) sjv[j] = sA[sj[j]].x;
+                for (int j = 0; j < 4; ++j) {
+                    sjv[j] = sA[sj[j]].x;
+                    tj[j] = MULTI ? B.type[sj[j]] : 0;
+                }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     Real dx = (Real)(xi0 - (xj[j][0] + R.L[0] * (double)unpack_w(wj[j], 0)));
                     Real dy = (Real)(xi1 - (xj[j][1] + R.L[1] * (double)unpack_w(wj[j], 1)));
                     Real dz = (Real)(xi2 - (xj[j][2] + R.L[2] * (double)unpack_w(wj[j], 2)));
                     Real r2 = dx * dx + dy * dy + dz * dz;
-                    Real uu = (sqrt_r(r2) - p0.m) * p0.inv_w;
-                    Real qq = Real(1) - uu * uu;
-                    if (vj[j] && qq > Real(0)) acc += (double)(sjv[j] * (-p0.E_a * qq * qq));
+                    if (MULTI) {
+                        // s'_ij(n_i) in FP64 by the pair's window; no attraction: E_a = 0
+                        const PairM<Real> &q2 = pm[ti * MAXT + tj[j]];
+                        const R4 qg = q2.geo;
+                        const Real uu = fma(sqrt_r(r2), qg.x, qg.y);
+                        const Real qq = fma(-uu, uu, Real(1));
+                        if (vj[j] && qq > Real(0)) {
+                            const double x1 = R.pair[ti * MAXT + tj[j]].x1;
+                            acc += omega_dd64(n_i, x1, x1 + 1.0) *
+                                   (double)(omega_win<Real>(sjv[j], q2.core.w) * (-q2.cnt.w * qq * qq));
+                        }
+                    } else {
+                        Real uu = (sqrt_r(r2) - p0.m) * p0.inv_w;
+                        Real qq = Real(1) - uu * uu;
+                        if (vj[j] && qq > Real(0)) acc += (double)(sjv[j] * (-p0.E_a * qq * qq));
+                    }
                 }
-            }
-        } else {
-            for (int cx = 0; cx < nch * EP; ++cx) {
-                const int c = cx / EP, x = e + LPP * (cx % EP);
-                uint4 q = B.nl[(size_t)c * S_ + i];
-                uint32_t wd = (x < 2) ? q.x : (x < 4) ? q.y : (x < 6) ? q.z : q.w;
-                int u = (int)((wd >> (16 * (x & 1))) & 0xffffu);
-                if (R.excl_span > 0) {
-                    if (u & 0x8000) continue;  // excluded pair: no attraction between them
-                }
-                if (u == P.stage_cap) continue;  // padding
-                int src = sm[u], w = wm[u];
-                Real dx = (Real)(xi0 - (X[3 * src] + R.L[0] * (double)unpack_w(w, 0)));
-                Real dy = (Real)(xi1 - (X[3 * src + 1] + R.L[1] * (double)unpack_w(w, 1)));
-                Real dz = (Real)(xi2 - (X[3 * src + 2] + R.L[2] * (double)unpack_w(w, 2)));
-                Real r2 = dx * dx + dy * dy + dz * dz;
-                int tj = B.type[src];
-                const PairR<Real> &q2 = pt[ti * MAXT + tj];
-                if (!q2.attract) continue;
-                Real uu = (sqrt_r(r2) - q2.m) * q2.inv_w;
-                Real qq = Real(1) - uu * uu;
-                if (!(qq > Real(0))) continue;
-                const PairDev &pd = R.pair[ti * MAXT + tj];
-                double sdi = omega_dd64(n_i, pd.x1, pd.x2);
-                Real sj = omega_r<Real>(sA[src].x, q2.x1, q2.x2);
-                acc += sdi * (double)(sj * (-q2.E_a * qq * qq));
             }
         }
         // fixed-order reduction over the lanes of the group
@@ -1627,7 +1672,7 @@ __device__ __forceinline__ void embed_brick(const Buffers &B, const Launch &P, c
 template <class Real, bool MULTI>
 __global__ void k_embed(Buffers B, Launch P, int cur)
 {
-    __shared__ PairR<Real> ptab[EMBED_WAVES][MAXT * MAXT];
+    __shared__ PairM<Real> ptab[EMBED_WAVES][MULTI ? MAXT * MAXT : 1];
     const int wv = threadIdx.x / VBC_WAVE, lane = threadIdx.x % VBC_WAVE;
     int b;
     if (!brick_of_block(P, B, b)) return;
@@ -1647,28 +1692,24 @@ __global__ void k_embed(Buffers B, Launch P, int cur)
     // four lanes each over every wave, so that up to EMBED_WAVES x 16 are in flight
     const bool one = nw <= VBC_WAVE / CHUNK;
     if (one && wv > 0) return;
-    PairR<Real> *pt = ptab[wv];
+    PairM<Real> *pm = ptab[wv];
     if (MULTI) {
-        const int nt = R.ntypes;
-        if (lane < nt * nt) {
-            const int a = lane / nt, c = lane % nt;
-            pt[a * MAXT + c] = pair_r<Real>(R.pair[a * MAXT + c], R.rc2);
-        }
+        load_pairs_m<Real>(R, pm, lane);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     if (one) {
-        embed_brick<CHUNK, Real, MULTI>(B, P, R, pt, b, base, nw, lane, lane / CHUNK, VBC_WAVE / CHUNK,
+        embed_brick<CHUNK, Real, MULTI>(B, P, R, pm, b, base, nw, lane, lane / CHUNK, VBC_WAVE / CHUNK,
                                         t_first, cur);
     } else if (nw <= EMBED_WAVES * (VBC_WAVE / CHUNK)) {
         // up to 32: eight lanes each over every wave, all of them in one round
         constexpr int G = VBC_WAVE / CHUNK;
-        embed_brick<CHUNK, Real, MULTI>(B, P, R, pt, b, base, nw, lane, wv * G + lane / CHUNK,
+        embed_brick<CHUNK, Real, MULTI>(B, P, R, pm, b, base, nw, lane, wv * G + lane / CHUNK,
                                         EMBED_WAVES * G, -1, cur);
     } else {
         constexpr int G = VBC_WAVE / 4;  // groups of four lanes per wave
-        embed_brick<4, Real, MULTI>(B, P, R, pt, b, base, nw, lane, wv * G + lane / 4, EMBED_WAVES * G,
+        embed_brick<4, Real, MULTI>(B, P, R, pm, b, base, nw, lane, wv * G + lane / 4, EMBED_WAVES * G,
                                     -1, cur);
     }
 }
@@ -1707,7 +1748,8 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
     using R4 = typename V4<Real>::t;
     using R2 = typename V2<Real>::t;
     extern __shared__ __align__(32) unsigned char smem[];
-    __shared__ PairR<Real> pt[MAXT * MAXT];
+    __shared__ PairR<Real> pt[1];
+    __shared__ PairM<Real> pm[MULTI ? MAXT * MAXT : 1];
     __shared__ double red[8][1024 / VBC_WAVE];
     __shared__ int moved;
     int b;
@@ -1726,6 +1768,7 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
     const int64_t S_ = P.nslots;
     const int64_t ntot = P.ntot;
     load_pairs<Real>(R, pt);
+    if (MULTI) load_pairs_m<Real>(R, pm, threadIdx.x);
     if (threadIdx.x == 0) moved = 0;
     // every thread reads the header itself (as in the count pass); the staging barrier
     // orders pt and moved
@@ -1789,31 +1832,24 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
             Real r2 = dx * dx + dy * dy + dz * dz;
             Real phr, ep;
             if (MULTI) {
-                int tj = (int)pj.w;
-                const PairR<Real> &q = pt[ti * MAXT + tj];
-                if (!(r2 < q.rc2)) return;
-                R2 saj = ssa[u];
-                Real rinv = rsqrt_r(r2 > Real(1e-30) ? r2 : Real(1e-30));
-                Real rr = r2 * rinv;
-                Real tc = Real(1) - r2 * q.inv_rr2;
-                tc = tc > Real(0) ? tc : Real(0);
-                phr = q.c_r * tc;
-                ep = q.E_r * tc * tc;
-                if (q.attract && !ex) {
-                    Real uu = (rr - q.m) * q.inv_w;
-                    Real qq = Real(1) - uu * uu;
-                    if (qq > Real(0)) {
-                        Real psi = omega_r<Real>(sai.x, q.x1, q.x2) * omega_r<Real>(saj.x, q.x1, q.x2);
-                        ep -= q.E_a * psi * qq * qq;
-                        phr += psi * q.c_a * uu * qq * rinv;
-                    }
-                }
-                Real asum = ex ? Real(0)
-                               : (((R.mask[ti] >> tj) & 1u) ? sai.y : Real(0)) +
-                                     (((R.mask[tj] >> ti) & 1u) ? saj.y : Real(0));
-                Real uc = (rr - q.r_l) * q.inv_dw;
-                uc = uc < Real(0) ? Real(0) : (uc > Real(1) ? Real(1) : uc);
-                phr += asum * q.c_c * uc * (Real(1) - uc * uc) * rinv;
+                // branch-free like the one-type path below, with the pair's constants in three
+                // LDS reads; an excluded pair neither counts nor attracts
+                const PairM<Real> &q = pm[ti * MAXT + (int)pj.w];
+                const R4 qc = q.core, qg = q.geo, qn = q.cnt;
+                const R2 saj = ssa[u];
+                const Real rinv = rsqrt_r(r2 > Real(1e-30) ? r2 : Real(1e-30));
+                const Real rr = r2 * rinv;
+                const Real pr = fmin(fma(r2, qc.y, qc.x), Real(0));
+                const Real uu = fma(rr, qg.x, qg.y);
+                const Real qq = fmax(fma(-uu, uu, Real(1)), Real(0));
+                Real psi = omega_win<Real>(sai.x, qc.w) * omega_win<Real>(saj.x, qc.w);
+                Real asum = fma(qn.x, sai.y, qn.y * saj.y);
+                if (xr && ex) psi = asum = Real(0);
+                const Real uc = clamp01(fma(rr, qg.z, qg.w));
+                const Real g = uc * fma(-uc, uc, Real(1));
+                phr = fma(fma(asum, g, qc.z * psi * uu * qq), rinv, pr);
+                // E_r (1 - r^2/r_r^2)^2 = (V_r'/r)^2 E_r / c_r^2
+                ep = fma(pr * pr, qn.z, -(qn.w * psi * qq * qq));
             } else {
                 // branch-free: beyond every cutoff (and for the padding slot) all three terms
                 // vanish through the clamps.  phi/r = min(c_r + k_r r^2, 0)
