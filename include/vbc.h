@@ -356,7 +356,9 @@ vbc_status vbc_replica_footprint(const vbc_replica_desc *d, const vbc_options *o
                                  vbc_footprint *out);
 
 /* Bytes of device workspace for a pool.  opt->k_max and opt->stage_cap must be set (a pool
- * has no replicas to derive them from); block defaults to 256, brick as for vbc_create. */
+ * has no replicas to derive them from); brick defaults as for vbc_create with replicas of
+ * ordinary density, block to 256 or, from the admission of a replica with fuller bricks on,
+ * to what covers their particles. */
 vbc_status vbc_pool_workspace_size(const vbc_pool_caps *caps, const vbc_options *opt,
                                    size_t *bytes);
 

@@ -53,6 +53,7 @@ struct vbc_handle_s {
     Buffers B;
     vbc_options opt;
     bool pool = false;      // made by vbc_pool_create (admission checks list and staging)
+    bool auto_block = false;  // a pool whose workgroup size follows the admitted replicas
     std::vector<RepDev> reps;   // host copy of every replica slot (n == 0: free)
     std::vector<char> live, has_state, need_full, fvalid;
     Arena a_slot, a_brick, a_cell, a_caller;
@@ -78,6 +79,7 @@ struct vbc_handle_s {
         hipGraphExec_t exec;
     };
     std::vector<GraphEntry> graphs;
+    std::vector<hipGraphExec_t> retired;  // replaced while they may still run: freed after a sync
     hipStream_t cap_stream = nullptr;
     bool use_graphs = true;
     ~vbc_handle_s()
@@ -86,6 +88,7 @@ struct vbc_handle_s {
             for (int e = 0; e < 2; ++e)
                 for (hipEvent_t x : ev[k][e]) (void)hipEventDestroy(x);
         for (auto &g : graphs) (void)hipGraphExecDestroy(g.exec);
+        for (hipGraphExec_t g : retired) (void)hipGraphExecDestroy(g);
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
         for (size_t r = 0; r < up_ev.size(); ++r) {
             if (up_pending[r]) (void)hipEventSynchronize(up_ev[r]);
@@ -100,6 +103,13 @@ struct vbc_handle_s {
 static constexpr int GRAPH_STEPS = 8;
 static constexpr int CALL_GRAPH_MAX = 64;
 static constexpr size_t GRAPH_CACHE = 16;
+
+// Forget the captured step graphs (the launches changed): the next call captures its own.
+static void drop_graphs(vbc_handle h)
+{
+    for (auto &g : h->graphs) (void)hipGraphExecDestroy(g.exec);
+    h->graphs.clear();
+}
 
 // Record the launch(es) of one kernel class between two events when timing is on.
 template <class Fn>
@@ -209,6 +219,25 @@ size_t carve(size_t &off, size_t bytes)
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
 int brick_default(int precision) { return precision == VBC_FP64 ? 3 : 4; }
+
+// Workgroup size of the brick kernels for bricks of `own` particles on average: one thread
+// per own particle of all but rare bricks, since a brick that holds a few more than the
+// workgroup has threads sweeps its lists twice, and in a launch whose workgroups all run at
+// once the slowest brick is the launch's time.  Three standard deviations of a uniform gas
+// above the mean (a step of 50,000 particles in FP64, 127 per brick: 59.3 us with 128
+// threads, 42.9 with 192; 343 per brick: 142 us with 384, 117 with 512), not beyond 512
+// where that covers the mean (455 per brick: a ninth wave would cost the count pass one of
+// its four workgroups per CU), else up to 1024 (811 per brick: 211 us with 512, 158).
+int block_for(double own)
+{
+    const int want = round_up((int)std::ceil(own + 3.0 * std::sqrt(own)), 64);
+    return std::max(128, std::min(own <= 512.0 ? 512 : 1024, want));
+}
+
+// Own particles per brick above which an automatic brick edge of four cells is lowered to
+// three (a melt of density 0.85, 811 per brick of 4^3 cells: 158 us a step with 1024 threads,
+// against 117 with bricks of 3^3 and 512).
+constexpr double OWN_MEAN_MAX = 512.0;
 
 vbc_status check_options(const vbc_options *opt_in, vbc_options &opt)
 {
@@ -831,12 +860,28 @@ static vbc_status plan_set(const vbc_replica_desc *reps, int32_t nrep, const vbc
     plans.resize(nrep);
     double rho_cell_max = 0.0, k_mean_max = 0.0, own_mean_max = 0.0;
     C.nrep = nrep;
-    for (int r = 0; r < nrep; ++r) {
-        st = plan_replica(reps[r], opt.brick, opt.rho_max, plans[r]);
-        if (st != VBC_OK) {
-            g_err = "replica " + std::to_string(r) + ": " + g_err;
-            return st;
+    auto plan_all = [&]() -> vbc_status {
+        for (int r = 0; r < nrep; ++r) {
+            vbc_status e = plan_replica(reps[r], opt.brick, opt.rho_max, plans[r]);
+            if (e != VBC_OK) {
+                g_err = "replica " + std::to_string(r) + ": " + g_err;
+                return e;
+            }
         }
+        return VBC_OK;
+    };
+    st = plan_all();
+    if (st != VBC_OK) return st;
+    if ((!opt_in || !opt_in->brick) && opt.brick > 3) {
+        for (const RepPlan &p : plans) own_mean_max = std::max(own_mean_max, p.own_mean);
+        if (own_mean_max > OWN_MEAN_MAX) {
+            opt.brick = 3;
+            st = plan_all();
+            if (st != VBC_OK) return st;
+        }
+        own_mean_max = 0.0;
+    }
+    for (int r = 0; r < nrep; ++r) {
         const RepPlan &p = plans[r];
         C.ntot += p.R.n;
         C.nslots += p.slots;
@@ -855,7 +900,7 @@ static vbc_status plan_set(const vbc_replica_desc *reps, int32_t nrep, const vbc
         if (C.nslots >= ((int64_t)1 << 31) - 1 || C.nbrick >= (1 << 30) || C.ncell >= (1 << 30))
             return fail(VBC_ERR_ARG, "more than 2^31 slots in total");
     }
-    if (!opt.block) opt.block = std::max(128, std::min(512, round_up((int)std::ceil(own_mean_max), 64)));
+    if (!opt.block) opt.block = block_for(own_mean_max);
     int k_auto = k_max_for(k_mean_max), s_auto = stage_cap_for(rho_cell_max, C.nh_max);
     for (const RepPlan &p : plans) {
         k_auto = std::max(k_auto, p.k_max_auto);
@@ -978,7 +1023,9 @@ vbc_status vbc_pool_create(const vbc_pool_caps *caps, const vbc_options *opt_in,
     Caps C;
     st = check_caps(caps, opt, C);
     if (st != VBC_OK) return st;
-    return make_handle(C, opt, true, d_ws, ws_bytes, s, out);
+    st = make_handle(C, opt, true, d_ws, ws_bytes, s, out);
+    if (st == VBC_OK) (*out)->auto_block = !opt_in || !opt_in->block;
+    return st;
 }
 
 vbc_status vbc_replica_footprint(const vbc_replica_desc *d, const vbc_options *opt_in, vbc_footprint *out)
@@ -1030,6 +1077,13 @@ vbc_status vbc_admit(vbc_handle h, const vbc_replica_desc *d, const double *d_x,
     int32_t r = -1;
     st = place(h, rp, s, &r);
     if (st != VBC_OK) return st;
+    if (h->auto_block && block_for(rp.own_mean) > h->P.block) {
+        // the first replicas of a pool set its workgroup size (it never shrinks, so a stream
+        // of requests recaptures the step graphs once or twice); results do not depend on it
+        h->P.block = h->opt.block = block_for(rp.own_mean);
+        for (auto &g : h->graphs) h->retired.push_back(g.exec);  // other replicas' steps may be running
+        h->graphs.clear();
+    }
     const RepDev &Rp = h->reps[r];
     VBC_TRY(h, launch_set_state(h->B, h->P, h->cur, r, Rp.n, d_x, d_v, d_type, 0, Rp.n, step0, s),
             "set_state");
@@ -1104,8 +1158,8 @@ vbc_status vbc_tune_set(vbc_handle h, const vbc_options *t)
             if (st != VBC_OK) return st;
             h->P.block = t->block;
             h->opt.block = t->block;
-            for (auto &g : h->graphs) (void)hipGraphExecDestroy(g.exec);
-            h->graphs.clear();
+            h->auto_block = false;
+            drop_graphs(h);
         }
     }
     return VBC_OK;
@@ -1277,6 +1331,8 @@ vbc_status vbc_check(vbc_handle h, hipStream_t s, uint32_t *flags_per_replica)
     Range range_("vbc_check");
     if (!h) return fail(VBC_ERR_ARG, "NULL handle");
     VBC_TRY(h, hipStreamSynchronize(s), "sync");
+    for (hipGraphExec_t g : h->retired) (void)hipGraphExecDestroy(g);
+    h->retired.clear();
     std::vector<uint32_t> f(h->P.nrep);
     VBC_TRY(h, hipMemcpy(f.data(), h->B.flags, sizeof(uint32_t) * h->P.nrep, hipMemcpyDeviceToHost),
             "flags readback");
@@ -1527,8 +1583,7 @@ vbc_status vbc_thermo(vbc_handle h, int32_t enable, hipStream_t s)
     if (!h) return fail(VBC_ERR_ARG, "NULL handle");
     if ((enable != 0) != h->thermo) {
         // the step graphs launch the force pass with or without the sums: recapture
-        for (auto &g : h->graphs) (void)hipGraphExecDestroy(g.exec);
-        h->graphs.clear();
+        drop_graphs(h);
     }
     h->thermo = enable != 0;
     VBC_TRY(h, launch_thermo_clear(h->B, h->P.nrep, s), "thermo reset");

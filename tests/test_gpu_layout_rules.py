@@ -1,0 +1,57 @@
+"""The automatic layout: a dense system gets smaller bricks and full-width workgroups and still
+matches the oracle; a pool's workgroup size grows with the admitted replicas, while others
+run, without changing a bit of any trajectory."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_07842_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("N,rho,brick", [(2900, 0.85, 3), (2900, 0.5, 3), (2900, 0.3, 4)])
+def test_automatic_brick_and_block(N, rho, brick):
+    from paper_2609_07842_amd import vbc
+    L, p = W.box_length(N, rho), W.vbc_params(E_a=5.0, f=12.0)
+    x = W.uniform_positions(N, L, seed=3)
+    s = vbc.System(vbc.replica(N, L, p), precision="fp32", rho_max=2.0)
+    o = s.options()
+    cells = int(L / 2.4) ** 3
+    assert o["brick"] == brick and o["block"] % 64 == 0
+    assert o["block"] >= min(512, N / cells * brick ** 3)
+    s.set_state(x)
+    F, e, UW = s.force()
+    s.check()
+    ref = oracle.evaluate(x, L, p)
+    err = np.linalg.norm(F.cpu().numpy() - ref["F"], axis=1).max() / np.linalg.norm(ref["F"], axis=1).max()
+    assert err <= 1e-5
+
+
+def test_pool_block_grows_with_admissions():
+    from paper_2609_07842_amd import vbc
+    sizes = [(400, 0.05), (3000, 0.3), (2900, 0.5)]
+    integ = dict(integrator="langevin", dt=0.005, kT=1.0, gamma=0.1, seed=5)
+    descs = [vbc.replica(n, W.box_length(n, r), W.vbc_params(E_a=4.0, f=3.0), seed=n) for n, r in sizes]
+    opts = dict(k_max=96, stage_cap=2400)
+    fps = [vbc.footprint(d, "fp32", **opts) for d in descs]
+    caps = dict(max_replicas=3, max_types=1, max_particles=sum(n for n, _ in sizes),
+                max_slots=sum(f["slots"] for f in fps), max_bricks=sum(f["bricks"] for f in fps),
+                max_cells=sum(f["cells"] for f in fps), max_bcap=max(f["bcap"] for f in fps), chains=False)
+    out = []
+    for block in (0, 256):
+        pool = vbc.Pool(caps, precision="fp32", block=block, **opts)
+        seen = []
+        for (n, r), d in zip(sizes, descs):
+            pool.admit(d, W.uniform_positions(n, W.box_length(n, r), n), W.maxwell_boltzmann(n, 1.0, n))
+            seen.append(pool.options()["block"])
+            for _ in range(3):
+                pool.step(8, **integ)
+        pool.check()
+        assert seen == sorted(seen) and (seen[-1] > 256 if block == 0 else seen == [256] * 3)
+        x, v = pool.get_state()
+        out.append((x.cpu().numpy(), v.cpu().numpy()))
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
