@@ -17,7 +17,7 @@ def test_automatic_brick_and_block(N, rho, brick):
     from paper_2609_07842_amd import vbc
     L, p = W.box_length(N, rho), W.vbc_params(E_a=5.0, f=12.0)
     x = W.uniform_positions(N, L, seed=3)
-    s = vbc.System(vbc.replica(N, L, p), precision="fp32", rho_max=2.0)
+    s = vbc.System(vbc.replica(N, L, p), precision="fp32")
     o = s.options()
     cells = int(L / 2.4) ** 3
     assert o["brick"] == brick and o["block"] % 64 == 0
@@ -35,7 +35,7 @@ def test_pool_block_grows_with_admissions():
     sizes = [(400, 0.05), (3000, 0.3), (2900, 0.5)]
     integ = dict(integrator="langevin", dt=0.005, kT=1.0, gamma=0.1, seed=5)
     descs = [vbc.replica(n, W.box_length(n, r), W.vbc_params(E_a=4.0, f=3.0), seed=n) for n, r in sizes]
-    opts = dict(k_max=96, stage_cap=2400)
+    opts = dict(k_max=96, stage_cap=2624)
     fps = [vbc.footprint(d, "fp32", **opts) for d in descs]
     caps = dict(max_replicas=3, max_types=1, max_particles=sum(n for n, _ in sizes),
                 max_slots=sum(f["slots"] for f in fps), max_bricks=sum(f["bricks"] for f in fps),
