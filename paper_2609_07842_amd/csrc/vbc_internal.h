@@ -130,6 +130,9 @@ struct Launch {
     int32_t nbrick_tot;
     int32_t b_lo, nb_launch; // bricks one launch covers: [b_lo, b_lo + nb_launch), or
     int32_t list;            // >= 0: the entries of that work list instead
+    int32_t lists;           // over all bricks of several replica slots: a rebuild makes the
+                             // work lists (list 0 of live bricks only for pools) and visits list 1
+    uint32_t due;            // flag bits that make the list kernel build a replica's lists
     int32_t k_max;           // multiple of CHUNK
     int32_t nchunk;          // k_max / CHUNK
     int32_t block;
@@ -186,6 +189,10 @@ hipError_t launch_set_state(const Buffers &B, const Launch &P, int cur, int r, i
 hipError_t launch_get_state(const Buffers &B, const Launch &P, int cur, int r, int64_t nslot,
                             int64_t out_off, int64_t out_stride, double *x, double *v,
                             hipStream_t s);
+hipError_t launch_set_state_all(const Buffers &B, const Launch &P, int cur, const double *x, const double *v,
+                                const int32_t *type, uint64_t step0, hipStream_t s);
+hipError_t launch_get_state_all(const Buffers &B, const Launch &P, int cur, double *x, double *v, hipStream_t s);
+hipError_t launch_full_build_all(const Buffers &B, const Launch &P, int cur, hipStream_t s);
 hipError_t launch_flags(const Buffers &B, int r_lo, int r_n, uint32_t bits, bool set,
                         hipStream_t s);
 hipError_t launch_admit(const Buffers &B, int r, int64_t nthreads, hipStream_t s);

@@ -432,14 +432,11 @@ __device__ __forceinline__ void stage_map4(const Buffers &B, int b, int stage_ca
 // Caller-order input of replica r (element tag at in_off + tag of each stride-in_stride
 // component array) into the live arrays at slot p_off + tag: the unsorted layout that the
 // next full build starts from.
-__global__ void k_set_state(Buffers B, int64_t S_, int cur, int r, int64_t in_off,
-                            int64_t in_stride, const double *__restrict__ x,
-                            const double *__restrict__ v, const int32_t *__restrict__ type,
-                            uint64_t step0)
+__device__ __forceinline__ void put_state(const Buffers &B, const RepDev &R, int64_t S_, int cur, int r,
+                                          int64_t tg, int64_t in_off, int64_t in_stride,
+                                          const double *__restrict__ x, const double *__restrict__ v,
+                                          const int32_t *__restrict__ type, uint64_t step0)
 {
-    const RepDev &R = B.reps[r];
-    int64_t tg = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tg >= R.n) return;
     int64_t i = in_off + tg;
     int64_t d = R.p_off + tg;
     for (int a = 0; a < 3; ++a) {
@@ -455,7 +452,45 @@ __global__ void k_set_state(Buffers B, int64_t S_, int cur, int r, int64_t in_of
     }
 }
 
-// Live state of replica r out in caller order (element out_off + tag).
+__global__ void k_set_state(Buffers B, int64_t S_, int cur, int r, int64_t in_off,
+                            int64_t in_stride, const double *__restrict__ x,
+                            const double *__restrict__ v, const int32_t *__restrict__ type,
+                            uint64_t step0)
+{
+    const RepDev &R = B.reps[r];
+    int64_t tg = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (tg >= R.n) return;
+    put_state(B, R, S_, cur, r, tg, in_off, in_stride, x, v, type, step0);
+}
+
+// Every live replica at once: the workgroup of brick b takes the tags whose unsorted slots
+// fall in the brick's slot range (a replica has at least as many slots as particles).  One
+// launch for all replicas: one for each cost 2.6 us apiece, 2.6 ms for a handle of 1024.
+__global__ void k_set_state_all(Buffers B, int64_t S_, int cur, int64_t in_stride,
+                                const double *__restrict__ x, const double *__restrict__ v,
+                                const int32_t *__restrict__ type, uint64_t step0)
+{
+    const int b = blockIdx.x, r = B.brick_rep[b];
+    if (r < 0) return;
+    const RepDev &R = B.reps[r];
+    const int64_t t0 = (int64_t)(b - R.b_off) * R.bcap, t1 = min(t0 + R.bcap, R.n);
+    for (int64_t tg = t0 + threadIdx.x; tg < t1; tg += blockDim.x)
+        put_state(B, R, S_, cur, r, tg, R.o_off, in_stride, x, v, type, step0);
+}
+
+// Live state of the particle at slot out in caller order (element out_off + tag).
+__device__ __forceinline__ void take_state(const Buffers &B, const RepDev &R, int64_t S_, int cur, int64_t slot,
+                                           int64_t out_off, int64_t out_stride, double *__restrict__ x,
+                                           double *__restrict__ v)
+{
+    int64_t dst = out_off + B.tag[slot];
+    for (int a = 0; a < 3; ++a) {
+        if (x) x[a * out_stride + dst] = wrap1(B.x[cur][3 * slot + a], R.L[a]);
+        if (v) v[a * out_stride + dst] = B.v[a * S_ + slot];
+    }
+}
+
+// Replica r.
 __global__ void k_get_state(Buffers B, int64_t S_, int cur, int r, int64_t out_off,
                             int64_t out_stride, double *__restrict__ x, double *__restrict__ v)
 {
@@ -464,12 +499,20 @@ __global__ void k_get_state(Buffers B, int64_t S_, int cur, int r, int64_t out_o
     if (k >= (int64_t)R.nbrick * R.bcap) return;
     int lb = (int)(k / R.bcap);
     if (k - (int64_t)lb * R.bcap >= B.bcnt[0][R.b_off + lb]) return;
-    int64_t slot = R.p_off + k;
-    int64_t dst = out_off + B.tag[slot];
-    for (int a = 0; a < 3; ++a) {
-        if (x) x[a * out_stride + dst] = wrap1(B.x[cur][3 * slot + a], R.L[a]);
-        if (v) v[a * out_stride + dst] = B.v[a * S_ + slot];
-    }
+    take_state(B, R, S_, cur, R.p_off + k, out_off, out_stride, x, v);
+}
+
+// Every live replica at once, a workgroup per brick (a launch per replica: 4.6 us each, a
+// twelfth of a ten-step call of 32 replicas).
+__global__ void k_get_state_all(Buffers B, int64_t S_, int cur, int64_t out_stride, double *__restrict__ x,
+                                double *__restrict__ v)
+{
+    const int b = blockIdx.x, r = B.brick_rep[b], n = B.bcnt[0][b];
+    if (r < 0) return;
+    const RepDev &R = B.reps[r];
+    const int64_t base = R.p_off + (int64_t)(b - R.b_off) * R.bcap;
+    for (int t = threadIdx.x; t < n; t += blockDim.x)
+        take_state(B, R, S_, cur, base + t, R.o_off, out_stride, x, v);
 }
 
 __global__ void k_flags(Buffers B, int r_lo, int r_n, uint32_t bits, int set)
@@ -478,6 +521,13 @@ __global__ void k_flags(Buffers B, int r_lo, int r_n, uint32_t bits, int set)
     if (r >= r_n) return;
     r += r_lo;
     if (set) B.flags[r] |= bits; else B.flags[r] &= ~bits;
+}
+
+// The replicas that a full build of all bricks has just built are no longer due.
+__global__ void k_full_done(Buffers B, int nrep)
+{
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < nrep && (B.flags[r] & FLAG_FULL)) B.flags[r] &= ~(uint32_t)(VBC_FLAG_REBUILD | FLAG_FULL);
 }
 
 // Rank of a cell in the brick-major order (bricks x-fastest, cells x-fastest inside a
@@ -557,10 +607,15 @@ __global__ void k_stamp(Buffers B, uint32_t mask)
 }
 
 // Work lists of the capacity-wide launches, made on the GPU at the start of every step
-// from the replica table: list 0 = every brick of every live replica, list 1 = the bricks
-// of the replicas whose list is due for an incremental rebuild.  Replica slots in order,
-// bricks in order inside a replica, so consecutive entries are neighbouring bricks.
-__global__ void __launch_bounds__(1024) k_worklist(Buffers B, int nrep)
+// from the replica table: list 0 = every brick of every live replica (pools; a fixed set's
+// bricks are all live, in order, and need no list), list 1 = the bricks of the replicas whose
+// list is due for an incremental rebuild.  Replica slots in order, bricks in order inside a
+// replica, so consecutive entries are neighbouring bricks.  Every workgroup scans the table
+// itself and writes its share of the entries: one workgroup for all took 32 us for 27,648
+// bricks of 1024 replicas and 7.3 us for 6,912 of 32.
+constexpr int WL_PER_GROUP = 2048;  // entries per workgroup
+
+__global__ void __launch_bounds__(1024) k_worklist(Buffers B, int nrep, int first)
 {
     __shared__ int pre[2][MAX_REPLICAS + 1];
     __shared__ int boff[MAX_REPLICAS];
@@ -574,18 +629,17 @@ __global__ void __launch_bounds__(1024) k_worklist(Buffers B, int nrep)
         boff[r] = R.b_off;
     }
     __syncthreads();
-    const int t0 = wave0_exclusive_scan(pre[0], nrep);
-    const int t1 = wave0_exclusive_scan(pre[1], nrep);
-    if (threadIdx.x == 0) {
-        tot[0] = t0;
-        tot[1] = t1;
-        B.wl_n[0] = t0;
-        B.wl_n[1] = t1;
+    for (int l = first; l < 2; ++l) {
+        const int t = wave0_exclusive_scan(pre[l], nrep);
+        if (threadIdx.x == 0) {
+            tot[l] = t;
+            if (blockIdx.x == 0) B.wl_n[l] = t;
+        }
     }
     __syncthreads();
-    for (int l = 0; l < 2; ++l) {
+    for (int l = first; l < 2; ++l) {
         const int T = tot[l];
-        for (int k = threadIdx.x; k < T; k += blockDim.x) {
+        for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < T; k += gridDim.x * blockDim.x) {
             // the last replica whose first entry is <= k (empty entries share their
             // successor's start, so the one found has bricks)
             int lo = 0, hi = nrep - 1;
@@ -680,13 +734,9 @@ __device__ __forceinline__ int local_cell(const RepDev &R, const StageHdr &S, co
     return l[0] + S.e[0] * (l[1] + S.e[1] * l[2]);
 }
 
-// Full build, part 1: bin the unsorted particles of replica r into per-brick buckets.
-__global__ void k_gbin(Buffers B, int64_t S_, int cur, int r)
+// Full build, part 1: bin the unsorted particle tg of replica r into its brick's bucket.
+__device__ __forceinline__ void bin_particle(const Buffers &B, const RepDev &R, int cur, int r, int64_t tg)
 {
-    const RepDev &R = B.reps[r];
-    int64_t tg = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (tg >= R.n) return;
-    if (!(B.flags[r] & FLAG_FULL)) return;
     int64_t d = R.p_off + tg;
     int c[3];
     bool bad = false;
@@ -707,6 +757,25 @@ __global__ void k_gbin(Buffers B, int64_t S_, int cur, int r)
         B.src[R.p_off + (int64_t)lb * R.bcap + idx] = (int32_t)d;
     else
         atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_STAGE_OVERFLOW);
+}
+
+__global__ void k_gbin(Buffers B, int64_t S_, int cur, int r)
+{
+    const RepDev &R = B.reps[r];
+    int64_t tg = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (tg >= R.n) return;
+    if (!(B.flags[r] & FLAG_FULL)) return;
+    bin_particle(B, R, cur, r, tg);
+}
+
+// Every replica with unsorted input at once (workgroups as in k_set_state_all).
+__global__ void k_gbin_all(Buffers B, int cur)
+{
+    const int b = blockIdx.x, r = B.brick_rep[b];
+    if (r < 0 || !(B.flags[r] & FLAG_FULL)) return;
+    const RepDev &R = B.reps[r];
+    const int64_t t0 = (int64_t)(b - R.b_off) * R.bcap, t1 = min(t0 + R.bcap, R.n);
+    for (int64_t tg = t0 + threadIdx.x; tg < t1; tg += blockDim.x) bin_particle(B, R, cur, r, tg);
 }
 
 // Full build, part 2: order each bucket and write the next layout.
@@ -857,7 +926,7 @@ __global__ void NLIST_ATTR k_nlist(Buffers B, Launch P, int cur)
     int b, r;
     const uint32_t fl0 = B.flags[0];  // as in k_resort
     if (!resolve_brick(P, B, b, r)) return;
-    if (!((r == 0 ? fl0 : B.flags[r]) & (VBC_FLAG_REBUILD | FLAG_FULL))) return;
+    if (!((r == 0 ? fl0 : B.flags[r]) & P.due)) return;
     const RepDev &R = B.reps[r];
     int lb = b - R.b_off;
     int nh_cap = (P.nh_max + 3) & ~3;
@@ -1354,7 +1423,9 @@ __device__ __forceinline__ void recount_window(const Buffers &B, const Launch &P
     }
 }
 
+template <int UN>
 __device__ __forceinline__ double replica_sum(const Buffers &B, const RepDev &R);
+template <int UN>
 __device__ __forceinline__ void thermo_add(const Buffers &B, const RepDev &R, int r);
 
 // STATS: also count the ordered pairs inside the interaction cutoff (the pair-evaluation
@@ -1407,7 +1478,7 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
             atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_STAGE_OVERFLOW);
             B.wcnt[b] = 0;
         }
-        if (pend) thermo_add(B, R, r);
+        if (pend) thermo_add<1>(B, R, r);
         return;
     }
     const double *X = B.x[cur];
@@ -1545,7 +1616,7 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
             if (advance) B.step[r] += 1ull;
         }
     }
-    if (pend) thermo_add(B, R, r);
+    if (pend) thermo_add<1>(B, R, r);
 }
 
 // ---------------------------------------------------------------------------
@@ -2014,15 +2085,31 @@ __global__ void k_kick_drift(Buffers B, Launch P, int cur, StepArgs st)
 // The eight sums of replica R's per-brick partial sums, in an order that does not depend on
 // the workgroup's size (the count pass and the closing reduction run it with different
 // sizes): lane l of the first wave adds bricks l, l + 64, ..., then the wave's lanes are
-// added in the fixed order of wave_sum.  Called by the whole workgroup; thread k < 8 gets
-// component k.
+// added in the fixed order of wave_sum, whatever UN, the bricks each lane has in flight (1600
+// bricks take 12.1 us with one, the latency of 25 dependent rounds; the count pass keeps one,
+// to stay within its registers, in a workgroup that is not its last).  Called by the whole
+// workgroup; thread k < 8 gets component k.
+template <int UN>
 __device__ __forceinline__ double replica_sum(const Buffers &B, const RepDev &R)
 {
     __shared__ double red[8];
     if (threadIdx.x < VBC_WAVE) {
         double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int b = threadIdx.x; b < R.nbrick; b += VBC_WAVE)
-            for (int k = 0; k < 8; ++k) acc[k] += B.part[(size_t)(R.b_off + b) * 8 + k];
+        const double *part = B.part + (size_t)R.b_off * 8;
+        for (int b0 = threadIdx.x; b0 < R.nbrick; b0 += UN * VBC_WAVE) {
+            // a brick past the end reads the lane's first one of the round and adds nothing
+            double q[UN][8];
+#pragma unroll
+            for (int j = 0; j < UN; ++j) {
+                const int b = b0 + j * VBC_WAVE < R.nbrick ? b0 + j * VBC_WAVE : b0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) q[j][k] = part[(size_t)b * 8 + k];
+            }
+#pragma unroll
+            for (int j = 0; j < UN; ++j)
+                if (b0 + j * VBC_WAVE < R.nbrick)
+                    for (int k = 0; k < 8; ++k) acc[k] += q[j][k];
+        }
         for (int k = 0; k < 8; ++k) {
             const double v = wave_sum(acc[k]);
             if (threadIdx.x == 0) red[k] = v;
@@ -2037,16 +2124,17 @@ __global__ void k_reduce(Buffers B, int nrep, double *__restrict__ UW)
 {
     int r = blockIdx.x;
     const RepDev &R = B.reps[r];
-    const double s = replica_sum(B, R);
+    const double s = replica_sum<4>(B, R);
     if (threadIdx.x < 8) UW[r * 8 + threadIdx.x] = s;
 }
 
 // A time step's energy and virial of replica r (kept as the last step's) added to its
 // running sums from the per-brick sums its force pass left, and its step count raised by
 // one; the pending mark cleared.  Called by a whole workgroup.
+template <int UN>
 __device__ __forceinline__ void thermo_add(const Buffers &B, const RepDev &R, int r)
 {
-    const double s = replica_sum(B, R);
+    const double s = replica_sum<UN>(B, R);
     if (threadIdx.x < 8) {
         double *T = B.thermo + (size_t)r * THERMO_WORDS;
         T[1 + threadIdx.x] = s;
@@ -2070,7 +2158,7 @@ __global__ void k_thermo_acc(Buffers B, int nrep)
         if (threadIdx.x == 0) B.tpend[r] = 0;
         return;
     }
-    thermo_add(B, R, r);
+    thermo_add<4>(B, R, r);
 }
 
 __global__ void k_thermo_clear(Buffers B, int n)
@@ -2815,6 +2903,19 @@ hipError_t launch_get_state(const Buffers &B, const Launch &P, int cur, int r, i
     return hipGetLastError();
 }
 
+hipError_t launch_set_state_all(const Buffers &B, const Launch &P, int cur, const double *x, const double *v,
+                                const int32_t *type, uint64_t step0, hipStream_t s)
+{
+    k_set_state_all<<<P.nbrick_tot, 256, 0, s>>>(B, P.nslots, cur, P.ntot, x, v, type, step0);
+    return hipGetLastError();
+}
+
+hipError_t launch_get_state_all(const Buffers &B, const Launch &P, int cur, double *x, double *v, hipStream_t s)
+{
+    k_get_state_all<<<P.nbrick_tot, 256, 0, s>>>(B, P.nslots, cur, P.ntot, x, v);
+    return hipGetLastError();
+}
+
 hipError_t launch_flags(const Buffers &B, int r_lo, int r_n, uint32_t bits, bool set,
                         hipStream_t s)
 {
@@ -2853,13 +2954,35 @@ hipError_t launch_full_build(const Buffers &B, const Launch &P, int cur, int r, 
     return hipGetLastError();
 }
 
-// Incremental rebuild of the replicas whose REBUILD flag is set.  A capacity-wide launch
-// first makes the step's work lists and visits only the bricks of those replicas.
+// Full builds of every replica with unsorted input, over all bricks at once.
+hipError_t launch_full_build_all(const Buffers &B, const Launch &P, int cur, hipStream_t s)
+{
+    Launch Q = P;
+    Q.b_lo = 0;
+    Q.nb_launch = P.nbrick_tot;
+    Q.list = -1;
+    Q.due = FLAG_FULL;  // a replica that is only due for a rebuild has no next layout yet
+    tlaunch(k_gbin_all, P.nbrick_tot, 256, 0, s, B, cur);
+    tlaunch(k_gsort, brick_grid(Q.nb_launch), Q.block, sort_bytes(Q), s, B, Q, cur);
+    tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.block, lds_bytes_nlist(Q), s, B, Q, cur);
+    tlaunch(k_full_done, blocks_for(P.nrep, 256), 256, 0, s, B, P.nrep);
+    return hipGetLastError();
+}
+
+static void launch_worklist(const Buffers &B, const Launch &P, hipStream_t s)
+{
+    const int groups = std::min(64, (P.nbrick_tot + WL_PER_GROUP - 1) / WL_PER_GROUP);
+    tlaunch(k_worklist, groups, 1024, 0, s, B, P.nrep, P.list == 0 ? 0 : 1);
+}
+
+// Incremental rebuild of the replicas whose REBUILD flag is set.  A launch over all bricks of
+// several replica slots first makes the step's work lists and visits only the bricks of those
+// replicas.
 hipError_t launch_rebuild(const Buffers &B, const Launch &P, int cur, hipStream_t s)
 {
     Launch Q = P;
-    if (P.list >= 0) {
-        tlaunch(k_worklist, 1, 1024, 0, s, B, P.nrep);
+    if (P.lists) {
+        launch_worklist(B, P, s);
         Q.list = 1;
     }
     tlaunch(k_resort, brick_grid(Q.nb_launch), Q.block, lds_bytes_sort(Q), s, B, Q, cur);
@@ -2971,7 +3094,7 @@ hipError_t launch_reduce(const Buffers &B, const Launch &P, double *UW, hipStrea
 hipError_t launch_kick_drift(const Buffers &B, const Launch &P, int cur, const StepArgs &st,
                              hipStream_t s)
 {
-    if (P.list >= 0) k_worklist<<<1, 1024, 0, s>>>(B, P.nrep);
+    if (P.list == 0) launch_worklist(B, P, s);
     k_kick_drift<<<brick_grid(P.nb_launch), 256, 0, s>>>(B, P, cur, st);
     return hipGetLastError();
 }
