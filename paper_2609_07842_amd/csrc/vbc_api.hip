@@ -61,6 +61,8 @@ struct vbc_handle_s {
     std::vector<hipEvent_t> up_ev;
     std::vector<char> up_pending;
     int cur = 0;            // which position buffer holds the current positions
+    bool maybe_due = false; // steps were taken since the last rebuild launch over all bricks
+    bool replayed = false;  // steps were captured into a caller's graph: they may run unseen
     std::string err;
     // kernel timing (vbc_profile)
     bool prof = false;
@@ -694,20 +696,15 @@ bool all_have_state(vbc_handle h)
 // list) of their own bricks before anything reads their layout.
 // Several of them are built together, over all bricks (a handle of 1024 replicas: 0.2 ms
 // instead of 28 ms for four launches each); one alone over its own bricks only, as when a
-// request enters a running pool.  Returns through fresh whether every live replica was built
-// here, so that no list can be due.
-static vbc_status ensure_layout(vbc_handle h, hipStream_t s, bool *fresh = nullptr)
+// request enters a running pool.
+static vbc_status ensure_layout(vbc_handle h, hipStream_t s)
 {
-    int pending = 0, live = 0, one = -1;
-    for (int r = 0; r < h->P.nrep; ++r) {
-        if (!h->live[r]) continue;
-        ++live;
-        if (h->need_full[r]) {
+    int pending = 0, one = -1;
+    for (int r = 0; r < h->P.nrep; ++r)
+        if (h->live[r] && h->need_full[r]) {
             ++pending;
             one = r;
         }
-    }
-    if (fresh) *fresh = pending > 0 && pending == live;
     if (!pending) return VBC_OK;
     if (pending == 1) {
         const RepDev &R = h->reps[one];
@@ -733,6 +730,25 @@ static vbc_status ensure_layout(vbc_handle h, hipStream_t s, bool *fresh = nullp
         if (_st != VBC_OK) return _st;            \
     } while (0)
 
+// The rebuild kernels before a pass over the current positions.  Without steps since they last
+// ran no list can be due, and a fixed set leaves the two idle launches (10 us) out; a pool's
+// passes need the work list they make, and a call being captured may be replayed after steps.
+static bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &st);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
+static hipError_t rebuild_if_due(vbc_handle h, hipStream_t s)
+{
+    if (!h->maybe_due && !h->replayed && h->P.list < 0 && !capturing(s)) return hipSuccess;
+    const hipError_t e = timed(h, VBC_K_BUILD, s, [&] { return launch_rebuild(h->B, h->P, h->cur, s); });
+    if (e == hipSuccess) h->maybe_due = false;
+    return e;
+}
+
 static StepArgs no_step()
 {
     StepArgs st;
@@ -743,12 +759,10 @@ static StepArgs no_step()
 // count, embed and force of the current positions into Fst (and the optional outputs),
 // over the bricks that Q covers
 static vbc_status eval_forces(vbc_handle h, const Launch &Q, bool thermo, const StepArgs &st,
-                              double *d_F, double *d_e, bool fresh, hipStream_t s)
+                              double *d_F, double *d_e, hipStream_t s)
 {
-    // lists built by this call's full builds are not due (unless a pool's passes need the work
-    // list of live bricks, which the rebuild makes)
-    if (!fresh || Q.list == 0)
-        VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_rebuild(h->B, Q, h->cur, s); }), "rebuild");
+    if (Q.nb_launch == h->P.nb_launch) VBC_TRY(h, rebuild_if_due(h, s), "rebuild");
+    else VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_rebuild(h->B, Q, h->cur, s); }), "rebuild");
     VBC_TRY(h, timed(h, VBC_K_COUNT, s, [&] { return launch_count(h->B, Q, h->cur, nullptr, 0, true, s); }), "count");
     VBC_TRY(h, timed(h, VBC_K_EMBED, s, [&] { return launch_embed(h->B, Q, h->cur, s); }), "embed");
     VBC_TRY(h, timed(h, VBC_K_FORCE, s, [&] {
@@ -760,7 +774,7 @@ static vbc_status eval_forces(vbc_handle h, const Launch &Q, bool thermo, const 
 
 // Forces for the replicas that have none stored yet: all bricks at once when no live
 // replica has them, else replica by replica so that the others are left untouched.
-static vbc_status eval_missing(vbc_handle h, const StepArgs &st, bool fresh, hipStream_t s)
+static vbc_status eval_missing(vbc_handle h, const StepArgs &st, hipStream_t s)
 {
     int missing = 0, live = 0;
     for (int r = 0; r < h->P.nrep; ++r)
@@ -770,12 +784,12 @@ static vbc_status eval_missing(vbc_handle h, const StepArgs &st, bool fresh, hip
         }
     if (!missing) return VBC_OK;
     if (missing == live) {
-        vbc_status st2 = eval_forces(h, h->P, false, st, nullptr, nullptr, fresh, s);
+        vbc_status st2 = eval_forces(h, h->P, false, st, nullptr, nullptr, s);
         if (st2 != VBC_OK) return st2;
     } else {
         for (int r = 0; r < h->P.nrep; ++r) {
             if (!h->live[r] || h->fvalid[r]) continue;
-            vbc_status st2 = eval_forces(h, restrict_to(h->P, h->reps[r]), false, st, nullptr, nullptr, fresh, s);
+            vbc_status st2 = eval_forces(h, restrict_to(h->P, h->reps[r]), false, st, nullptr, nullptr, s);
             if (st2 != VBC_OK) return st2;
         }
     }
@@ -1264,7 +1278,7 @@ vbc_status vbc_count(vbc_handle h, double *d_n, hipStream_t s)
     if (!h) return fail(VBC_ERR_ARG, "NULL handle");
     VBC_NEED_STATE(h);
     VBC_LAYOUT(h, s);
-    VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_rebuild(h->B, h->P, h->cur, s); }), "rebuild");
+    VBC_TRY(h, rebuild_if_due(h, s), "rebuild");
     VBC_TRY(h, timed(h, VBC_K_COUNT, s, [&] { return launch_count(h->B, h->P, h->cur, d_n, 0, true, s); }), "count");
     return VBC_OK;
 }
@@ -1274,11 +1288,9 @@ vbc_status vbc_force(vbc_handle h, double *d_F, double *d_e, double *d_UW, hipSt
     Range range_("vbc_force");
     if (!h) return fail(VBC_ERR_ARG, "NULL handle");
     VBC_NEED_STATE(h);
-    bool fresh = false;
-    vbc_status st = ensure_layout(h, s, &fresh);
-    if (st != VBC_OK) return st;
+    VBC_LAYOUT(h, s);
     bool thermo = d_e || d_UW;
-    st = eval_forces(h, h->P, thermo, no_step(), d_F, d_e, fresh, s);
+    vbc_status st = eval_forces(h, h->P, thermo, no_step(), d_F, d_e, s);
     if (st != VBC_OK) return st;
     if (d_UW)
         VBC_TRY(h, timed(h, VBC_K_REDUCE, s, [&] { return launch_reduce(h->B, h->P, d_UW, s); }),
@@ -1334,12 +1346,12 @@ vbc_status vbc_step(vbc_handle h, int32_t nsteps, const vbc_integrator *it, hipS
         if (r0 != VBC_OK) return r0;
     }
     if (nsteps == 0) return VBC_OK;
-    bool fresh = false;
-    vbc_status r = ensure_layout(h, s, &fresh);
-    if (r != VBC_OK) return r;
+    VBC_LAYOUT(h, s);
     const StepArgs st = step_args(it);
-    r = eval_missing(h, st, fresh, s);
+    vbc_status r = eval_missing(h, st, s);
     if (r != VBC_OK) return r;
+    h->maybe_due = true;
+    if (!h->replayed && capturing(s)) h->replayed = true;
     const bool graphs = h->use_graphs && !h->prof;
     if (graphs && nsteps <= CALL_GRAPH_MAX) {
         // the whole call as one graph launch
@@ -1428,7 +1440,7 @@ vbc_status vbc_observables(vbc_handle h, int32_t *d_z, int32_t *d_pen, int64_t *
     if (!h) return fail(VBC_ERR_ARG, "NULL handle");
     VBC_NEED_STATE(h);
     VBC_LAYOUT(h, s);
-    VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_rebuild(h->B, h->P, h->cur, s); }), "rebuild");
+    VBC_TRY(h, rebuild_if_due(h, s), "rebuild");
     VBC_TRY(h, launch_observe(h->B, h->P, h->cur, d_z, d_pen, d_sums, s), "observables");
     return VBC_OK;
 }
@@ -1454,7 +1466,7 @@ vbc_status vbc_clusters(vbc_handle h, void *d_scratch, size_t scratch_bytes, int
         return hfail(h, VBC_ERR_ARG, "hist_len must be 1..2^24, and 2 x slots x hist_len below 2^31, when d_hist is given");
     VBC_NEED_STATE(h);
     VBC_LAYOUT(h, s);
-    VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_rebuild(h->B, h->P, h->cur, s); }), "rebuild");
+    VBC_TRY(h, rebuild_if_due(h, s), "rebuild");
     const size_t a = cluster_array_bytes(h->P);
     char *base = (char *)d_scratch;
     ClusterWork W;
@@ -1542,7 +1554,7 @@ vbc_status vbc_bond_track(vbc_handle h, void *d_state, size_t state_bytes, int32
     if (d_hist && bin_steps < 1) return hfail(h, VBC_ERR_ARG, "bin_steps must be >= 1");
     VBC_NEED_STATE(h);
     VBC_LAYOUT(h, s);
-    VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_rebuild(h->B, h->P, h->cur, s); }), "rebuild");
+    VBC_TRY(h, rebuild_if_due(h, s), "rebuild");
     const size_t n = (size_t)h->P.ntot;
     char *base = (char *)d_state;
     BondTrack T;

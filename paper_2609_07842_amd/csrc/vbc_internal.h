@@ -218,11 +218,13 @@ hipError_t launch_observe(const Buffers &B, const Launch &P, int cur, int32_t *z
 
 // Scratch of the cluster analysis: five int32 arrays over the slots.
 struct ClusterWork {
-    int32_t *parent;  // union-find forest; after counting, the root of every particle
-    int32_t *size;    // particles per cluster (at the root)
-    uint32_t *ends;   // bond ends per cluster (twice its bonds)
-    int32_t *mintag;  // smallest caller tag per cluster
-    int32_t *z;       // bonds of every particle
+    int32_t *parent;  // union-find forest
+    int32_t *size;    // particles per component (at a brick-local component's root, 0 elsewhere),
+                      // after counting per cluster (at its root)
+    uint32_t *ends;   // bond ends, likewise (twice the bonds)
+    int32_t *mintag;  // smallest caller tag, likewise
+    int32_t *z;       // bonds of every particle; then, at a brick's first slot, the number of its
+                      // bonds into neighbouring bricks
 };
 // State of the bond tracker, by caller index: partner count, then M partner tags and M
 // birth steps per particle.

@@ -358,18 +358,8 @@ __device__ __forceinline__ void pass_header(const RepDev &R, const Buffers &B, i
     S.overflow = S.total > stage_cap;
 }
 
-// Call fn(staged_slot, source_slot, packed_shift) for every particle staged by brick b,
-// from the staging map the list build recorded: one coalesced read, no cell-table walk.
-template <class F>
-__device__ __forceinline__ void stage_map(const Buffers &B, int b, int stage_cap,
-                                          const StageHdr &S, F &&fn)
-{
-    const int32_t *sm = B.smap + (size_t)b * stage_cap;
-    const uint8_t *wm = B.wmap + (size_t)b * stage_cap;
-    for (int t = threadIdx.x; t < S.total; t += blockDim.x) fn(t, sm[t], (int)wm[t]);
-}
-
-// stage_map with four staged particles per thread at a time: the map reads of all four go
+// Every particle staged by brick b, from the staging map the list build recorded (one
+// coalesced read, no cell-table walk), four per thread at a time: the map reads of all four go
 // out first, then fn(staged_slot, source_slot, packed_shift, valid) for each; fn must do
 // its own loads unconditionally (the indices are clamped into the staging) and guard only
 // its stores with valid, so that the gathers of the four overlap.
@@ -1005,6 +995,7 @@ __global__ void NLIST_ATTR k_nlist(Buffers B, Launch P, int cur)
                 const int t = off + k, src = src0 + k;
                 sm[t] = src;
                 wm[t] = (uint8_t)w;
+                if (S.n_own == 0) continue;  // only the re-sort reads an empty brick's staging
                 float4 p;
                 p.x = (float)((B.xs[3 * src] + R.L[0] * (double)unpack_w(w, 0)) - S.O[0]);
                 p.y = (float)((B.xs[3 * src + 1] + R.L[1] * (double)unpack_w(w, 1)) - S.O[1]);
@@ -1482,7 +1473,8 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
         return;
     }
     const double *X = B.x[cur];
-    stage_map4(B, b, P.stage_cap, S, mf, [&](int t, int src, int w, bool ok) {
+    // an empty brick stages nothing (many small replicas; a single one has few)
+    if (ONE || S.n_own > 0) stage_map4(B, b, P.stage_cap, S, mf, [&](int t, int src, int w, bool ok) {
         const R4 p = local_pos<Real>(R, S, X, S_, src, w, MULTI ? B.type[src] : 0);
         if (ok) {
             if (SOA) {
@@ -1854,7 +1846,7 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
     }
     const double *X = B.x[cur];
     const Real cc0 = pair_r<Real>(R.pair[0], R.rc2).c_c;
-    stage_map4(B, b, P.stage_cap, S, mf, [&](int t, int src, int w, bool ok) {
+    if (ONE || S.n_own > 0) stage_map4(B, b, P.stage_cap, S, mf, [&](int t, int src, int w, bool ok) {
         R4 p = local_pos<Real>(R, S, X, S_, src, w, MULTI ? B.type[src] : 0);
         const R2 sa = sA[src];
         if (!MULTI) p.w = sa.x;
@@ -2228,17 +2220,54 @@ __device__ __forceinline__ double obs_r2(const RepDev &R, const double *__restri
     return (d[0] * d[0] + d[1] * d[1]) + d[2] * d[2];
 }
 
-// Brick-local FP32 positions (type in w) of every particle the brick staged at the last
-// list build, and the dummy slot far away; optionally their slots.  All threads call this.
-__device__ __forceinline__ void stage_bonds(const Buffers &B, const Launch &P, const RepDev &R,
-                                            const StageHdr &S, int b, const double *X, float4 *spos,
-                                            int32_t *ssrc)
+// Brick-local FP32 positions of every particle the brick staged at the last list build, and
+// the dummy slot far away, in LDS as (x, y) | z | type, the types only with several of them:
+// 12 bytes per particle with one type, which lets a third workgroup of a layout sized for
+// condensation share the CU (the bond sweep of 500,000 particles: 102.6 -> 69.4 us together with
+// reading a bond's slot only where it is needed).
+struct Staged {
+    float2 *xy;
+    float *z;
+    int32_t *type;  // several types only
+};
+
+__device__ __forceinline__ Staged carve_staged(unsigned char *smem, int stage_cap)
 {
-    stage_map(B, b, P.stage_cap, S, [&](int t, int src, int w) {
-        spos[t] = local_pos<float>(R, S, X, P.nslots, src, w, B.type[src]);
-        if (ssrc) ssrc[t] = src;
+    Staged T;
+    T.xy = (float2 *)smem;
+    T.z = (float *)(T.xy + stage_cap + 1);
+    T.type = (int32_t *)(T.z + stage_cap + 1);
+    return T;
+}
+
+// All threads call this.
+template <bool MULTI>
+__device__ __forceinline__ void stage_bonds(const Buffers &B, const Launch &P, const RepDev &R,
+                                            const StageHdr &S, int b, const double *X, const Staged &T,
+                                            const MapFirst &first)
+{
+    stage_map4(B, b, P.stage_cap, S, first, [&](int t, int src, int w, bool ok) {
+        const float4 p = local_pos<float>(R, S, X, P.nslots, src, w, 0);
+        const int ty = MULTI ? B.type[src] : 0;
+        if (ok) {
+            T.xy[t] = make_float2(p.x, p.y);
+            T.z[t] = p.z;
+            if (MULTI) T.type[t] = ty;
+        }
     });
-    if (threadIdx.x == 0) spos[P.stage_cap] = dummy_pos<float4>();
+    if (threadIdx.x == 0) {
+        T.xy[P.stage_cap] = make_float2(1.0e6f, 1.0e6f);
+        T.z[P.stage_cap] = 1.0e6f;
+        if (MULTI) T.type[P.stage_cap] = 0;
+    }
+}
+
+// Squared distance of staged particle u from (a, az).
+__device__ __forceinline__ float staged_r2(const Staged &T, const float2 &a, float az, int u)
+{
+    const float2 q = T.xy[u];
+    const float dx = a.x - q.x, dy = a.y - q.y, dz = az - T.z[u];
+    return dx * dx + dy * dy + dz * dz;
 }
 
 // Threshold r^2 < c2 decided on the staged FP32 distance outside a band around c2 that is
@@ -2254,20 +2283,17 @@ __device__ __forceinline__ Band make_band(double c2)
     return Band{(float)(c2 * (1.0 - 2e-5) - 1e-4), (float)(c2 * (1.0 + 2e-5) + 1e-4), c2};
 }
 
+// r2f below the band is inside, above it outside; slot() (the neighbour's slot, read only in
+// the band) decides the rest.
+template <class F>
 __device__ __forceinline__ bool within(float r2f, const Band &bd, const RepDev &R, const double *X,
-                                       int64_t S_, int64_t i, int64_t j)
+                                       int64_t S_, int64_t i, F &&slot)
 {
     if (r2f < bd.lo) return true;
     if (!(r2f < bd.hi)) return false;
     double wi[3];
     for (int a = 0; a < 3; ++a) wi[a] = wrap1(X[3 * i + a], R.L[a]);
-    return obs_r2(R, X, S_, wi, j) < bd.c2;
-}
-
-__device__ __forceinline__ float staged_r2(const float4 &a, const float4 &b)
-{
-    const float dx = a.x - b.x, dy = a.y - b.y, dz = a.z - b.z;
-    return dx * dx + dy * dy + dz * dz;
+    return obs_r2(R, X, S_, wi, slot()) < bd.c2;
 }
 
 // Observables of valency control: for every own particle the number of list neighbours
@@ -2275,48 +2301,50 @@ __device__ __forceinline__ float staged_r2(const float4 &a, const float4 &b)
 // decided by `within` (exactly as the plain FP64 definition on the wrapped positions), plus
 // per-replica sums {sum z, #(z > f), sum p}.  The list holds every pair within the
 // interaction cutoff.
+template <bool MULTI>
 __global__ void k_observe(Buffers B, Launch P, int cur, int32_t *__restrict__ z_out,
                           int32_t *__restrict__ pen_out, int64_t *__restrict__ sums)
 {
-    extern __shared__ __align__(16) float4 spos[];  // [stage_cap + 1]
-    __shared__ StageHdr S;
+    extern __shared__ __align__(16) unsigned char smem[];  // Staged
     __shared__ unsigned long long tot[3];
-    int b, r;
-    if (!resolve_brick(P, B, b, r)) return;
+    int b;
+    if (!brick_of_block(P, B, b)) return;
+    const MapFirst mf = map_prefetch(B, b, P.stage_cap);
+    const int r = B.brick_rep[b];
+    if (r < 0) return;
     const RepDev &R = B.reps[r];
     const int lb = b - R.b_off;
-    if (threadIdx.x == 0) {
-        pass_header(R, B, b, lb, P.stage_cap, S);
-        tot[0] = tot[1] = tot[2] = 0ull;
-    }
-    __syncthreads();
+    if (threadIdx.x == 0) tot[0] = tot[1] = tot[2] = 0ull;
+    StageHdr S;
+    pass_header(R, B, b, lb, P.stage_cap, S);
     if (S.overflow) return;
     const int64_t S_ = P.nslots;
     const double *X = B.x[cur];
     const int32_t *sm = B.smap + (size_t)b * P.stage_cap;
-    stage_bonds(B, P, R, S, b, X, spos, nullptr);
+    const Staged T = carve_staged(smem, P.stage_cap);
+    stage_bonds<MULTI>(B, P, R, S, b, X, T, mf);
     __syncthreads();
-    const bool one = R.ntypes == 1;
+    const bool xr = R.excl_span > 0;
     const Band ba0 = make_band(R.pair[0].ra2), br0 = make_band(R.pair[0].rr2);
     unsigned long long zs = 0, over = 0, ps = 0;
     for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
         const int64_t i = S.base + t;
-        const float4 pi = spos[t];
-        const int ti = (int)pi.w;
+        const float2 pi = T.xy[t];
+        const float zi = T.z[t];
+        const int ti = MULTI ? T.type[t] : 0;
         int z = 0, p = 0;
         for_each_neighbour(B.nl, S_, i, B.nn[i], [&](int u) {
-            if (R.excl_span > 0) u &= 0x7fff;
-            const float4 pj = spos[u];
-            const float r2f = staged_r2(pi, pj);
+            if (MULTI && xr) u &= 0x7fff;
+            const float r2f = staged_r2(T, pi, zi, u);
             Band ba = ba0, br = br0;
-            if (!one) {
-                const PairDev &pd = R.pair[ti * MAXT + (int)pj.w];
+            if (MULTI) {
+                const PairDev &pd = R.pair[ti * MAXT + T.type[u]];
                 ba = make_band(pd.ra2);
                 br = make_band(pd.rr2);
             }
             if (!(r2f < ba.hi) && !(r2f < br.hi)) return;  // beyond both (and the padding)
-            z += within(r2f, ba, R, X, S_, i, sm[u]) ? 1 : 0;
-            p += within(r2f, br, R, X, S_, i, sm[u]) ? 1 : 0;
+            z += within(r2f, ba, R, X, S_, i, [&] { return (int64_t)sm[u]; }) ? 1 : 0;
+            p += within(r2f, br, R, X, S_, i, [&] { return (int64_t)sm[u]; }) ? 1 : 0;
         });
         const int32_t tg = B.tag[i];
         if (z_out) z_out[R.o_off + tg] = z;
@@ -2386,17 +2414,6 @@ __device__ __forceinline__ void cc_union(int32_t *parent, int32_t a, int32_t b)
     }
 }
 
-__global__ void k_cc_init(ClusterWork W, int64_t S_)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < S_; i += (int64_t)gridDim.x * blockDim.x) {
-        W.parent[i] = (int32_t)i;
-        W.size[i] = 0;
-        W.ends[i] = 0u;
-        W.mintag[i] = INT32_MAX;
-        W.z[i] = 0;
-    }
-}
-
 // LDS union-find over the own particles of one brick (their staged index is their index in
 // the brick), with the same smaller-root rule.
 __device__ __forceinline__ int32_t lcc_find(int32_t *lp, int32_t x)
@@ -2428,241 +2445,332 @@ __device__ __forceinline__ void lcc_union(int32_t *lp, int32_t a, int32_t b)
     }
 }
 
+// Bonds that leave a brick, as (own slot, slot in the neighbouring brick) with the smaller
+// slot first, recorded by the sweep of the bonds in the brick's share of the next layout's
+// positions (free between list builds): up to three per slot.
+__device__ __forceinline__ int2 *cross_bonds(const Buffers &B, int64_t base) { return (int2 *)(B.xs + 3 * base); }
+__device__ __forceinline__ int cross_cap(const RepDev &R) { return 3 * R.bcap; }
+
 // Bonds of every own particle (the z_i criterion of the observables) from its list.  Bonds
-// between two own particles of the brick are joined in LDS first; the forest then starts
-// from the brick's local components, each a star under its smallest slot.
-__global__ void k_cc_local(Buffers B, Launch P, int cur, ClusterWork W)
+// between two own particles of the brick are joined in LDS first; the forest then starts from
+// the brick's local components, each a star under its smallest slot, with the component's
+// size, bond ends and smallest tag summed in LDS at that slot (size 0 marks the others).
+// Bonds that leave the brick are recorded for the next kernel, so that the lists are swept
+// once, not twice.  Also clears the statistics that the labelling adds to.
+template <bool MULTI>
+__global__ void k_cc_local(Buffers B, Launch P, int cur, ClusterWork W, int64_t *__restrict__ stats,
+                           int64_t *__restrict__ hist, int64_t nhist)
 {
-    extern __shared__ __align__(16) float4 spos[];  // [stage_cap + 1], then lp[bcap]
-    __shared__ StageHdr S;
-    int b, r;
-    if (!resolve_brick(P, B, b, r)) return;
+    extern __shared__ __align__(16) unsigned char smem[];  // Staged, then lp[bcap]
+    __shared__ int ncross;
+    const int64_t g0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gn = (int64_t)gridDim.x * blockDim.x;
+    if (stats)
+        for (int64_t k = g0; k < 5 * (int64_t)P.nrep; k += gn) stats[k] = 0;
+    if (hist)
+        for (int64_t k = g0; k < nhist; k += gn) hist[k] = 0;
+    int b;
+    if (!brick_of_block(P, B, b)) return;
+    const MapFirst mf = map_prefetch(B, b, P.stage_cap);
+    const int r = B.brick_rep[b];
+    if (r < 0) return;
     const RepDev &R = B.reps[r];
     const int lb = b - R.b_off;
-    if (threadIdx.x == 0) pass_header(R, B, b, lb, P.stage_cap, S);
-    __syncthreads();
-    if (S.overflow) return;
+    if (threadIdx.x == 0) ncross = 0;
+    StageHdr S;
+    pass_header(R, B, b, lb, P.stage_cap, S);
+    if (S.overflow) {
+        // no lists: its particles stay single, uncounted, and may be joined from outside
+        for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
+            const int64_t i = S.base + t;
+            W.parent[i] = (int32_t)i;
+            W.size[i] = 0;
+            W.ends[i] = 0u;
+            W.mintag[i] = INT32_MAX;
+        }
+        return;
+    }
     const int64_t S_ = P.nslots;
     const double *X = B.x[cur];
     const int32_t *sm = B.smap + (size_t)b * P.stage_cap;
-    int32_t *lp = (int32_t *)(spos + P.stage_cap + 1);
-    stage_bonds(B, P, R, S, b, X, spos, nullptr);
+    const Staged T = carve_staged(smem, P.stage_cap);
+    int32_t *lp = T.type + (MULTI ? P.stage_cap + 1 : 0);
+    stage_bonds<MULTI>(B, P, R, S, b, X, T, mf);
     for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) lp[t] = t;
     __syncthreads();
-    const bool one = R.ntypes == 1;
+    const bool xr = R.excl_span > 0;
     const Band ba0 = make_band(R.pair[0].ra2);
+    int2 *cross = cross_bonds(B, S.base);
+    const int cap = cross_cap(R);
     for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
         const int64_t i = S.base + t;
-        const float4 pi = spos[t];
-        const int ti = (int)pi.w;
+        const float2 pi = T.xy[t];
+        const float zi = T.z[t];
+        const int ti = MULTI ? T.type[t] : 0;
         int z = 0;
         for_each_neighbour(B.nl, S_, i, B.nn[i], [&](int u) {
-            if (R.excl_span > 0) u &= 0x7fff;
-            const float4 pj = spos[u];
-            const float r2f = staged_r2(pi, pj);
-            const Band ba = one ? ba0 : make_band(R.pair[ti * MAXT + (int)pj.w].ra2);
+            if (MULTI && xr) u &= 0x7fff;
+            const float r2f = staged_r2(T, pi, zi, u);
+            const Band ba = MULTI ? make_band(R.pair[ti * MAXT + T.type[u]].ra2) : ba0;
             if (!(r2f < ba.hi)) return;  // also the padding
-            if (!within(r2f, ba, R, X, S_, i, sm[u])) return;
+            if (!within(r2f, ba, R, X, S_, i, [&] { return (int64_t)sm[u]; })) return;
             ++z;
-            if (u < S.n_own && u > t) lcc_union(lp, t, u);
+            if (u < S.n_own) {
+                if (u > t) lcc_union(lp, t, u);
+            } else {
+                const int j = sm[u];
+                if (j > (int)i) {
+                    const int k = atomicAdd(&ncross, 1);
+                    if (k < cap) cross[k] = make_int2((int)i, j);
+                }
+            }
         });
         W.z[i] = z;
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x)
-        W.parent[S.base + t] = (int32_t)(S.base + lcc_find(lp, t));
+    // the staged positions are no longer needed: their space takes the components' sums
+    int32_t *csize = (int32_t *)smem, *cends = csize + S.n_own, *cmin = cends + S.n_own;
+    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
+        csize[t] = cends[t] = 0;
+        cmin[t] = INT32_MAX;
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
+        const int64_t i = S.base + t;
+        const int root = lcc_find(lp, t);
+        W.parent[i] = (int32_t)(S.base + root);
+        atomicAdd(csize + root, 1);
+        const int z = W.z[i];  // written by this thread
+        if (z) atomicAdd(cends + root, z);
+        atomicMin(cmin + root, B.tag[i]);
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
+        const int64_t i = S.base + t;
+        W.size[i] = csize[t];
+        W.ends[i] = (uint32_t)cends[t];
+        W.mintag[i] = cmin[t];
+    }
+    if (threadIdx.x == 0) W.z[S.base] = ncross;  // bond counts are summed: their first word counts these
 }
 
-// Bonds that leave the brick join the global forest (each once, from its smaller slot).  A
-// bond is taken between the current parents of its ends (ancestors, so in the same clusters),
-// and a workgroup joins each distinct pair of them once: a condensed brick has hundreds of
-// bonds into a few dozen neighbouring components.  The set of pairs lives in LDS with open
-// addressing; when it is full the join simply runs.
+// Bonds that leave the brick join the global forest.  A bond is taken between the current
+// parents of its ends (ancestors, so in the same clusters), and a workgroup joins each
+// distinct pair of them once: a condensed brick has hundreds of bonds into a few dozen
+// neighbouring components.  The set of pairs lives in LDS with open addressing; when it is
+// full the join simply runs.  A brick with more such bonds than were recorded finds them
+// again from its lists, by the plain FP64 definition.
 constexpr int CC_SET = 512;
 
 __global__ void k_cc_hook(Buffers B, Launch P, int cur, ClusterWork W)
 {
-    extern __shared__ __align__(16) float4 spos[];  // [stage_cap + 1], ssrc[stage_cap], set
-    __shared__ StageHdr S;
+    __shared__ unsigned long long set[CC_SET];
     int b, r;
     if (!resolve_brick(P, B, b, r)) return;
     const RepDev &R = B.reps[r];
-    const int lb = b - R.b_off;
-    if (threadIdx.x == 0) pass_header(R, B, b, lb, P.stage_cap, S);
-    __syncthreads();
-    if (S.overflow) return;
-    const int64_t S_ = P.nslots;
-    const double *X = B.x[cur];
-    int32_t *ssrc = (int32_t *)(spos + P.stage_cap + 1);
-    unsigned long long *set =
-        (unsigned long long *)(((uintptr_t)(ssrc + P.stage_cap) + 15) & ~(uintptr_t)15);
-    stage_bonds(B, P, R, S, b, X, spos, ssrc);
+    const int lb = b - R.b_off, n_own = B.bcnt[0][b];
+    if (n_own == 0 || B.stotal[b] > P.stage_cap) return;
+    const int64_t base = R.p_off + (int64_t)lb * R.bcap;
+    const int nc = W.z[base];
     for (int k = threadIdx.x; k < CC_SET; k += blockDim.x) set[k] = ~0ull;
     __syncthreads();
-    const bool one = R.ntypes == 1;
-    const Band ba0 = make_band(R.pair[0].ra2);
-    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
-        const int64_t i = S.base + t;
-        if (W.z[i] == 0) continue;
-        const float4 pi = spos[t];
-        const int ti = (int)pi.w;
-        for_each_neighbour(B.nl, S_, i, B.nn[i], [&](int u) {
+    auto join = [&](int i, int j) {
+        int32_t pa = cc_ld(W.parent + i), pb = cc_ld(W.parent + j);
+        if (pa == pb) return;
+        if (pa > pb) {
+            const int32_t tmp = pa;
+            pa = pb;
+            pb = tmp;
+        }
+        const unsigned long long key = ((unsigned long long)(uint32_t)pa << 32) | (uint32_t)pb;
+        unsigned h = (unsigned)((key * 0x9E3779B97F4A7C15ull) >> 55) & (CC_SET - 1);
+        for (int probe = 0; probe < 16; ++probe) {
+            const unsigned long long prev = atomicCAS(set + h, ~0ull, key);
+            if (prev == key) return;  // this pair is joined already
+            if (prev == ~0ull) break;  // first of its pair
+            h = (h + 1) & (CC_SET - 1);
+        }
+        cc_union(W.parent, pa, pb);
+    };
+    if (nc <= cross_cap(R)) {
+        const int2 *cross = cross_bonds(B, base);
+        for (int k = threadIdx.x; k < nc; k += blockDim.x) join(cross[k].x, cross[k].y);
+        return;
+    }
+    const double *X = B.x[cur];
+    const int32_t *sm = B.smap + (size_t)b * P.stage_cap;
+    for (int t = threadIdx.x; t < n_own; t += blockDim.x) {
+        const int64_t i = base + t;
+        const int ti = B.type[i];
+        double wi[3];
+        for (int a = 0; a < 3; ++a) wi[a] = wrap1(X[3 * i + a], R.L[a]);
+        for_each_neighbour(B.nl, P.nslots, i, B.nn[i], [&](int u) {
             if (R.excl_span > 0) u &= 0x7fff;
-            if (u < S.n_own || u == P.stage_cap) return;  // inside the brick, or padding
-            const int64_t j = ssrc[u];
-            if (j < i) return;
-            const float4 pj = spos[u];
-            const float r2f = staged_r2(pi, pj);
-            const Band ba = one ? ba0 : make_band(R.pair[ti * MAXT + (int)pj.w].ra2);
-            if (!(r2f < ba.hi) || !within(r2f, ba, R, X, S_, i, j)) return;
-            int32_t pa = cc_ld(W.parent + i), pb = cc_ld(W.parent + j);
-            if (pa == pb) return;
-            if (pa > pb) {
-                const int32_t tmp = pa;
-                pa = pb;
-                pb = tmp;
-            }
-            const unsigned long long key = ((unsigned long long)(uint32_t)pa << 32) | (uint32_t)pb;
-            unsigned h = (unsigned)((key * 0x9E3779B97F4A7C15ull) >> 55) & (CC_SET - 1);
-            for (int probe = 0; probe < 16; ++probe) {
-                const unsigned long long prev = atomicCAS(set + h, ~0ull, key);
-                if (prev == key) return;  // this pair is joined already
-                if (prev == ~0ull) break;  // first of its pair
-                h = (h + 1) & (CC_SET - 1);
-            }
-            cc_union(W.parent, pa, pb);
+            if (u < n_own || u == P.stage_cap) return;  // inside the brick, or padding
+            const int j = sm[u];
+            if (j < (int)i || !(obs_r2(R, X, P.nslots, wi, j) < R.pair[ti * MAXT + B.type[j]].ra2)) return;
+            join((int)i, j);
         });
     }
 }
 
-// Size, bond ends and smallest tag of every cluster, gathered at its root; each particle
-// keeps its root as parent for the labelling pass.  A workgroup first sums the particles
-// of the cluster of its first particle in LDS (in a condensed fluid nearly all of them),
-// so that the root of a large cluster takes one atomic per workgroup, not per particle.
+// Size, bond ends and smallest tag of every cluster, gathered at its root from the bricks'
+// local components; each component's root keeps the cluster's root as parent for the
+// labelling pass.  A workgroup first sums its components by cluster in an LDS table: the
+// root of a percolating cluster then takes a few atomics per workgroup, and a small cluster
+// one per brick it touches (one per particle: 247 us at 500,000 particles).
+constexpr int CC_TAB = 256;
+
 __global__ void k_cc_count(Buffers B, Launch P, ClusterWork W)
 {
-    __shared__ StageHdr S;
-    __shared__ int32_t broot, bmin;
-    __shared__ uint32_t bsize, bends;
+    __shared__ int32_t troot[CC_TAB], tsize[CC_TAB], tmin[CC_TAB];
+    __shared__ uint32_t tends[CC_TAB];
     int b, r;
     if (!resolve_brick(P, B, b, r)) return;
     const RepDev &R = B.reps[r];
-    const int lb = b - R.b_off;
-    if (threadIdx.x == 0) {
-        pass_header(R, B, b, lb, P.stage_cap, S);
-        broot = -1;
-        bmin = INT32_MAX;
-        bsize = 0u;
-        bends = 0u;
+    const int n_own = B.bcnt[0][b];
+    if (n_own == 0 || B.stotal[b] > P.stage_cap) return;
+    const int64_t base = R.p_off + (int64_t)(b - R.b_off) * R.bcap;
+    for (int k = threadIdx.x; k < CC_TAB; k += blockDim.x) {
+        troot[k] = -1;
+        tsize[k] = 0;
+        tends[k] = 0u;
+        tmin[k] = INT32_MAX;
     }
     __syncthreads();
-    if (S.overflow || S.n_own == 0) return;
-    if (threadIdx.x == 0) broot = cc_find(W.parent, (int32_t)S.base);
-    __syncthreads();
-    const int32_t br = broot;
-    uint32_t ls = 0u, le = 0u;
-    int32_t lm = INT32_MAX;
-    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
-        const int64_t i = S.base + t;
+    for (int t = threadIdx.x; t < n_own; t += blockDim.x) {
+        const int64_t i = base + t;
+        const int32_t sz = W.size[i];
+        if (sz == 0) continue;  // not a component's root
         const int32_t root = cc_find(W.parent, (int32_t)i);
-        const int32_t tg = B.tag[i];
-        if (root == br) {
-            ls += 1u;
-            le += (uint32_t)W.z[i];
-            lm = tg < lm ? tg : lm;
-        } else {
-            atomicAdd(W.size + root, 1);
-            atomicAdd(W.ends + root, (uint32_t)W.z[i]);
-            atomicMin(W.mintag + root, tg);
-        }
+        if (root == (int32_t)i) continue;
         cc_st(W.parent + i, root);
-    }
-    ls = wave_sum(ls);
-    le = wave_sum(le);
-    for (int o = VBC_WAVE / 2; o > 0; o >>= 1) {
-        const int32_t v = __shfl_down(lm, o, VBC_WAVE);
-        lm = v < lm ? v : lm;
-    }
-    if ((threadIdx.x % VBC_WAVE) == 0 && ls) {
-        atomicAdd(&bsize, ls);
-        atomicAdd(&bends, le);
-        atomicMin(&bmin, lm);
+        const uint32_t en = W.ends[i];
+        const int32_t mt = W.mintag[i];
+        int h = (int)(((uint32_t)root * 0x9E3779B1u) >> 24) & (CC_TAB - 1);
+        int at = -1;
+        for (int probe = 0; probe < 8; ++probe) {
+            const int32_t prev = atomicCAS(troot + h, -1, root);
+            if (prev == -1 || prev == root) {
+                at = h;
+                break;
+            }
+            h = (h + 1) & (CC_TAB - 1);
+        }
+        if (at >= 0) {
+            atomicAdd(tsize + at, sz);
+            if (en) atomicAdd(tends + at, en);
+            atomicMin(tmin + at, mt);
+        } else {
+            atomicAdd(W.size + root, sz);
+            if (en) atomicAdd(W.ends + root, en);
+            atomicMin(W.mintag + root, mt);
+        }
     }
     __syncthreads();
-    if (threadIdx.x == 0 && bsize) {
-        atomicAdd(W.size + br, (int32_t)bsize);
-        atomicAdd(W.ends + br, bends);
-        atomicMin(W.mintag + br, bmin);
+    for (int k = threadIdx.x; k < CC_TAB; k += blockDim.x) {
+        const int32_t root = troot[k];
+        if (root < 0) continue;
+        atomicAdd(W.size + root, tsize[k]);
+        if (tends[k]) atomicAdd(W.ends + root, tends[k]);
+        atomicMin(W.mintag + root, tmin[k]);
     }
 }
 
 // Per particle: its cluster's smallest tag.  Per root: the cluster's statistics and its
-// histogram bins (all clusters, acyclic clusters).
+// histogram bins (all clusters, acyclic clusters), the latter summed in LDS first where they
+// fit.  A workgroup takes a run of consecutive bricks and adds its sums to the replica's when
+// the replica changes and at the end: all workgroups add to the same few words, and with a
+// workgroup per brick and an atomic per cluster the pass took 88 us at 500,000 particles.
+constexpr int CC_HIST = 2048;    // sizes a workgroup sums in LDS
+constexpr int CC_GROUPS = 512;   // workgroups
+
 __global__ void k_cc_label(Buffers B, Launch P, ClusterWork W, int32_t *__restrict__ label,
                            int64_t *__restrict__ stats, int64_t *__restrict__ hist, int hist_len)
 {
-    __shared__ StageHdr S;
-    __shared__ unsigned long long tot[4];
-    __shared__ unsigned long long big;
-    int b, r;
-    if (!resolve_brick(P, B, b, r)) return;
-    const RepDev &R = B.reps[r];
-    const int lb = b - R.b_off;
-    if (threadIdx.x == 0) {
-        pass_header(R, B, b, lb, P.stage_cap, S);
-        tot[0] = tot[1] = tot[2] = tot[3] = 0ull;
-        big = 0ull;
-    }
+    extern __shared__ uint32_t lh[];  // [2][hist_len] where hist_len <= CC_HIST
+    __shared__ unsigned long long tot[5];
+    const int T = P.list < 0 ? P.nb_launch : B.wl_n[P.list];
+    const int per = (T + gridDim.x - 1) / gridDim.x;
+    const int k0 = blockIdx.x * per, k1 = min(k0 + per, T);
+    const bool inlds = hist && hist_len <= CC_HIST;
+    if (threadIdx.x < 5) tot[threadIdx.x] = 0ull;
+    if (inlds)
+        for (int k = threadIdx.x; k < 2 * hist_len; k += blockDim.x) lh[k] = 0u;
     __syncthreads();
-    if (S.overflow) return;
     unsigned long long nc = 0, cp = 0, bonds = 0, ncyc = 0, lg = 0;
-    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
-        const int64_t i = S.base + t;
-        const int32_t root = W.parent[i];
-        if (label) label[R.o_off + B.tag[i]] = W.mintag[root];
-        if (root != (int32_t)i) continue;
-        const unsigned long long sz = (unsigned long long)W.size[i];
-        const unsigned long long e = (unsigned long long)(W.ends[i] / 2u);
-        const bool cyc = e >= sz;
-        nc += 1ull;
-        bonds += e;
-        if (cyc) {
-            cp += sz;
-            ncyc += 1ull;
+    int rc = -1;  // the replica whose sums are open
+    auto flush = [&](int r) {
+        const unsigned long long v0 = wave_sum(nc), v2 = wave_sum(cp), v3 = wave_sum(bonds), v4 = wave_sum(ncyc);
+        for (int o = VBC_WAVE / 2; o > 0; o >>= 1) {
+            const unsigned long long v = __shfl_down(lg, o, VBC_WAVE);
+            lg = v > lg ? v : lg;
         }
-        lg = sz > lg ? sz : lg;
-        if (hist) {
-            const int bin = sz < (unsigned long long)hist_len ? (int)sz : 0;
-            int64_t *h = hist + (size_t)r * 2 * hist_len;
-            atomicAdd((unsigned long long *)(h + bin), 1ull);
-            if (!cyc) atomicAdd((unsigned long long *)(h + hist_len + bin), 1ull);
+        if ((threadIdx.x % VBC_WAVE) == 0 && v0) {
+            atomicAdd(&tot[0], v0);
+            atomicMax(&tot[1], lg);
+            atomicAdd(&tot[2], v2);
+            atomicAdd(&tot[3], v3);
+            atomicAdd(&tot[4], v4);
+        }
+        __syncthreads();
+        if (inlds)
+            for (int k = threadIdx.x; k < 2 * hist_len; k += blockDim.x)
+                if (lh[k]) {
+                    atomicAdd((unsigned long long *)(hist + (size_t)r * 2 * hist_len + k), (unsigned long long)lh[k]);
+                    lh[k] = 0u;
+                }
+        if (threadIdx.x < 5) {
+            unsigned long long *st = (unsigned long long *)(stats + 5 * (size_t)r) + threadIdx.x;
+            const unsigned long long v = tot[threadIdx.x];
+            if (stats && v) {
+                if (threadIdx.x == 1) atomicMax(st, v);
+                else atomicAdd(st, v);
+            }
+            tot[threadIdx.x] = 0ull;
+        }
+        __syncthreads();
+        nc = cp = bonds = ncyc = lg = 0;
+    };
+    for (int k = k0; k < k1; ++k) {
+        const int b = P.list < 0 ? P.b_lo + k : B.wl[P.list][k];
+        const int r = B.brick_rep[b], n_own = B.bcnt[0][b];
+        if (r < 0 || n_own == 0 || B.stotal[b] > P.stage_cap) continue;
+        if (r != rc) {
+            if (rc >= 0) flush(rc);
+            rc = r;
+        }
+        const RepDev &R = B.reps[r];
+        const int64_t base = R.p_off + (int64_t)(b - R.b_off) * R.bcap;
+        int64_t *h = hist + (size_t)r * 2 * hist_len;
+        for (int t = threadIdx.x; t < n_own; t += blockDim.x) {
+            const int64_t i = base + t;
+            // the particle's component root, whose parent is the cluster's root
+            const int32_t root = W.parent[W.parent[i]];
+            if (label) label[R.o_off + B.tag[i]] = W.mintag[root];
+            if (root != (int32_t)i) continue;
+            const unsigned long long sz = (unsigned long long)W.size[i];
+            const unsigned long long e = (unsigned long long)(W.ends[i] / 2u);
+            const bool cyc = e >= sz;
+            nc += 1ull;
+            bonds += e;
+            if (cyc) {
+                cp += sz;
+                ncyc += 1ull;
+            }
+            lg = sz > lg ? sz : lg;
+            if (hist) {
+                const int bin = sz < (unsigned long long)hist_len ? (int)sz : 0;
+                if (inlds) {
+                    atomicAdd(lh + bin, 1u);
+                    if (!cyc) atomicAdd(lh + hist_len + bin, 1u);
+                } else {
+                    atomicAdd((unsigned long long *)(h + bin), 1ull);
+                    if (!cyc) atomicAdd((unsigned long long *)(h + hist_len + bin), 1ull);
+                }
+            }
         }
     }
-    nc = wave_sum(nc);
-    cp = wave_sum(cp);
-    bonds = wave_sum(bonds);
-    ncyc = wave_sum(ncyc);
-    for (int o = VBC_WAVE / 2; o > 0; o >>= 1) {
-        const unsigned long long v = __shfl_down(lg, o, VBC_WAVE);
-        lg = v > lg ? v : lg;
-    }
-    if ((threadIdx.x % VBC_WAVE) == 0) {
-        atomicAdd(&tot[0], nc);
-        atomicAdd(&tot[1], cp);
-        atomicAdd(&tot[2], bonds);
-        atomicAdd(&tot[3], ncyc);
-        atomicMax(&big, lg);
-    }
-    __syncthreads();
-    if (stats && threadIdx.x == 0 && tot[0]) {
-        // only workgroups that hold a root have anything to add
-        unsigned long long *st = (unsigned long long *)(stats + 5 * (size_t)r);
-        atomicAdd(st + 0, tot[0]);
-        atomicMax(st + 1, big);
-        if (tot[1]) atomicAdd(st + 2, tot[1]);
-        if (tot[2]) atomicAdd(st + 3, tot[2]);
-        if (tot[3]) atomicAdd(st + 4, tot[3]);
-    }
+    if (rc >= 0) flush(rc);
 }
 
 // ---------------------------------------------------------------------------
@@ -2677,51 +2785,48 @@ __global__ void k_cc_label(Buffers B, Launch P, ClusterWork W, int32_t *__restri
 // born now.  Each event is counted at the end with the smaller tag, once per bond.
 // stats per replica: {formed, broken with a lifetime, broken without one, partners that did
 // not fit, bonds now}.
+template <bool MULTI>
 __global__ void k_bond_track(Buffers B, Launch P, int cur, BondTrack T, int reset,
                              int64_t *__restrict__ hist, int hist_len, int64_t bin_steps,
                              int64_t *__restrict__ stats)
 {
-    extern __shared__ __align__(16) float4 spos[];  // [stage_cap + 1], then stag[stage_cap]
-    __shared__ StageHdr S;
+    extern __shared__ __align__(16) unsigned char smem[];  // Staged
     __shared__ unsigned long long tot[5];
-    int b, r;
-    if (!resolve_brick(P, B, b, r)) return;
+    int b;
+    if (!brick_of_block(P, B, b)) return;
+    const MapFirst mf = map_prefetch(B, b, P.stage_cap);
+    const int r = B.brick_rep[b];
+    if (r < 0) return;
     const RepDev &R = B.reps[r];
     const int lb = b - R.b_off;
-    if (threadIdx.x == 0) {
-        pass_header(R, B, b, lb, P.stage_cap, S);
-        for (int k = 0; k < 5; ++k) tot[k] = 0ull;
-    }
-    __syncthreads();
+    if (threadIdx.x < 5) tot[threadIdx.x] = 0ull;
+    StageHdr S;
+    pass_header(R, B, b, lb, P.stage_cap, S);
     if (S.overflow) return;
     const int64_t S_ = P.nslots;
     const double *X = B.x[cur];
     const int32_t *sm = B.smap + (size_t)b * P.stage_cap;
-    int32_t *stag = (int32_t *)(spos + P.stage_cap + 1);
-    stage_map(B, b, P.stage_cap, S, [&](int t, int src, int w) {
-        spos[t] = local_pos<float>(R, S, X, S_, src, w, B.type[src]);
-        stag[t] = B.tag[src];
-    });
-    if (threadIdx.x == 0) spos[P.stage_cap] = dummy_pos<float4>();
+    const Staged G = carve_staged(smem, P.stage_cap);
+    stage_bonds<MULTI>(B, P, R, S, b, X, G, mf);
     __syncthreads();
-    const bool one = R.ntypes == 1;
+    const bool xr = MULTI && R.excl_span > 0;
     const Band ba0 = make_band(R.pair[0].ra2);
     const int M = T.M;
     const int64_t now = (int64_t)B.step[r];
     unsigned long long formed = 0, broken = 0, cens = 0, over = 0, bonds = 0;
     for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
         const int64_t i = S.base + t;
-        const float4 pi = spos[t];
-        const int ti = (int)pi.w;
-        const int32_t tg = stag[t];
+        const float2 pi = G.xy[t];
+        const float zi = G.z[t];
+        const int ti = MULTI ? G.type[t] : 0;
+        const int32_t tg = B.tag[i];
         const int64_t c = R.o_off + tg;
         int32_t *ptag = T.tags + c * M;
         int64_t *pbirth = T.births + c * M;
         auto bonded = [&](int u) {
-            const float4 pj = spos[u];
-            const float r2f = staged_r2(pi, pj);
-            const Band ba = one ? ba0 : make_band(R.pair[ti * MAXT + (int)pj.w].ra2);
-            return r2f < ba.hi && within(r2f, ba, R, X, S_, i, sm[u]);
+            const float r2f = staged_r2(G, pi, zi, u);
+            const Band ba = MULTI ? make_band(R.pair[ti * MAXT + G.type[u]].ra2) : ba0;
+            return r2f < ba.hi && within(r2f, ba, R, X, S_, i, [&] { return (int64_t)sm[u]; });
         };
         int n = 0;
         if (!reset) {
@@ -2729,9 +2834,9 @@ __global__ void k_bond_track(Buffers B, Launch P, int cur, BondTrack T, int rese
             const int n_old = min(max(T.count[c], 0), M);
             uint64_t keep = 0ull;
             for_each_neighbour(B.nl, S_, i, B.nn[i], [&](int u) {
-                if (R.excl_span > 0) u &= 0x7fff;
-                if (u == P.stage_cap || !bonded(u)) return;
-                const int32_t tj = stag[u];
+                if (xr) u &= 0x7fff;
+                if (!bonded(u)) return;
+                const int32_t tj = B.tag[sm[u]];
                 for (int k = 0; k < n_old; ++k)
                     if (ptag[k] == tj) {
                         keep |= 1ull << k;
@@ -2764,9 +2869,9 @@ __global__ void k_bond_track(Buffers B, Launch P, int cur, BondTrack T, int rese
         // 3. bonds not stored are new (at a reset: present from the start, birth unknown)
         const int n_keep = n;
         for_each_neighbour(B.nl, S_, i, B.nn[i], [&](int u) {
-            if (R.excl_span > 0) u &= 0x7fff;
-            if (u == P.stage_cap || !bonded(u)) return;
-            const int32_t tj = stag[u];
+            if (xr) u &= 0x7fff;
+            if (!bonded(u)) return;
+            const int32_t tj = B.tag[sm[u]];
             if (tg < tj) ++bonds;
             for (int k = 0; k < n_keep; ++k)
                 if (ptag[k] == tj) return;
@@ -2829,11 +2934,11 @@ size_t lds_bytes_count(const Launch &P)
     return (size_t)(P.stage_cap + 1) * (P.precision == VBC_FP64 ? 32 : (P.multi ? 16 : 12));
 }
 size_t lds_bytes_embed(const Launch &P) { (void)P; return 0; }
-// bond tests (observables, clusters): FP32 staging, then the slots or the brick's forest
+// bond tests (observables, clusters, bond tracker): FP32 staging, and the brick's forest
+static size_t staged_bytes(const Launch &P) { return (size_t)(P.stage_cap + 1) * (P.multi ? 16 : 12); }
 size_t lds_bytes_bonds(const Launch &P)
 {
-    return (size_t)(P.stage_cap + 1) * 16 + (size_t)std::max(P.stage_cap, P.bcap_max) * sizeof(int32_t) + 16 +
-           CC_SET * sizeof(unsigned long long);
+    return staged_bytes(P) + (size_t)P.bcap_max * sizeof(int32_t) + 16;
 }
 size_t lds_bytes_force(const Launch &P)
 {
@@ -2906,13 +3011,14 @@ hipError_t launch_get_state(const Buffers &B, const Launch &P, int cur, int r, i
 hipError_t launch_set_state_all(const Buffers &B, const Launch &P, int cur, const double *x, const double *v,
                                 const int32_t *type, uint64_t step0, hipStream_t s)
 {
-    k_set_state_all<<<P.nbrick_tot, 256, 0, s>>>(B, P.nslots, cur, P.ntot, x, v, type, step0);
+    // one wave per brick where bricks are small
+    k_set_state_all<<<P.nbrick_tot, P.bcap_max <= 128 ? VBC_WAVE : 256, 0, s>>>(B, P.nslots, cur, P.ntot, x, v, type, step0);
     return hipGetLastError();
 }
 
 hipError_t launch_get_state_all(const Buffers &B, const Launch &P, int cur, double *x, double *v, hipStream_t s)
 {
-    k_get_state_all<<<P.nbrick_tot, 256, 0, s>>>(B, P.nslots, cur, P.ntot, x, v);
+    k_get_state_all<<<P.nbrick_tot, P.bcap_max <= 128 ? VBC_WAVE : 256, 0, s>>>(B, P.nslots, cur, P.ntot, x, v);
     return hipGetLastError();
 }
 
@@ -2962,7 +3068,7 @@ hipError_t launch_full_build_all(const Buffers &B, const Launch &P, int cur, hip
     Q.nb_launch = P.nbrick_tot;
     Q.list = -1;
     Q.due = FLAG_FULL;  // a replica that is only due for a rebuild has no next layout yet
-    tlaunch(k_gbin_all, P.nbrick_tot, 256, 0, s, B, cur);
+    tlaunch(k_gbin_all, P.nbrick_tot, P.bcap_max <= 128 ? VBC_WAVE : 256, 0, s, B, cur);
     tlaunch(k_gsort, brick_grid(Q.nb_launch), Q.block, sort_bytes(Q), s, B, Q, cur);
     tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.block, lds_bytes_nlist(Q), s, B, Q, cur);
     tlaunch(k_full_done, blocks_for(P.nrep, 256), 256, 0, s, B, P.nrep);
@@ -3103,20 +3209,23 @@ hipError_t launch_observe(const Buffers &B, const Launch &P, int cur, int32_t *z
                           int32_t *pen_out, int64_t *sums, hipStream_t s)
 {
     if (sums) k_zero_i64<<<blocks_for(3 * P.nrep, 256), 256, 0, s>>>(sums, 3 * P.nrep);
-    k_observe<<<brick_grid(P.nb_launch), P.block, lds_bytes_bonds(P), s>>>(B, P, cur, z_out, pen_out, sums);
+    const unsigned g = brick_grid(P.nb_launch);
+    if (P.multi) k_observe<true><<<g, P.block, staged_bytes(P), s>>>(B, P, cur, z_out, pen_out, sums);
+    else k_observe<false><<<g, P.block, staged_bytes(P), s>>>(B, P, cur, z_out, pen_out, sums);
     return hipGetLastError();
 }
 
 hipError_t launch_clusters(const Buffers &B, const Launch &P, int cur, const ClusterWork &W,
                            int32_t *label, int64_t *stats, int64_t *hist, int hist_len, hipStream_t s)
 {
-    if (stats) k_zero_i64<<<blocks_for(5 * P.nrep, 256), 256, 0, s>>>(stats, 5 * P.nrep);
-    if (hist) k_zero_i64<<<blocks_for(2 * (int64_t)P.nrep * hist_len, 256), 256, 0, s>>>(hist, 2 * P.nrep * hist_len);
-    k_cc_init<<<blocks_for(P.nslots, 256), 256, 0, s>>>(W, P.nslots);
-    k_cc_local<<<brick_grid(P.nb_launch), P.block, lds_bytes_bonds(P), s>>>(B, P, cur, W);
-    k_cc_hook<<<brick_grid(P.nb_launch), P.block, lds_bytes_bonds(P), s>>>(B, P, cur, W);
-    k_cc_count<<<brick_grid(P.nb_launch), P.block, 0, s>>>(B, P, W);
-    k_cc_label<<<brick_grid(P.nb_launch), P.block, 0, s>>>(B, P, W, label, stats, hist, hist_len);
+    const unsigned g = brick_grid(P.nb_launch);
+    const int64_t nhist = 2 * (int64_t)P.nrep * hist_len;
+    if (P.multi) k_cc_local<true><<<g, P.block, lds_bytes_bonds(P), s>>>(B, P, cur, W, stats, hist, nhist);
+    else k_cc_local<false><<<g, P.block, lds_bytes_bonds(P), s>>>(B, P, cur, W, stats, hist, nhist);
+    k_cc_hook<<<g, 256, 0, s>>>(B, P, cur, W);
+    k_cc_count<<<g, 256, 0, s>>>(B, P, W);
+    const size_t lh = hist && hist_len <= CC_HIST ? (size_t)2 * hist_len * sizeof(uint32_t) : 0;
+    k_cc_label<<<std::min<unsigned>(g, CC_GROUPS), 256, lh, s>>>(B, P, W, label, stats, hist, hist_len);
     return hipGetLastError();
 }
 
@@ -3125,8 +3234,11 @@ hipError_t launch_bond_track(const Buffers &B, const Launch &P, int cur, const B
 {
     if (reset && stats) k_zero_i64<<<blocks_for(5 * P.nrep, 256), 256, 0, s>>>(stats, 5 * P.nrep);
     if (reset && hist) k_zero_i64<<<blocks_for((int64_t)P.nrep * hist_len, 256), 256, 0, s>>>(hist, P.nrep * hist_len);
-    k_bond_track<<<brick_grid(P.nb_launch), P.block, lds_bytes_bonds(P), s>>>(B, P, cur, T, reset, hist, hist_len,
-                                                                              bin_steps, stats);
+    const unsigned g = brick_grid(P.nb_launch);
+    if (P.multi)
+        k_bond_track<true><<<g, P.block, staged_bytes(P), s>>>(B, P, cur, T, reset, hist, hist_len, bin_steps, stats);
+    else
+        k_bond_track<false><<<g, P.block, staged_bytes(P), s>>>(B, P, cur, T, reset, hist, hist_len, bin_steps, stats);
     return hipGetLastError();
 }
 

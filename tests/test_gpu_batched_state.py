@@ -69,3 +69,25 @@ def test_batched_states_equal_single(pool, precision):
         alone, _ = _run(vbc, [k], pool, precision, again)
         for a, b in zip(got[k], alone[k]):
             assert np.array_equal(a, b), k
+
+
+def test_captured_analysis_replays_after_steps():
+    """An analysis captured into a graph while no list can be due still rebuilds the lists when
+    it is replayed after steps (of even count: a captured call keeps its position buffer)."""
+    from paper_2609_07842_amd import vbc
+    N, L = 5000, W.box_length(5000, 0.3)
+    s = vbc.System(vbc.replica(N, L, W.vbc_params(E_a=5.0, f=3.0)), precision="fp32", rho_max=1.0)
+    s.set_state(W.uniform_positions(N, L, 3), W.maxwell_boltzmann(N, 1.0, 4))
+    s.observables()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        z, pen, sums = s.observables()
+    for _ in range(5):
+        s.step(30, **INTEG)
+        g.replay()
+        torch.cuda.synchronize()
+        ze, pe, se = s.observables()
+        assert torch.equal(z, ze) and torch.equal(pen, pe) and torch.equal(sums, se)
+    s.check()
+
