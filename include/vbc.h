@@ -180,7 +180,10 @@ vbc_status vbc_force(vbc_handle h, double *d_F, double *d_e, double *d_UW, hipSt
  * build.  Replicas without stored forces (new state) get them first, each on its own,
  * so that the others are not touched.  Calls of up to 64 steps run as one captured HIP
  * graph launch (captured once per step count, integrator and buffer parity); longer
- * calls replay graphs of 8 steps. */
+ * calls replay graphs of 8 steps.  A set of eight or more small replicas (vbc_create; one type,
+ * at most 1024 particles each) may run as one launch of one workgroup per replica instead,
+ * whose trajectories differ from the others' in the rounding of sums only; its passes are not
+ * told apart by vbc_profile. */
 vbc_status vbc_step(vbc_handle h, int32_t nsteps, const vbc_integrator *it, hipStream_t s);
 
 /* Capture, without launching anything, the step graphs that vbc_step(h, nsteps, it, ...)

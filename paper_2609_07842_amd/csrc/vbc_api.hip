@@ -56,6 +56,9 @@ struct vbc_handle_s {
     bool auto_block = false;  // a pool whose workgroup size follows the admitted replicas
     std::vector<RepDev> reps;   // host copy of every replica slot (n == 0: free)
     std::vector<char> live, has_state, need_full, fvalid;
+    int resident = 0;           // > 0: steps run in one workgroup per replica, of at most this many
+                                // particles (k_resident)
+    std::vector<char> res;      // resident replicas standing in caller order after steps (FLAG_RES)
     Arena a_slot, a_brick, a_cell, a_caller;
     RepDev *up = nullptr;       // pinned upload staging, one entry per slot
     std::vector<hipEvent_t> up_ev;
@@ -368,6 +371,28 @@ bool partial_mask(const RepDev &R)
     return false;
 }
 
+// Whether a fixed set of replicas steps with one workgroup per replica: sets of at least eight,
+// all of which can, where the slowest replica's workgroup is estimated faster than the set's
+// bricks.  (A set and a single replica then differ in the rounding of FP32 sums only; smaller
+// sets keep the bits that each replica has alone.)  Measured on sets of replicas with one
+// common size: a resident step takes about 9 us + 0.8 us per 1000 particles times (mean list
+// length + 8) (9.8 at 2,700, 25 at 21,800, 43 at 43,600 of them; 1.3 us per 1000 in FP64), a
+// step of bricks 25 us + 0.025 us per brick (20 replicas of 4000 at density 0.05, 2500
+// bricks: 130 us; 32 of 1000 in bricks of 2^3 cells, 6912 bricks: 190 us).
+constexpr int RES_MIN_SET = 8;
+bool resident_set(const std::vector<RepPlan> &plans, int precision)
+{
+    if ((int)plans.size() < RES_MIN_SET) return false;
+    double work = 0.0, bricks = 0.0;
+    for (const RepPlan &p : plans) {
+        if (!resident_can(p.R)) return false;
+        work = std::max(work, (double)p.R.n * (p.k_mean + 8.0));
+        bricks += p.R.nbrick;
+    }
+    const double rounds = std::ceil((double)plans.size() / 256.0);
+    return rounds * (9.0 + work * (precision == VBC_FP64 ? 1.3e-3 : 0.8e-3)) < 25.0 + 0.025 * bricks;
+}
+
 // Workspace layout for a capacity; every array is 256-byte aligned.
 Offsets layout(const Caps &C, int precision, int nchunk, int stage_cap)
 {
@@ -546,6 +571,7 @@ vbc_status make_handle(const Caps &C, const vbc_options &opt, bool pool, void *d
     h->has_state.assign(C.nrep, 0);
     h->need_full.assign(C.nrep, 0);
     h->fvalid.assign(C.nrep, 0);
+    h->res.assign(C.nrep, 0);
     h->up_pending.assign(C.nrep, 0);
     // a fixed single replica (not a pool): count and force take its descriptor as a kernel
     // argument (h->reps is sized once here, so the pointer stays valid)
@@ -659,6 +685,7 @@ vbc_status place(vbc_handle h, const RepPlan &rp, hipStream_t s, int32_t *rep_ou
     h->has_state[r] = 0;
     h->need_full[r] = 0;
     h->fvalid[r] = 0;
+    h->res[r] = 0;
     *rep_out = r;
     return VBC_OK;
 }
@@ -711,16 +738,13 @@ static vbc_status ensure_layout(vbc_handle h, hipStream_t s)
         Launch Q = restrict_to(h->P, R);
         VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_full_build(h->B, Q, h->cur, one, R.n, s); }),
                 "full build");
-        VBC_TRY(h, launch_flags(h->B, one, 1, VBC_FLAG_REBUILD | FLAG_FULL, false, s), "flags");
+        VBC_TRY(h, launch_flags(h->B, one, 1, VBC_FLAG_REBUILD | FLAG_FULL | FLAG_RES, false, s), "flags");
     } else {
         VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_full_build_all(h->B, h->P, h->cur, s); }),
                 "full builds");
     }
     for (int r = 0; r < h->P.nrep; ++r)
-        if (h->live[r] && h->need_full[r]) {
-            h->need_full[r] = 0;
-            h->fvalid[r] = 0;
-        }
+        if (h->live[r] && h->need_full[r]) h->need_full[r] = h->fvalid[r] = h->res[r] = 0;
     return VBC_OK;
 }
 
@@ -984,9 +1008,14 @@ vbc_status vbc_create(const vbc_replica_desc *reps, int32_t nrep, const vbc_opti
     std::vector<RepPlan> plans;
     vbc_status st = plan_set(reps, nrep, opt_in, C, opt, plans);
     if (st != VBC_OK) return st;
+    const bool resident = resident_set(plans, opt.precision);
     vbc_handle h = nullptr;
     st = make_handle(C, opt, false, d_ws, ws_bytes, s, &h);
     if (st != VBC_OK) return st;
+    for (RepPlan &p : plans) {
+        p.R.resident = resident ? 1 : 0;
+        if (resident) h->resident = std::max(h->resident, (int)p.R.n);
+    }
     // first fit on empty ranges: replica r lands at the prefix sums of the ones before it
     for (int r = 0; r < nrep; ++r) {
         int32_t got = -1;
@@ -1231,6 +1260,7 @@ vbc_status vbc_set_state(vbc_handle h, int32_t rep, const double *d_x, const dou
         h->has_state[r] = 1;
         h->need_full[r] = 1;
         h->fvalid[r] = 0;
+        h->res[r] = 0;
     }
     return VBC_OK;
 }
@@ -1241,7 +1271,10 @@ vbc_status vbc_get_state(vbc_handle h, int32_t rep, double *d_x, double *d_v, hi
     if (!h) return fail(VBC_ERR_ARG, "NULL handle");
     if (rep >= h->P.nrep || (rep >= 0 && !h->live[rep])) return hfail(h, VBC_ERR_ARG, "no such live replica");
     if (rep >= 0 ? !h->has_state[rep] : !all_have_state(h)) return hfail(h, VBC_ERR_STATE, "no state set");
-    VBC_LAYOUT(h, s);
+    // resident replicas are read from caller order; the others need their layout
+    bool layout = false;
+    for (int r = 0; r < h->P.nrep; ++r) layout = layout || (h->live[r] && h->need_full[r] && !h->res[r]);
+    if (layout) VBC_LAYOUT(h, s);
     if (rep < 0 && live_count(h) > 1) {
         VBC_TRY(h, launch_get_state_all(h->B, h->P, h->cur, d_x, d_v, s), "get_state");
         return VBC_OK;
@@ -1261,9 +1294,11 @@ vbc_status vbc_build_nlist(vbc_handle h, hipStream_t s)
     Range range_("vbc_build_nlist");
     if (!h) return fail(VBC_ERR_ARG, "NULL handle");
     VBC_NEED_STATE(h);
-    bool full = false;
-    for (int r = 0; r < h->P.nrep; ++r) full = full || (h->live[r] && h->need_full[r]);
+    bool full = true;
+    for (int r = 0; r < h->P.nrep; ++r) full = full && (!h->live[r] || h->need_full[r]);
     VBC_LAYOUT(h, s);
+    // resident replicas too build their lists from here on
+    VBC_TRY(h, launch_flags(h->B, 0, h->P.nrep, FLAG_XREF, false, s), "flags");
     if (full) return VBC_OK;
     VBC_TRY(h, launch_flags(h->B, 0, h->P.nrep, VBC_FLAG_REBUILD, true, s), "flags");
     VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_rebuild(h->B, h->P, h->cur, s); }), "rebuild");
@@ -1328,7 +1363,7 @@ vbc_status vbc_step_prepare(vbc_handle h, int32_t nsteps, const vbc_integrator *
     if (!h || !it) return fail(VBC_ERR_ARG, "NULL argument");
     vbc_status r = check_integrator(h, nsteps, it);
     if (r != VBC_OK) return r;
-    if (nsteps == 0 || !h->use_graphs || h->prof) return VBC_OK;
+    if (nsteps == 0 || !h->use_graphs || h->prof || h->resident) return VBC_OK;
     const StepArgs st = step_args(it);
     hipGraphExec_t ge = nullptr;
     if (nsteps <= CALL_GRAPH_MAX) VBC_TRY(h, get_graph(h, 1, nsteps, h->cur, st, &ge), "call graph");
@@ -1346,8 +1381,21 @@ vbc_status vbc_step(vbc_handle h, int32_t nsteps, const vbc_integrator *it, hipS
         if (r0 != VBC_OK) return r0;
     }
     if (nsteps == 0) return VBC_OK;
-    VBC_LAYOUT(h, s);
     const StepArgs st = step_args(it);
+    if (h->resident) {
+        StepArgs sr = st;
+        sr.acc = h->thermo ? 1 : 0;
+        // with time stamps, each step is a launch with its stamp
+        const int each = h->stamps ? 1 : nsteps;
+        for (int k = 0; k < nsteps; k += each) {
+            VBC_TRY(h, launch_resident(h->B, h->P, h->cur, each, k, h->resident, sr, s), "resident steps");
+            if (h->stamps) VBC_TRY(h, launch_stamp(h->B, s), "stamp");
+        }
+        for (int k = 0; k < h->P.nrep; ++k)
+            if (h->live[k]) h->need_full[k] = h->res[k] = 1;
+        return VBC_OK;
+    }
+    VBC_LAYOUT(h, s);
     vbc_status r = eval_missing(h, st, s);
     if (r != VBC_OK) return r;
     h->maybe_due = true;

@@ -55,6 +55,7 @@ struct RepDev {
     int32_t nb[3];         // bricks per axis
     int32_t ntypes;
     int32_t chain_len;
+    int32_t resident;      // time steps run in one workgroup that keeps the replica in LDS
     int32_t excl_span;     // > 0: chain neighbours up to this many beads apart neither count
                            // nor attract each other (list entries carry bit 15)
     uint32_t mask[MAXT];
@@ -155,7 +156,10 @@ template <> struct OneRep<true> { RepDev R; };
 
 // internal flag bits (beyond the public ones in vbc.h)
 enum : uint32_t {
-    FLAG_FULL = 1u << 8      // next build starts from unsorted (caller-order) input
+    FLAG_FULL = 1u << 8,     // next build starts from unsorted (caller-order) input
+    // resident replicas, whose particles stand in caller order between their calls of steps:
+    FLAG_RES = 1u << 9,      // positions wrapped, forces and the resident list valid
+    FLAG_XREF = 1u << 10     // xref holds the positions of the last resident list build
 };
 
 enum Mode { MODE_EVAL = 0, MODE_MID = 1, MODE_LAST = 2 };
@@ -238,6 +242,11 @@ hipError_t launch_bond_track(const Buffers &B, const Launch &P, int cur, const B
                              int64_t *hist, int hist_len, int64_t bin_steps, int64_t *stats, hipStream_t s);
 hipError_t launch_clusters(const Buffers &B, const Launch &P, int cur, const ClusterWork &W,
                            int32_t *label, int64_t *stats, int64_t *hist, int hist_len, hipStream_t s);
+// One call of nsteps steps (or, with time stamps, one step of it) of a set of resident
+// replicas of at most max_n particles; k0: the first step's index in the call.
+hipError_t launch_resident(const Buffers &B, const Launch &P, int cur, int nsteps, int k0, int max_n,
+                           const StepArgs &st, hipStream_t s);
+bool resident_can(const RepDev &R);
 size_t lds_bytes_sort(const Launch &P);
 size_t lds_bytes_nlist(const Launch &P);
 size_t lds_bytes_count(const Launch &P);

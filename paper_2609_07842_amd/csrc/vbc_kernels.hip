@@ -488,7 +488,12 @@ __global__ void k_get_state(Buffers B, int64_t S_, int cur, int r, int64_t out_o
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= (int64_t)R.nbrick * R.bcap) return;
     int lb = (int)(k / R.bcap);
-    if (k - (int64_t)lb * R.bcap >= B.bcnt[0][R.b_off + lb]) return;
+    // after resident steps the particles stand in caller order
+    if (B.flags[r] & FLAG_RES) {
+        if (k >= R.n) return;
+    } else if (k - (int64_t)lb * R.bcap >= B.bcnt[0][R.b_off + lb]) {
+        return;
+    }
     take_state(B, R, S_, cur, R.p_off + k, out_off, out_stride, x, v);
 }
 
@@ -497,10 +502,12 @@ __global__ void k_get_state(Buffers B, int64_t S_, int cur, int r, int64_t out_o
 __global__ void k_get_state_all(Buffers B, int64_t S_, int cur, int64_t out_stride, double *__restrict__ x,
                                 double *__restrict__ v)
 {
-    const int b = blockIdx.x, r = B.brick_rep[b], n = B.bcnt[0][b];
+    const int b = blockIdx.x, r = B.brick_rep[b];
+    int n = B.bcnt[0][b];
     if (r < 0) return;
     const RepDev &R = B.reps[r];
-    const int64_t base = R.p_off + (int64_t)(b - R.b_off) * R.bcap;
+    const int64_t k0 = (int64_t)(b - R.b_off) * R.bcap, base = R.p_off + k0;
+    if (B.flags[r] & FLAG_RES) n = (int)min((int64_t)R.bcap, R.n - k0);  // caller order
     for (int t = threadIdx.x; t < n; t += blockDim.x)
         take_state(B, R, S_, cur, base + t, R.o_off, out_stride, x, v);
 }
@@ -517,7 +524,7 @@ __global__ void k_flags(Buffers B, int r_lo, int r_n, uint32_t bits, int set)
 __global__ void k_full_done(Buffers B, int nrep)
 {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < nrep && (B.flags[r] & FLAG_FULL)) B.flags[r] &= ~(uint32_t)(VBC_FLAG_REBUILD | FLAG_FULL);
+    if (r < nrep && (B.flags[r] & FLAG_FULL)) B.flags[r] &= ~(uint32_t)(VBC_FLAG_REBUILD | FLAG_FULL | FLAG_RES);
 }
 
 // Rank of a cell in the brick-major order (bricks x-fastest, cells x-fastest inside a
@@ -940,7 +947,8 @@ __global__ void NLIST_ATTR k_nlist(Buffers B, Launch P, int cur)
         for (int a = 0; a < 3; ++a) {
             double xa = B.xs[3 * i + a];
             B.x[cur][3 * i + a] = xa;
-            B.xref[a * S_ + i] = xa;
+            // a resident replica steps by its own list, whose reference positions stay
+            if (!R.resident) B.xref[a * S_ + i] = xa;
             B.v[a * S_ + i] = B.vs[a * S_ + i];
         }
         B.tag[i] = B.tags[i];
@@ -2904,6 +2912,622 @@ __global__ void k_bond_track(Buffers B, Launch P, int cur, BondTrack T, int rese
 }
 
 // ---------------------------------------------------------------------------
+// resident steps of small replicas
+// ---------------------------------------------------------------------------
+
+// A set of small replicas takes a step of brick kernels at the pace of its many small bricks:
+// 32 replicas of 1000 particles laid out for condensation are 6912 bricks of five particles,
+// whose reserved LDS leaves two workgroups of two waves on a CU (190 us a step), and some
+// replica's list is due in nearly every step.  The steps of such a set run with one workgroup
+// per replica instead: its positions and switching factors stay in LDS, a barrier takes the
+// place of a launch, and one launch does a whole call for all replicas (that set: 20 us a step
+// from a uniform start, 65 once some replicas have collapsed into droplets with lists of a
+// hundred neighbours; then one CU's VALU issue on the densest replica is the bound).
+//
+// Between calls the particles stand in caller order (slot p_off + tag, positions wrapped
+// every step) with their forces (Fst), velocities, the positions of the last list build
+// (xref) and the list (nl, nn: tags in 16 bits, eight per chunk).  An analysis or a force
+// evaluation in between takes the replica into the brick layout, which leaves xref alone; the
+// next step then builds the same list again from xref and the same forces, so that the
+// trajectory does not depend on it.  The list orders neighbours by cell of a grid of at least
+// the list radius and by tag inside a cell, so it depends on xref alone, and every sum here is
+// per particle in list order or over 64 consecutive tags: neither the workgroup's size nor
+// the other replicas change a bit.
+//
+// FP32 pair arithmetic: positions are 64-bit fractions of the box, and a distance starts from
+// the wrapped integer difference of their upper halves: the minimum image without a test, and
+// an error of L 2^-32 where a staged FP32 coordinate has up to 5e-7.  The FP64 recount of
+// particles near a switching window takes the whole 64 bits.
+//
+// A thread owns the particle of its index: position, velocity, force and reference position
+// stay in registers through a call, and only the list is read from memory.
+constexpr int RES_MAX_N = 1024;
+constexpr double RES_MAX_L = 512.0;
+
+template <class Real> struct ResLds;
+
+template <> struct ResLds<float> {
+    int2 *xy, *zs;       // upper halves of the fractions; s beside z
+    float *A;            // c_c dU/dn
+    uint32_t *lo[3];     // lower halves
+    int4 *sorted;        // list build: (x, y, z, tag) by cell, then by tag
+    int *cell;           // [n + 2] list build: end of each cell
+    uint16_t *order;     // [n] list build: members; then the window particles
+    static size_t bytes(int n) { return (size_t)n * (32 + 16 + 4 + 2) + 64; }
+    __device__ void carve(unsigned char *p, int n)
+    {
+        sorted = (int4 *)p;
+        xy = (int2 *)(sorted + n);
+        zs = xy + n;
+        A = (float *)(zs + n);
+        for (int a = 0; a < 3; ++a) lo[a] = (uint32_t *)(A + (a + 1) * n);
+        cell = (int *)(lo[2] + n);
+        order = (uint16_t *)(cell + n + 2);
+    }
+    struct Pos { int x, y, z; };
+    struct Scale { float h[3]; };  // L 2^-32
+    static __device__ Scale scale(const double L[3])
+    {
+        return Scale{{(float)(L[0] * 0x1p-32), (float)(L[1] * 0x1p-32), (float)(L[2] * 0x1p-32)}};
+    }
+    __device__ void put(int k, const double x[3], const double iL[3])
+    {
+        uint32_t hi[3];
+        for (int a = 0; a < 3; ++a) {
+            double f = x[a] * iL[a];
+            f = f < 1.0 ? f * 0x1p32 : 0.0;  // x < L, but the product may round up to 1
+            const double fl = floor(f);
+            hi[a] = (uint32_t)fl;
+            lo[a][k] = (uint32_t)((f - fl) * 0x1p32);
+        }
+        xy[k] = make_int2((int)hi[0], (int)hi[1]);
+        zs[k].x = (int)hi[2];
+    }
+    __device__ Pos own(int k) const { return Pos{xy[k].x, xy[k].y, zs[k].x}; }
+    __device__ void sort_in(int q, int k) { sorted[q] = make_int4(xy[k].x, xy[k].y, zs[k].x, k); }
+    static __device__ int cell_axis(const Pos &p, int a, int g, const double[3])
+    {
+        return (int)__umulhi((uint32_t)(a == 0 ? p.x : a == 1 ? p.y : p.z), (uint32_t)g);
+    }
+    static __device__ void sub(const Pos &p, int x, int y, int z, const Scale &H, float d[3])
+    {
+        d[0] = (float)(int)((uint32_t)p.x - (uint32_t)x) * H.h[0];
+        d[1] = (float)(int)((uint32_t)p.y - (uint32_t)y) * H.h[1];
+        d[2] = (float)(int)((uint32_t)p.z - (uint32_t)z) * H.h[2];
+    }
+    // d = x_i - x_j, minimum image
+    __device__ void diff(const Pos &p, int j, const Scale &H, float d[3]) const
+    {
+        const int2 q = xy[j];
+        sub(p, q.x, q.y, zs[j].x, H, d);
+    }
+    __device__ void diff_s(const Pos &p, int j, const Scale &H, float d[3], float &s) const
+    {
+        const int2 q = xy[j], r = zs[j];
+        sub(p, q.x, q.y, r.x, H, d);
+        s = __int_as_float(r.y);
+    }
+    __device__ int diff_sorted(const Pos &p, int q, const Scale &H, float d[3]) const
+    {
+        const int4 v = sorted[q];
+        sub(p, v.x, v.y, v.z, H, d);
+        return v.w;
+    }
+    // squared distance in FP64 from the whole fractions
+    __device__ double r2_64(int i, int j, const double L[3]) const
+    {
+        const uint32_t hi[3] = {(uint32_t)xy[i].x, (uint32_t)xy[i].y, (uint32_t)zs[i].x};
+        const uint32_t hj[3] = {(uint32_t)xy[j].x, (uint32_t)xy[j].y, (uint32_t)zs[j].x};
+        double d[3];
+        for (int a = 0; a < 3; ++a) {
+            const uint64_t u = (((uint64_t)hi[a] << 32) | lo[a][i]) - (((uint64_t)hj[a] << 32) | lo[a][j]);
+            const double f = (double)(int)(uint32_t)(u >> 32) + (double)(uint32_t)u * 0x1p-32;
+            d[a] = f * (L[a] * 0x1p-32);
+        }
+        return (d[0] * d[0] + d[1] * d[1]) + d[2] * d[2];
+    }
+    __device__ void set_s(int k, float v) { zs[k].y = __float_as_int(v); }
+    __device__ float get_s(int k) const { return __int_as_float(zs[k].y); }
+};
+
+template <> struct ResLds<double> {
+    double *x[3], *s, *A;
+    int *tag;            // list build: tags by cell, then by tag
+    int *cell;
+    uint16_t *order;
+    static size_t bytes(int n) { return (size_t)n * (40 + 4 + 4 + 2) + 64; }
+    __device__ void carve(unsigned char *p, int n)
+    {
+        for (int a = 0; a < 3; ++a) x[a] = (double *)p + a * n;
+        s = x[2] + n;
+        A = s + n;
+        tag = (int *)(A + n);
+        cell = tag + n;
+        order = (uint16_t *)(cell + n + 2);
+    }
+    struct Pos { double x, y, z; };
+    struct Scale { double L[3], iL[3]; };
+    static __device__ Scale scale(const double L[3])
+    {
+        return Scale{{L[0], L[1], L[2]}, {1.0 / L[0], 1.0 / L[1], 1.0 / L[2]}};
+    }
+    __device__ void put(int k, const double q[3], const double[3])
+    {
+        for (int a = 0; a < 3; ++a) x[a][k] = q[a];
+    }
+    __device__ Pos own(int k) const { return Pos{x[0][k], x[1][k], x[2][k]}; }
+    __device__ void sort_in(int q, int k) { tag[q] = k; }
+    static __device__ int cell_axis(const Pos &p, int a, int g, const double iL[3])
+    {
+        const int c = (int)((a == 0 ? p.x : a == 1 ? p.y : p.z) * iL[a] * (double)g);
+        return c < 0 ? 0 : (c >= g ? g - 1 : c);
+    }
+    __device__ void diff(const Pos &p, int j, const Scale &H, double d[3]) const
+    {
+        d[0] = p.x - x[0][j];
+        d[1] = p.y - x[1][j];
+        d[2] = p.z - x[2][j];
+        for (int a = 0; a < 3; ++a) d[a] = fma(-H.L[a], rint(d[a] * H.iL[a]), d[a]);
+    }
+    __device__ void diff_s(const Pos &p, int j, const Scale &H, double d[3], double &sj) const
+    {
+        diff(p, j, H, d);
+        sj = s[j];
+    }
+    __device__ int diff_sorted(const Pos &p, int q, const Scale &H, double d[3]) const
+    {
+        const int j = tag[q];
+        diff(p, j, H, d);
+        return j;
+    }
+    __device__ void set_s(int k, double v) { s[k] = v; }
+    __device__ double get_s(int k) const { return s[k]; }
+};
+
+// Visit the nn list entries of the particle at slot i, in order; fn(j).
+template <class F>
+__device__ __forceinline__ void res_list(const uint4 *nl, int64_t S_, int64_t i, int nn, F &&fn)
+{
+    const uint4 *lp = nl + i;
+    const int nfull = nn / CHUNK, rest = nn % CHUNK;
+    uint4 q = nn > 0 ? lp[0] : make_uint4(0u, 0u, 0u, 0u);
+    for (int c = 0; c < nfull; ++c) {
+        const uint4 qn = (c + 1) * CHUNK < nn ? lp[(size_t)(c + 1) * S_] : q;
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int e = 0; e < CHUNK; ++e) fn((int)((w[e >> 1] >> (16 * (e & 1))) & 0xffffu));
+        q = qn;
+    }
+    if (rest) {
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int e = 0; e < CHUNK - 1; ++e)
+            if (e < rest) fn((int)((w[e >> 1] >> (16 * (e & 1))) & 0xffffu));
+    }
+}
+
+template <class Real, bool THERMO>
+__global__ void __launch_bounds__(RES_MAX_N) k_resident(Buffers B, Launch P, int cur, int nsteps, int k0,
+                                                        int max_n, StepArgs st)
+{
+    extern __shared__ __align__(32) unsigned char smem[];
+    __shared__ int nwin, wsum[RES_MAX_N / VBC_WAVE];
+    __shared__ unsigned long long evals_s, ent_s;
+    __shared__ double red[8][RES_MAX_N / VBC_WAVE];
+    const int r = blockIdx.x;
+    const RepDev &R = B.reps[r];
+    const int n = (int)R.n;
+    // an empty slot; a larger replica is not reached: the launch takes the largest of the set
+    if (!R.resident || n <= 0 || n > max_n) return;
+    const int k = threadIdx.x, nt = blockDim.x, wv = k / VBC_WAVE, ln = k % VBC_WAVE;
+    const bool own = k < n;
+    const int64_t S_ = P.nslots, base = R.p_off, i = base + k;
+    // every condition around a barrier is made a scalar: the compiler takes what it loads into
+    // vector registers as different per lane, and splits a loop with a barrier in it between the
+    // lanes that leave and those that stay
+    const uint32_t fl = (uint32_t)__builtin_amdgcn_readfirstlane((int)B.flags[r]);
+    auto any_thread = [](bool v) { return __builtin_amdgcn_readfirstlane(__syncthreads_or(v)) != 0; };
+    const double L[3] = {R.L[0], R.L[1], R.L[2]};
+    const double iL[3] = {1.0 / L[0], 1.0 / L[1], 1.0 / L[2]};
+    const double disp2 = R.disp2;
+    const uint64_t key = st.seed + R.seed;
+    using Lds = ResLds<Real>;
+    Lds T;
+    T.carve(smem, max_n);
+    const typename Lds::Scale H = Lds::scale(L);
+    const PairR<Real> p0 = pair_r<Real>(R.pair[0], R.rc2);
+    const PairDev &pd = R.pair[0];
+    const double wx1 = pd.x1, wx2 = pd.x2;
+    const bool watt = pd.attract;
+    double *X = B.x[cur];
+    bool bad = false;
+
+    // ---- the state: from the brick layout by way of the next layout's space, or in place ----
+    double x[3] = {0, 0, 0}, v[3] = {0, 0, 0}, xr[3] = {0, 0, 0}, F[3] = {0, 0, 0};
+    if (!(fl & FLAG_FULL)) {
+        for (int lb = wv; lb < R.nbrick; lb += nt / VBC_WAVE) {
+            const int cnt = B.bcnt[0][R.b_off + lb];
+            for (int t = ln; t < cnt; t += VBC_WAVE) {
+                const int64_t j = base + (int64_t)lb * R.bcap + t, d = base + B.tag[j];
+                for (int a = 0; a < 3; ++a) {
+                    B.xs[3 * d + a] = X[3 * j + a];
+                    B.vs[a * S_ + d] = B.v[a * S_ + j];
+                }
+            }
+        }
+        __syncthreads();
+    }
+    if (own) {
+        for (int a = 0; a < 3; ++a) {
+            double t = (fl & FLAG_FULL) ? X[3 * i + a] : B.xs[3 * i + a];
+            if (!isfinite(t)) {
+                bad = true;
+                t = 0.0;
+            }
+            x[a] = wrap1(t, L[a]);
+            v[a] = (fl & FLAG_FULL) ? B.v[a * S_ + i] : B.vs[a * S_ + i];
+            F[a] = B.Fst[a * S_ + i];
+            xr[a] = B.xref[a * S_ + i];
+        }
+        B.tag[i] = k;
+    }
+
+    uint64_t step = B.step[r];
+    const bool need_eval = !(fl & FLAG_RES);
+    bool moved = false;  // the list is due (scalar)
+    int nn = own ? (int)B.nn[i] : 0;
+
+    // after a drift: wrap, and whether the particle has left its buffer
+    auto drifted = [&]() {
+        double d2 = 0.0;
+        for (int a = 0; a < 3; ++a) {
+            x[a] = wrap1(x[a], L[a]);
+            if (!isfinite(x[a])) {
+                bad = true;
+                x[a] = 0.0;
+            }
+            double dd = x[a] - xr[a];
+            dd -= L[a] * rint(dd * iL[a]);
+            d2 += dd * dd;
+        }
+        return d2 > disp2;
+    };
+
+    if (!need_eval) {
+        bool mv = false;
+        if (own) {
+            integrate_one(st, MODE_MID, true, F, v, x, key, (uint64_t)k, step);
+            mv = drifted();
+        }
+        moved = any_thread(mv);
+    }
+
+    // step -1 evaluates the forces that the opening half-kick needs where none are stored; step
+    // -2 makes a list lost to the brick layout again from its own reference positions
+    const int m0 = need_eval ? ((fl & FLAG_XREF) ? -2 : -1) : 0;
+    for (int m = m0; m < nsteps; ++m) {
+        // ---- positions into LDS; a list when one is due ----
+        if (own) T.put(k, m == -2 ? xr : x, iL);
+        if (k == 0) {
+            nwin = 0;
+            evals_s = 0ull;
+            ent_s = 0ull;
+        }
+        __syncthreads();
+        if ((need_eval && m == m0) || moved) {
+            moved = false;
+            const typename Lds::Pos pi = own ? T.own(k) : typename Lds::Pos{};
+            if (m > -2 && own) {
+                bool lost = false;
+                for (int a = 0; a < 3; ++a) {
+                    // further than one cell since the last build: unstable dynamics
+                    const int dc = abs(cell_of(x[a], R.h[a], R.nc[a]) - cell_of(xr[a], R.h[a], R.nc[a]));
+                    if (m >= 0 && min(dc, R.nc[a] - dc) > 1) lost = true;
+                    xr[a] = x[a];
+                }
+                if (lost) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_LOST);
+            }
+            // cells: at most one per particle, none smaller than the list radius; in a small
+            // system every particle is a candidate, in one cell
+            const bool all = n < 128;
+            int g[3] = {1, 1, 1};
+            if (!all) {
+                int c = 3;
+                while (c < 10 && (c + 1) * (c + 1) * (c + 1) <= n) ++c;
+                for (int a = 0; a < 3; ++a) g[a] = min(c, R.nc[a]);
+            }
+            const int ncell = g[0] * g[1] * g[2];
+            const int cx = all ? 0 : Lds::cell_axis(pi, 0, g[0], iL), cy = all ? 0 : Lds::cell_axis(pi, 1, g[1], iL),
+                      cz = all ? 0 : Lds::cell_axis(pi, 2, g[2], iL);
+            const int cid = cx + g[0] * (cy + g[1] * cz);
+            if (k < ncell) T.cell[k] = 0;  // ncell <= n <= threads
+            __syncthreads();
+            if (own) atomicAdd(&T.cell[cid], 1);
+            __syncthreads();
+            {
+                const int c = k < ncell ? T.cell[k] : 0;
+                int incl = c;
+#pragma unroll
+                for (int o = 1; o < VBC_WAVE; o <<= 1) {
+                    const int t = __shfl_up(incl, o, VBC_WAVE);
+                    if (ln >= o) incl += t;
+                }
+                if (ln == VBC_WAVE - 1) wsum[wv] = incl;
+                __syncthreads();
+                int off = incl - c;
+                for (int w = 0; w < wv; ++w) off += wsum[w];
+                if (k < ncell) T.cell[k] = off;
+            }
+            __syncthreads();
+            // members in any order (a cell's counter runs to its end), then ranked by tag
+            if (own) T.order[atomicAdd(&T.cell[cid], 1)] = (uint16_t)k;
+            __syncthreads();
+            // cell c now ends at cell[c], where the next one starts
+            auto begin = [&](int c) { return c ? T.cell[c - 1] : 0; };
+            if (own) {
+                const int lo = begin(cid), hi = T.cell[cid];
+                int rank = lo;
+                for (int j = lo; j < hi; ++j) rank += (int)T.order[j] < k ? 1 : 0;
+                T.sort_in(rank, k);
+            }
+            __syncthreads();
+            const Real rl2 = (Real)(R.rlist2 * (1.0 + 1e-6));
+            const int kmax = P.k_max;
+            bool ovf = false;
+            if (own) {
+                int e = 0;
+                nn = 0;
+                uint32_t b0 = 0u, b1 = 0u, b2 = 0u, b3 = 0u;
+                uint4 *wp = B.nl + i;
+                auto chunk = [&] {  // the oldest entry first
+                    return make_uint4((b3 >> 16) | (b3 << 16), (b2 >> 16) | (b2 << 16), (b1 >> 16) | (b1 << 16),
+                                      (b0 >> 16) | (b0 << 16));
+                };
+                auto push = [&](uint32_t j) {
+                    b3 = __builtin_amdgcn_alignbit(b3, b2, 16);
+                    b2 = __builtin_amdgcn_alignbit(b2, b1, 16);
+                    b1 = __builtin_amdgcn_alignbit(b1, b0, 16);
+                    b0 = (b0 << 16) | j;
+                };
+                // segments of up to 32 candidates: a tight loop marks those within the radius, a
+                // second one appends only the marked (as the list build of the bricks)
+                auto visit = [&](int lo, int hi) {
+                    for (int q0 = lo; q0 < hi; q0 += 32) {
+                        const int cnt = min(32, hi - q0);
+                        uint32_t near = 0u;
+                        for (int q = 0; q < cnt; ++q) {
+                            Real d[3];
+                            const int j = T.diff_sorted(pi, q0 + q, H, d);
+                            const Real r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                            near |= (r2 < rl2 && j != k) ? 1u << q : 0u;
+                        }
+                        while (near) {
+                            const int q = __builtin_ctz(near);
+                            near &= near - 1u;
+                            uint32_t j;
+                            if constexpr (sizeof(Real) == 4) j = (uint32_t)T.sorted[q0 + q].w;
+                            else j = (uint32_t)T.tag[q0 + q];
+                            push(j);
+                            ++nn;
+                            if (++e == CHUNK) {
+                                if (nn <= kmax) *wp = chunk();
+                                wp += S_;
+                                e = 0;
+                            }
+                        }
+                    }
+                };
+                if (all) {
+                    visit(0, n);
+                } else {
+                    for (int dz = -1; dz <= 1; ++dz)
+                        for (int dy = -1; dy <= 1; ++dy) {
+                            const int z = cz + dz + (cz + dz < 0 ? g[2] : 0) - (cz + dz >= g[2] ? g[2] : 0);
+                            const int y = cy + dy + (cy + dy < 0 ? g[1] : 0) - (cy + dy >= g[1] ? g[1] : 0);
+                            const int row = g[0] * (y + g[1] * z);
+                            // three cells along x: one range, or two where the row wraps
+                            visit(begin(row + max(cx - 1, 0)), T.cell[row + min(cx + 1, g[0] - 1)]);
+                            if (cx == 0) visit(begin(row + g[0] - 1), T.cell[row + g[0] - 1]);
+                            if (cx == g[0] - 1) visit(begin(row), T.cell[row]);
+                        }
+                }
+                if (e && nn <= kmax) {
+                    for (; e < CHUNK; ++e) push(0u);
+                    *wp = chunk();
+                }
+                if (nn > kmax) {
+                    ovf = true;
+                    nn = kmax;
+                }
+                B.nn[i] = (uint16_t)nn;
+            }
+            if (ovf) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_NLIST_OVERFLOW);
+            const unsigned long long entries = wave_sum((unsigned long long)nn);
+            if (ln == 0 && entries) atomicAdd(&ent_s, entries);
+            for (int lb = k; lb < R.nbrick; lb += nt) B.bentries[R.b_off + lb] = 0u;
+            __syncthreads();
+            if (k == 0) {
+                B.bentries[R.b_off] = (uint32_t)ent_s;
+                if (m > -2) B.stats[4 * r + 0] += 1ull;  // not for the same list made again
+            }
+        }
+        if (m == -2) continue;
+
+        // ---- counts ----
+        const bool stats = m < 0 || (k0 + m) % 8 == 0;
+        const typename Lds::Pos pi = own ? T.own(k) : typename Lds::Pos{};
+        int inside = 0;
+        if (own) {
+            double nc = 0.0;
+            Real part = Real(0);
+            int e = 0;
+            res_list(B.nl, S_, i, nn, [&](int j) {
+                Real d[3];
+                T.diff(pi, j, H, d);
+                const Real r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                if (stats) inside += r2 < p0.rc2 ? 1 : 0;
+                const Real uu = clamp01(fma(sqrt_r(r2), p0.inv_dw, p0.nrl_dw));
+                const Real qq = fma(-uu, uu, Real(1));
+                part = fma(qq, qq, part);
+                if (++e == CHUNK) {
+                    nc += (double)part;
+                    part = Real(0);
+                    e = 0;
+                }
+            });
+            nc += (double)part;
+            const double mg = sizeof(Real) == 4 ? COUNT_MARGIN : 0.0;
+            T.A[k] = Real(0);
+            if (watt && nc > wx1 - mg && nc < wx2 + mg) {
+                T.order[atomicAdd(&nwin, 1)] = (uint16_t)k;
+                B.nd[i] = nc;
+            }
+            T.set_s(k, (Real)omega_d64(nc, wx1, wx2));
+        }
+        if (stats) {
+            const int ev = wave_sum(inside);
+            if (ln == 0 && ev) atomicAdd(&evals_s, (unsigned long long)ev);
+        }
+        __syncthreads();
+        const int nw = __builtin_amdgcn_readfirstlane(nwin);
+        if (m >= 0) ++step;
+        if (stats && k == 0) {
+            B.bevals[R.b_off] += evals_s;
+            B.stats[4 * r + 3] += 1ull;
+        }
+
+        // ---- particles in a switching window, eight lanes each: recount, dU/dn ----
+        if (nw > 0) {
+            const int e = k % CHUNK, grp = k / CHUNK, ng = nt / CHUNK;
+            if constexpr (sizeof(Real) == 4) {
+                for (int w = grp; w < nw; w += ng) {
+                    const int kw = T.order[w], nj = B.nn[base + kw];
+                    double acc = 0.0;
+                    for (int c = 0; c * CHUNK < nj; ++c)
+                        if (c * CHUNK + e < nj) {
+                            const int j = ((const uint16_t *)(B.nl + (size_t)c * S_ + base + kw))[e];
+                            acc += count_term64(T.r2_64(kw, j, L), pd);
+                        }
+#pragma unroll
+                    for (int o = CHUNK / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, CHUNK);
+                    if (e == 0) {
+                        B.nd[base + kw] = acc;
+                        T.set_s(kw, (Real)omega_d64(acc, wx1, wx2));
+                    }
+                }
+                __syncthreads();
+            }
+            for (int w = grp; w < nw; w += ng) {
+                const int kw = T.order[w], nj = B.nn[base + kw];
+                const typename Lds::Pos pw = T.own(kw);
+                double acc = 0.0;
+                for (int c = 0; c * CHUNK < nj; ++c)
+                    if (c * CHUNK + e < nj) {
+                        const int j = ((const uint16_t *)(B.nl + (size_t)c * S_ + base + kw))[e];
+                        Real d[3], sj;
+                        T.diff_s(pw, j, H, d, sj);
+                        const Real r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                        const Real uu = (sqrt_r(r2) - p0.m) * p0.inv_w;
+                        const Real qq = Real(1) - uu * uu;
+                        if (qq > Real(0)) acc += (double)(sj * (-p0.E_a * qq * qq));
+                    }
+#pragma unroll
+                for (int o = CHUNK / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, CHUNK);
+                if (e == 0) T.A[kw] = (Real)(omega_dd64(B.nd[base + kw], wx1, wx2) * acc) * p0.c_c;
+            }
+            __syncthreads();
+        }
+
+        // ---- forces and the integrator ----
+        const int mode = m < 0 ? MODE_MID : (m == nsteps - 1 ? MODE_LAST : MODE_MID);
+        bool mv = false;
+        double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (own) {
+            const Real si = T.get_s(k), cAi = T.A[k], cai = p0.c_a * si;
+            Real fx = 0, fy = 0, fz = 0, ei = 0, ea = 0;
+            Real wxx = 0, wyy = 0, wzz = 0, wxy = 0, wxz = 0, wyz = 0;
+            // the terms of k_force's one-type path
+            res_list(B.nl, S_, i, nn, [&](int j) {
+                Real d[3], sj;
+                T.diff_s(pi, j, H, d, sj);
+                const Real cAj = T.A[j];
+                const Real r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+                const Real rinv = rsqrt_r(r2 > Real(1e-30) ? r2 : Real(1e-30));
+                const Real rr = r2 * rinv;
+                const Real pr = fmin(fma(r2, p0.k_r, p0.c_r), Real(0));
+                const Real uu = fma(rr, p0.inv_w, p0.nm_w);
+                const Real qq = fmax(fma(-uu, uu, Real(1)), Real(0));
+                const Real uc = clamp01(fma(rr, p0.inv_dw, p0.nrl_dw));
+                const Real gg = uc * fma(-uc, uc, Real(1));
+                const Real t = fma(cAi + cAj, gg, cai * sj * uu * qq);
+                const Real phr = fma(t, rinv, pr);
+                fx -= phr * d[0];
+                fy -= phr * d[1];
+                fz -= phr * d[2];
+                if (THERMO) {
+                    const Real tc = fmax(fma(-r2, p0.inv_rr2, Real(1)), Real(0));
+                    ei = fma(tc, tc, ei);
+                    ea = fma(sj * qq, qq, ea);
+                    wxx -= phr * d[0] * d[0];
+                    wyy -= phr * d[1] * d[1];
+                    wzz -= phr * d[2] * d[2];
+                    wxy -= phr * d[0] * d[1];
+                    wxz -= phr * d[0] * d[2];
+                    wyz -= phr * d[1] * d[2];
+                }
+            });
+            F[0] = (double)fx;
+            F[1] = (double)fy;
+            F[2] = (double)fz;
+            if (!(isfinite(F[0]) && isfinite(F[1]) && isfinite(F[2]))) bad = true;
+            if (THERMO) {
+                acc[0] = 0.5 * (double)(p0.E_r * ei - p0.E_a * si * ea);
+                acc[2] = 0.5 * (double)wxx;
+                acc[3] = 0.5 * (double)wyy;
+                acc[4] = 0.5 * (double)wzz;
+                acc[5] = 0.5 * (double)wxy;
+                acc[6] = 0.5 * (double)wxz;
+                acc[7] = 0.5 * (double)wyz;
+            }
+            integrate_one(st, mode, m < 0, F, v, x, key, (uint64_t)k, step);
+            if (mode != MODE_LAST) mv = drifted();
+        }
+        if (THERMO) {
+            const double w = wave_sum8(acc);
+            if ((ln & 7) == 0) red[ln >> 3][wv] = w;
+        }
+        moved = any_thread(mv);
+        if (THERMO && m >= 0 && k < 8) {
+            // 64 consecutive tags at a time, whatever the workgroup's size
+            const int nb = (n + VBC_WAVE - 1) / VBC_WAVE;
+            double sum = 0.0;
+            if (k == 1) {
+                for (int w = 0; w < nb; ++w) sum += (red[2][w] + red[3][w]) + red[4][w];
+            } else {
+                for (int w = 0; w < nb; ++w) sum += red[k][w];
+            }
+            double *A = B.thermo + (size_t)r * THERMO_WORDS;
+            A[1 + k] = sum;
+            A[9 + k] += sum;
+            if (k == 0) A[0] += 1.0;
+        }
+    }
+    if (own)
+        for (int a = 0; a < 3; ++a) {
+            X[3 * i + a] = x[a];
+            B.v[a * S_ + i] = v[a];
+            B.Fst[a * S_ + i] = F[a];
+            B.xref[a * S_ + i] = xr[a];
+        }
+    if (bad) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_NONFINITE);
+    if (k == 0) {
+        B.step[r] = step;
+        atomicAnd(&B.flags[r], ~(uint32_t)VBC_FLAG_REBUILD);
+        atomicOr(&B.flags[r], (uint32_t)(FLAG_FULL | FLAG_RES | FLAG_XREF));
+    }
+}
+
+// ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
 
@@ -3202,6 +3826,33 @@ hipError_t launch_kick_drift(const Buffers &B, const Launch &P, int cur, const S
 {
     if (P.list == 0) launch_worklist(B, P, s);
     k_kick_drift<<<brick_grid(P.nb_launch), 256, 0, s>>>(B, P, cur, st);
+    return hipGetLastError();
+}
+
+// Whether a replica can take its steps in one workgroup (k_resident): one type that counts
+// every neighbour, no chains, and small enough for its LDS.
+bool resident_can(const RepDev &R)
+{
+    if (R.ntypes != 1 || R.chain_len || !(R.mask[0] & 1u)) return false;
+    if (R.n > RES_MAX_N) return false;
+    for (int a = 0; a < 3; ++a)
+        if (!(R.L[a] <= RES_MAX_L)) return false;
+    return true;
+}
+
+hipError_t launch_resident(const Buffers &B, const Launch &P, int cur, int nsteps, int k0, int max_n,
+                           const StepArgs &st, hipStream_t s)
+{
+    const int bs = std::max(128, (max_n + VBC_WAVE - 1) / VBC_WAVE * VBC_WAVE);  // a thread per particle
+    const bool fp64 = P.precision == VBC_FP64;
+    const size_t lds = fp64 ? ResLds<double>::bytes(max_n) : ResLds<float>::bytes(max_n);
+    if (fp64) {
+        if (st.acc) k_resident<double, true><<<P.nrep, bs, lds, s>>>(B, P, cur, nsteps, k0, max_n, st);
+        else k_resident<double, false><<<P.nrep, bs, lds, s>>>(B, P, cur, nsteps, k0, max_n, st);
+    } else {
+        if (st.acc) k_resident<float, true><<<P.nrep, bs, lds, s>>>(B, P, cur, nsteps, k0, max_n, st);
+        else k_resident<float, false><<<P.nrep, bs, lds, s>>>(B, P, cur, nsteps, k0, max_n, st);
+    }
     return hipGetLastError();
 }
 
