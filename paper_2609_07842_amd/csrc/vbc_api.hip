@@ -36,6 +36,7 @@ struct Caps {
     int32_t nrep = 0, ntypes_max = 1, any_chains = 0, any_excl = 0, any_mask = 0, bcap_max = 0, nh_max = 1, ncb_max = 1;
     int64_t ntot = 0, nslots = 0;
     int32_t nbrick = 0, ncell = 0;
+    double own_mean = 0.0, k_mean = 0.0;  // of the densest replica
 };
 
 struct Offsets {
@@ -293,6 +294,11 @@ vbc_status plan_replica(const vbc_replica_desc &d, int brick_target, double rho_
     double rl = rc + d.skin;
     R.rc2 = rc * rc;
     R.rlist2 = rl * rl;
+    R.scan.lo2 = (float)(R.rlist2 * (1.0 - 2e-5) - 1e-4);
+    R.scan.hi2 = (float)(R.rlist2 * (1.0 + 2e-5) + 1e-4);
+    R.scan.mid = 0.5f * (R.scan.lo2 + R.scan.hi2);
+    R.scan.half = 0.5f * (R.scan.hi2 - R.scan.lo2);
+    R.scan.reach = 1.01f * (float)rl;
     R.disp2 = 0.25 * d.skin * d.skin;
     int64_t ncell = 1;
     for (int a = 0; a < 3; ++a) {
@@ -492,6 +498,9 @@ Launch launch_for(const Caps &C, const vbc_options &opt)
     P.any_chains = C.any_chains;
     P.multi = (C.ntypes_max > 1 || C.any_excl || C.any_mask) ? 1 : 0;
     P.precision = opt.precision;
+    P.own_mean = C.own_mean;
+    P.k_mean = C.k_mean;
+    list_shape(P);
     return P;
 }
 
@@ -531,7 +540,7 @@ static vbc_status check_lds(vbc_handle h, const Launch &P)
     int lds_max = 0;
     e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
     if (e != hipSuccess) return hip_fail(h, e, "hipDeviceGetAttribute");
-    size_t need = std::max(std::max(lds_bytes_nlist(P), lds_bytes_count(P)),
+    size_t need = std::max(std::max(lds_need_nlist(P), lds_bytes_count(P)),
                            std::max(std::max(lds_bytes_embed(P), lds_bytes_force(P)),
                                     std::max(lds_bytes_sort(P), lds_bytes_bonds(P))));
     if (need + 2048 > (size_t)lds_max) {
@@ -972,6 +981,8 @@ static vbc_status plan_set(const vbc_replica_desc *reps, int32_t nrep, const vbc
         if (C.nslots >= ((int64_t)1 << 31) - 1 || C.nbrick >= (1 << 30) || C.ncell >= (1 << 30))
             return fail(VBC_ERR_ARG, "more than 2^31 slots in total");
     }
+    C.own_mean = own_mean_max;
+    C.k_mean = k_mean_max;
     if (!opt.block) opt.block = block_for(own_mean_max);
     int k_auto = k_max_for(k_mean_max), s_auto = stage_cap_for(rho_cell_max, C.nh_max);
     for (const RepPlan &p : plans) {
@@ -1154,10 +1165,17 @@ vbc_status vbc_admit(vbc_handle h, const vbc_replica_desc *d, const double *d_x,
     int32_t r = -1;
     st = place(h, rp, s, &r);
     if (st != VBC_OK) return st;
-    if (h->auto_block && block_for(rp.own_mean) > h->P.block) {
-        // the first replicas of a pool set its workgroup size (it never shrinks, so a stream
-        // of requests recaptures the step graphs once or twice); results do not depend on it
-        h->P.block = h->opt.block = block_for(rp.own_mean);
+    // the first replicas of a pool set its workgroup sizes (they never shrink, so a stream of
+    // requests recaptures the step graphs once or twice); results do not depend on them
+    Launch Q = h->P;
+    if (h->auto_block) Q.block = std::max(Q.block, block_for(rp.own_mean));
+    Q.own_mean = std::max(Q.own_mean, rp.own_mean);
+    Q.k_mean = std::max(Q.k_mean, rp.k_mean);
+    list_shape(Q);
+    const bool resized = Q.block != h->P.block || Q.list_block != h->P.list_block || Q.list_win != h->P.list_win;
+    h->P = Q;
+    if (resized) {
+        h->opt.block = Q.block;
         for (auto &g : h->graphs) h->retired.push_back(g.exec);  // other replicas' steps may be running
         h->graphs.clear();
     }

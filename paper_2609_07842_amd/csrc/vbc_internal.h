@@ -41,6 +41,13 @@ struct PairDev {
     int32_t pad;
 };
 
+// The list build's FP32 thresholds around the squared list radius (set with rlist2).
+struct ScanDev {
+    float lo2, hi2;  // below lo2 the staged positions put a pair in the list, above hi2 out of it
+    float mid, half; // middle and half width of [lo2, hi2]
+    float reach;     // a little more than the list radius
+};
+
 struct RepDev {
     int64_t p_off;         // first slot of this replica
     int64_t n;             // particles
@@ -62,6 +69,7 @@ struct RepDev {
     double L[3], h[3];
     double rc2;            // largest interaction cutoff squared
     double rlist2;         // list radius squared (FP64, exact comparison)
+    ScanDev scan;
     double disp2;          // squared displacement that triggers a rebuild ((skin/2)^2)
     double k_bond, r0_bond;
     uint64_t seed;         // added to the integrator's seed: this replica's noise key
@@ -86,7 +94,8 @@ struct Buffers {
                              // halo are one contiguous run), double-buffered by step parity
     double *v;               // velocities SoA [3][nslots]
     double *Fst;             // forces kept between calls SoA [3][nslots]
-    double *xref;            // positions at the last build SoA [3][nslots]
+    double *xref;            // resident replicas: positions at the last build SoA [3][nslots];
+                             // the others have those in xs, and this is scratch
     int32_t *tag;            // [nslots]
     int32_t *type;           // [nslots]
     uint8_t *lcell;          // [nslots] cell of the particle inside its brick
@@ -137,6 +146,8 @@ struct Launch {
     int32_t k_max;           // multiple of CHUNK
     int32_t nchunk;          // k_max / CHUNK
     int32_t block;
+    int32_t list_block;      // threads of the list build and entries of its output windows
+    int32_t list_win;        // (list_shape)
     int32_t stage_cap;
     int32_t nh_max;          // max halo-grid cells of any brick
     int32_t bcap_max;
@@ -148,6 +159,8 @@ struct Launch {
     // host side only: the one replica of a fixed single-replica handle (not a pool), whose
     // descriptor the count and force passes then take as a kernel argument; else null
     const RepDev *one;
+    // host side only: largest mean number of own particles of a brick and of list entries
+    double own_mean, k_mean;
 };
 
 // The replica descriptor as a kernel argument (ONE) or nothing.
@@ -249,6 +262,8 @@ hipError_t launch_resident(const Buffers &B, const Launch &P, int cur, int nstep
 bool resident_can(const RepDev &R);
 size_t lds_bytes_sort(const Launch &P);
 size_t lds_bytes_nlist(const Launch &P);
+size_t lds_need_nlist(const Launch &P);
+void list_shape(Launch &P);  // the list build's workgroup and windows, by own_mean and k_mean
 size_t lds_bytes_count(const Launch &P);
 size_t lds_bytes_embed(const Launch &P);
 size_t lds_bytes_bonds(const Launch &P);

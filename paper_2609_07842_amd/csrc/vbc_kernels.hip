@@ -189,25 +189,38 @@ __device__ __forceinline__ double wave_sum8(const double (&a)[8])
 
 // Exclusive scan of a[0..n) in place by the first wave; returns the total (valid in the
 // first wave).  Call from all threads of the block between barriers.
-__device__ __forceinline__ int wave0_exclusive_scan(int *a, int n)
+// Sum of v over this and the lower lanes of the wave: shifts within rows of sixteen, then the
+// last lane of each row and of the lower half handed up, all in the vector unit (the same by
+// lane shuffles through LDS took 1.2 us for 216 cells).
+__device__ __forceinline__ int wave_inclusive_sum(int v)
 {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// Exclusive scan of a[0..n) by one whole wave; the total.
+__device__ __forceinline__ int wave_exclusive_scan(int *a, int n)
+{
+    const int lane = threadIdx.x % VBC_WAVE;
     int carry = 0;
-    if (threadIdx.x < VBC_WAVE) {
-        int lane = threadIdx.x;
-        for (int base = 0; base < n; base += VBC_WAVE) {
-            int q = base + lane;
-            int v = q < n ? a[q] : 0;
-            int incl = v;
-#pragma unroll
-            for (int o = 1; o < VBC_WAVE; o <<= 1) {
-                int t = __shfl_up(incl, o, VBC_WAVE);
-                if (lane >= o) incl += t;
-            }
-            if (q < n) a[q] = carry + incl - v;
-            carry += __shfl(incl, VBC_WAVE - 1, VBC_WAVE);
-        }
+    for (int base = 0; base < n; base += VBC_WAVE) {
+        const int q = base + lane;
+        const int v = q < n ? a[q] : 0;
+        const int incl = wave_inclusive_sum(v);
+        if (q < n) a[q] = carry + incl - v;
+        carry += __builtin_amdgcn_readlane(incl, VBC_WAVE - 1);
     }
     return carry;
+}
+
+__device__ __forceinline__ int wave0_exclusive_scan(int *a, int n)
+{
+    return threadIdx.x < VBC_WAVE ? wave_exclusive_scan(a, n) : 0;
 }
 
 // Wrap one coordinate into [0, L).
@@ -290,17 +303,12 @@ __device__ __forceinline__ void brick_geometry(const RepDev &R, int lb, StageHdr
 // Lay out the staging of brick b (local index lb) of replica R from a set of cell tables:
 // own particles first (the brick's slot range), then every halo cell of the (e+2)^3 grid
 // in x-fastest order.  All threads of the block call this.
-__device__ void stage_tables(const RepDev &R, int b, int lb, const int32_t *brick_rank0,
-                             const int32_t *cell_rank, const int32_t *cstart,
-                             const int32_t *ccnt, const int32_t *bcnt, StageHdr &S,
-                             StageTabs T, int stage_cap)
+// The cells of a brick's halo grid: first slot, count, image shift, staged offset of the own
+// ones (-1: halo) and the halo counts; all: every cell's count, if asked.
+__device__ __forceinline__ void stage_cells(const RepDev &R, const StageHdr &S, const int32_t *cell_rank,
+                                            const int32_t *cstart, const int32_t *ccnt, StageTabs T,
+                                            int *all)
 {
-    if (threadIdx.x == 0) {
-        brick_geometry(R, lb, S);
-        S.rank0 = brick_rank0[b];
-        S.n_own = bcnt[b];
-    }
-    __syncthreads();
     for (int q = threadIdx.x; q < S.nh; q += blockDim.x) {
         int h[3] = {q % S.H[0], (q / S.H[0]) % S.H[1], q / (S.H[0] * S.H[1])};
         int g[3], w = 0;
@@ -320,7 +328,22 @@ __device__ void stage_tables(const RepDev &R, int b, int lb, const int32_t *bric
         T.q_w[q] = w;
         T.q_off[q] = own ? (int)(st - S.base) : -1;
         T.q_hpre[q] = own ? 0 : cnt;
+        if (all) all[q] = cnt;
     }
+}
+
+__device__ void stage_tables(const RepDev &R, int b, int lb, const int32_t *brick_rank0,
+                             const int32_t *cell_rank, const int32_t *cstart,
+                             const int32_t *ccnt, const int32_t *bcnt, StageHdr &S,
+                             StageTabs T, int stage_cap)
+{
+    if (threadIdx.x == 0) {
+        brick_geometry(R, lb, S);
+        S.rank0 = brick_rank0[b];
+        S.n_own = bcnt[b];
+    }
+    __syncthreads();
+    stage_cells(R, S, cell_rank, cstart, ccnt, T, nullptr);
     __syncthreads();
     int tot = wave0_exclusive_scan(T.q_hpre, S.nh);
     if (threadIdx.x == 0) {
@@ -905,266 +928,378 @@ __global__ void k_resort(Buffers B, Launch P, int cur)
 //
 // The candidate scan reads a second copy of the staged positions in LDS, laid out in the
 // x-fastest order of the whole (e+2)^3 cell grid, own and halo cells together: the three
-// cells of a stencil row along x are then one contiguous range, and a lane walks 9 ranges
+// cells of a stencil row along x are then one contiguous range, and a particle has 9 ranges
 // instead of 27 cells (a wave pays the longest range among its lanes, about 20 % fewer
 // iterations).  Entries are the staging-order indices, so the lists are the same.
+//
+// Three lanes scan for one particle, a plane of the stencil (three rows) each: first the masks
+// of its rows' neighbours, then, with the lanes' counts added up, the entries, gathered in LDS
+// and written out as chunks.  What bounds a build is the chain of one wave: LDS reads, the
+// loop over a row's candidates and the loop over its entries, at two waves per SIMD or fewer.
+// With one lane per particle a workgroup took 25 to 27 us at density 0.3 (scan 16) and 20 at
+// 0.05 (7.7 of them the staging, a memory round trip per few cells); now 13 and 9.  At density
+// 0.5 and a million particles a build takes 10 % less, near the issue rate of the test of
+// some 270 candidates per particle.  The registers must stay below 80 with none spilled: a
+// kernel that uses scratch memory costs 0.5 us more in every step without a build.
 #ifndef NLIST_ATTR
 #define NLIST_ATTR __attribute__((amdgpu_waves_per_eu(6)))
 #endif
 #ifndef SCAN_UNROLL
 #define SCAN_UNROLL 4  // candidate positions read ahead in the list build's scan
 #endif
-__global__ void NLIST_ATTR k_nlist(Buffers B, Launch P, int cur)
+constexpr int NL_PPW = VBC_WAVE / 3;  // particles of one wave (its last lane idles)
+
+__global__ void __launch_bounds__(1024) NLIST_ATTR k_nlist(Buffers B, Launch P, int cur)
 {
     extern __shared__ __align__(32) unsigned char smem[];
-    __shared__ StageHdr S;
-    __shared__ unsigned long long lost_sum, ent_sum;
-    __shared__ unsigned pmax_bits;  // largest |p|^2 of the staged positions (FP32 bits)
+    __shared__ unsigned long long lost_sum;
+    __shared__ unsigned ent_sum;
+    __shared__ int halo_s;          // staged particles of the halo cells
     int b, r;
     const uint32_t fl0 = B.flags[0];  // as in k_resort
     if (!resolve_brick(P, B, b, r)) return;
     if (!((r == 0 ? fl0 : B.flags[r]) & P.due)) return;
     const RepDev &R = B.reps[r];
-    int lb = b - R.b_off;
-    int nh_cap = (P.nh_max + 3) & ~3;
+    const int lb = b - R.b_off;
+    const int nh_cap = (P.nh_max + 3) & ~3;
     StageTabs T = carve_tabs(smem, nh_cap);
     float4 *hpos = (float4 *)after_tabs(smem, nh_cap);    // staged positions, grid order
     int *hq = (int *)(hpos + P.stage_cap + SCAN_UNROLL);  // first grid-order index of each cell
-    uint16_t *conv = (uint16_t *)(hq + nh_cap + 4);      // grid order -> staging order
+    uint16_t *wbuf = (uint16_t *)(hq + nh_cap + 4);       // entries on their way out, per particle
+    const int bstride = P.list_win + CHUNK;
+    uint16_t *conv = wbuf + (blockDim.x / VBC_WAVE) * (NL_PPW * bstride);  // grid order -> staging order
     const int64_t S_ = P.nslots;
 
+    // every thread forms the header itself (uniform values)
+    StageHdr S;
+    brick_geometry(R, lb, S);
+    S.rank0 = B.brick_rank0[b];
+    S.n_own = B.bcnt[1][b];
     if (threadIdx.x == 0) {
         lost_sum = 0ull;
-        ent_sum = 0ull;
-        pmax_bits = 0u;
+        ent_sum = 0u;
     }
-    stage_tables(R, b, lb, B.brick_rank0, B.cell_rank, B.cstart[1], B.ccnt[1], B.bcnt[1], S, T,
-                 P.stage_cap);
-
-    // next layout -> live for the own range and the own cell tables
-    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
-        int64_t i = S.base + t;
-        for (int a = 0; a < 3; ++a) {
-            double xa = B.xs[3 * i + a];
-            B.x[cur][3 * i + a] = xa;
-            // a resident replica steps by its own list, whose reference positions stay
-            if (!R.resident) B.xref[a * S_ + i] = xa;
-            B.v[a * S_ + i] = B.vs[a * S_ + i];
+    stage_cells(R, S, B.cell_rank, B.cstart[1], B.ccnt[1], T, hq);
+    __syncthreads();
+    // halo offsets by the first wave, grid-order offsets by the second
+    {
+        const int w2 = blockDim.x > VBC_WAVE ? 1 : 0;
+        if (threadIdx.x < VBC_WAVE) {
+            const int tot = wave_exclusive_scan(T.q_hpre, S.nh);
+            if (threadIdx.x == 0) halo_s = tot;
         }
-        B.tag[i] = B.tags[i];
-        B.type[i] = B.types[i];
-        B.lcell[i] = B.lcells[i];
+        if (threadIdx.x / VBC_WAVE == w2) {
+            const int tot = wave_exclusive_scan(hq, S.nh);
+            if (threadIdx.x % VBC_WAVE == 0) hq[S.nh] = tot;
+        }
     }
+    __syncthreads();
+    S.total = S.n_own + halo_s;
+    S.overflow = S.total > P.stage_cap;
+
+    if (!S.overflow) {
+        // the brick's staging map and, at each particle's grid-order index, a record of where
+        // it comes from: no memory is read, so a cell's few particles cost no round trip
+        int32_t *sm = B.smap + (size_t)b * P.stage_cap;
+        uint8_t *wm = B.wmap + (size_t)b * P.stage_cap;
+        const int gid = threadIdx.x / VBC_GROUP, gl = threadIdx.x % VBC_GROUP;
+        const int ng = blockDim.x / VBC_GROUP;
+        for (int q = gid; q < S.nh; q += ng) {
+            const int own = T.q_off[q], src0 = T.q_src[q], cnt = T.q_cnt[q], w = T.q_w[q], h0 = hq[q];
+            const int off = own >= 0 ? own : S.n_own + T.q_hpre[q];
+            for (int k = gl; k < cnt; k += VBC_GROUP) {
+                const int t = off + k, src = src0 + k;
+                sm[t] = src;
+                wm[t] = (uint8_t)w;
+                *(int4 *)(hpos + h0 + k) = make_int4(src, w, t, 0);
+            }
+        }
+        __syncthreads();
+        // then every staged position, gathered all at once, with |p|^2 in the fourth component
+        // (brick-centred FP32 coordinates); the own particles go into the live arrays on the way.
+        // An empty brick needs the map only, for the re-sort.
+        if (S.n_own > 0) {
+            const int nt = blockDim.x, last = S.total - 1;
+            const int64_t i0 = S.base + min((int)threadIdx.x, S.n_own - 1);
+            const double v0[3] = {B.vs[i0], B.vs[S_ + i0], B.vs[2 * S_ + i0]};
+            const int32_t tag0 = B.tags[i0];
+            const auto type0 = B.types[i0];
+            const auto lc0 = B.lcells[i0];
+            for (int h0 = threadIdx.x; h0 < S.total; h0 += 2 * nt) {
+                int4 rec[2];
+                double x[2][3];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) rec[j] = *(const int4 *)(hpos + min(h0 + j * nt, last));
+                // a record past the end may be a position by now: not used as an index
+                if (h0 + nt > last) rec[1] = rec[0];
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    for (int a = 0; a < 3; ++a) x[j][a] = B.xs[3 * rec[j].x + a];
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int h = h0 + j * nt, w = rec[j].y;
+                    float4 p;
+                    p.x = (float)((x[j][0] + R.L[0] * (double)unpack_w(w, 0)) - S.O[0]);
+                    p.y = (float)((x[j][1] + R.L[1] * (double)unpack_w(w, 1)) - S.O[1]);
+                    p.z = (float)((x[j][2] + R.L[2] * (double)unpack_w(w, 2)) - S.O[2]);
+                    p.w = fmaf(p.x, p.x, fmaf(p.y, p.y, p.z * p.z));
+                    if (h <= last) {
+                        hpos[h] = p;
+                        conv[h] = (uint16_t)rec[j].z;
+                        if (rec[j].z < S.n_own)
+                            for (int a = 0; a < 3; ++a) B.x[cur][3 * rec[j].x + a] = x[j][a];
+                    }
+                }
+            }
+            if ((int)threadIdx.x < S.n_own) {
+                for (int a = 0; a < 3; ++a) B.v[a * S_ + i0] = v0[a];
+                B.tag[i0] = tag0;
+                B.type[i0] = type0;
+                B.lcell[i0] = lc0;
+            }
+            for (int t = threadIdx.x + nt; t < S.n_own; t += nt) {
+                const int64_t i = S.base + t;
+                for (int a = 0; a < 3; ++a) B.v[a * S_ + i] = B.vs[a * S_ + i];
+                B.tag[i] = B.tags[i];
+                B.type[i] = B.types[i];
+                B.lcell[i] = B.lcells[i];
+            }
+        }
+        // the scan reads up to SCAN_UNROLL - 1 records past a row's end: far-away padding
+        if ((int)threadIdx.x < SCAN_UNROLL) hpos[S.total + threadIdx.x] = make_float4(1e18f, 1e18f, 1e18f, 3e36f);
+        __syncthreads();
+
+        // The pre-filter forms d = (|p_u|^2 - c_i) - 2 p_i.p_u with c_i = mid - |p_i|^2, mid the
+        // middle of [lo2, hi2]: one subtraction and three fused steps per candidate.  With
+        // u = 2^-24 and Q = (|p_i| + |p_u|)^2 + hi2, the rounded squares, the subtractions and the
+        // fused steps (whose partial sums stay below 2 Q) err by less than 26 u Q in total, and
+        // the direct form |p_i - p_u|^2 differs from the exact local distance by at most 5 u hi2.
+        // A candidate within a hundredth of the list radius of it has |p_u| < |p_i| + 1.01 sqrt(rl2),
+        // so that with hd = (hi2 - lo2) / 2 + 64 u ((2 |p_i| + 1.01 sqrt(rl2))^2 + hi2), over twice
+        // the bound, d <= -hd puts the direct form below lo2 (in the list) and d >= hd above hi2
+        // (not in it); one further off has |d| above 0.02 rl2, a hundred times the error
+        // over a brick, and the right sign.  The few in between (one row in a thousand holds
+        // one: the smallest |d| of the row tells) are decided by the direct form against lo2 and
+        // hi2, and in FP64 between those.
+        // (R.scan; read where they are used, which costs scalar loads instead of registers)
+        const int kmax = P.k_max, W = P.list_win;
+        // read once: the global descriptor cannot be kept in registers across the list stores
+        const int xspan = R.excl_span, cl = R.chain_len;
+        // division of a cell index (below 256) by the brick's edges: ceil(2^16 / e)
+        const uint32_t d0 = (65535u + S.e[0]) / (uint32_t)S.e[0], d1 = (65535u + S.e[1]) / (uint32_t)S.e[1];
+        const int lane = threadIdx.x % VBC_WAVE, nwv = blockDim.x / VBC_WAVE;
+        const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / VBC_WAVE);
+        const int g = lane / 3, sub = lane - 3 * g;  // particle of the wave, plane of the stencil
+        uint16_t *buf = wbuf + (wv * NL_PPW + min(g, NL_PPW - 1)) * bstride;
+        for (int t0 = wv * NL_PPW; t0 < S.n_own; t0 += nwv * NL_PPW) {
+            const bool live = g < NL_PPW && t0 + g < S.n_own;
+            const int t = live ? t0 + g : t0;
+            const int64_t i = S.base + t;
+            const uint32_t loc = B.lcells[i];
+            const uint32_t lyz = (loc * d0) >> 16;  // ly + e1 lz
+            const int lz = (int)((lyz * d1) >> 16), ly = (int)lyz - S.e[1] * lz,
+                      lx = (int)loc - S.e[0] * (int)lyz;
+            const int qs = (lx + 1) + S.H[0] * ((ly + 1) + S.H[1] * (lz + 1));
+            const int hs = hq[qs] + (t - T.q_off[qs]);  // this particle in grid order
+            const float4 pi = hpos[hs];
+            const float mx = -2.0f * pi.x, my = -2.0f * pi.y, mz = -2.0f * pi.z, ci = R.scan.mid - pi.w;
+            const float reach = 2.0f * sqrtf(pi.w) + R.scan.reach;
+            const float hd = R.scan.half + 0x1p-18f * fmaf(reach, reach, R.scan.hi2);
+            // the neighbours among the n <= 32 candidates u0, u0 + 1, ... of the row of cells
+            // q0, q0 + 1, q0 + 2, candidate k at bit 31 - k
+            auto segment = [&](int u0, int n, int q0) -> uint32_t {
+                if (n <= 0) return 0u;
+                uint32_t near = 0u;
+                float closest = 3e38f;
+                int k0 = 0;
+                for (; k0 < n; k0 += SCAN_UNROLL) {
+                    const float4 *pp = hpos + (u0 + k0);
+                    float4 pu[SCAN_UNROLL];
+                    float d[SCAN_UNROLL];
+#pragma unroll
+                    for (int j = 0; j < SCAN_UNROLL; ++j) pu[j] = pp[j];
+#pragma unroll
+                    for (int j = 0; j < SCAN_UNROLL; ++j) {
+                        d[j] = fmaf(pu[j].z, mz, fmaf(pu[j].y, my, fmaf(pu[j].x, mx, pu[j].w - ci)));
+                        near = __builtin_amdgcn_alignbit(near, __float_as_uint(d[j]), 31);
+                    }
+#pragma unroll
+                    for (int j = 0; j < SCAN_UNROLL; j += 2)
+                        closest = fminf(closest, fminf(fabsf(d[j]), fabsf(d[j + 1])));
+                }
+                near <<= 32 - k0;
+                if (n < 32) near &= ~(0xffffffffu >> n);  // reads past the row
+                if (closest < hd) {
+                    uint32_t close = 0u;
+                    for (k0 = 0; k0 < n; k0 += SCAN_UNROLL) {
+#pragma unroll
+                        for (int j = 0; j < SCAN_UNROLL; ++j) {
+                            const float4 pu = hpos[u0 + k0 + j];
+                            const float d = fmaf(pu.z, mz, fmaf(pu.y, my, fmaf(pu.x, mx, pu.w - ci)));
+                            close = __builtin_amdgcn_alignbit(close, __float_as_uint(fabsf(d) - hd), 31);
+                        }
+                    }
+                    close <<= 32 - k0;
+                    if (n < 32) close &= ~(0xffffffffu >> n);
+                    while (close) {
+                        const int k = __builtin_clz(close);
+                        const uint32_t bit = 0x80000000u >> k;
+                        close &= ~bit;
+                        const float4 pu = hpos[u0 + k];
+                        const float ex = -0.5f * mx - pu.x, ey = -0.5f * my - pu.y, ez = -0.5f * mz - pu.z;
+                        const float r2f = ex * ex + ey * ey + ez * ez;
+                        bool in = r2f < R.scan.lo2;
+                        if (!in && r2f < R.scan.hi2) {
+                            // near the list radius: decide with the exact FP64 expression
+                            const int u = u0 + k;
+                            const int q = q0 + (u >= hq[q0 + 1] ? 1 : 0) + (u >= hq[q0 + 2] ? 1 : 0);
+                            const int w = T.q_w[q];
+                            const int64_t js = T.q_src[q] + (u - hq[q]);
+                            // axis by axis: a rare path that must not cost the scan registers
+                            double r2 = 0.0;
+#pragma unroll 1
+                            for (int a = 0; a < 3; ++a) {
+#pragma clang fp contract(off)
+                                double ta = B.xs[3 * i + a] - B.xs[3 * js + a];
+                                double da = ta - R.L[a] * (double)unpack_w(w, a);
+                                r2 = r2 + da * da;
+                            }
+                            in = r2 < R.rlist2;
+                        }
+                        near = in ? (near | bit) : (near & ~bit);
+                    }
+                }
+                if (u0 <= hs && hs < u0 + n) near &= ~(0x80000000u >> (hs - u0));  // not itself
+                return near;
+            };
+            // the masks of the first 64 candidates of each row are kept (the rows' pairs of
+            // masks rotate through three); longer rows (dense clusters) are scanned again when
+            // their entries are written
+            uint32_t ma[2] = {0u, 0u}, mb[2] = {0u, 0u}, mc[2] = {0u, 0u};
+            int cnt = 0;
+            const int qz = lx + S.H[0] * (ly + S.H[1] * (lz + sub));
+#pragma unroll 1
+            for (int dy = 0; dy < 3; ++dy) {
+                const int q0 = qz + S.H[0] * dy, ub = hq[q0], ue = live ? hq[q0 + 3] : ub;
+                ma[0] = mb[0], ma[1] = mb[1];
+                mb[0] = mc[0], mb[1] = mc[1];
+                mc[0] = mc[1] = 0u;
+#pragma unroll 1
+                for (int u0 = ub; u0 < ue; u0 += 32) {
+                    const uint32_t mk = segment(u0, min(32, ue - u0), q0);
+                    if (u0 == ub) mc[0] = mk;
+                    if (u0 == ub + 32) mc[1] = mk;
+                    cnt += __popc(mk);
+                }
+            }
+            const int n0 = __shfl(cnt, 3 * g), n1 = __shfl(cnt, 3 * g + 1), n2 = __shfl(cnt, 3 * g + 2);
+            const int tot = live ? n0 + n1 + n2 : 0;
+            const int off = sub == 0 ? 0 : (sub == 1 ? n0 : n0 + n1);
+            // bit 15 of an entry: chain neighbours up to excl_span beads apart
+            auto excluded = [&](int u, int q0) -> uint32_t {
+                const int q = q0 + (u >= hq[q0 + 1] ? 1 : 0) + (u >= hq[q0 + 2] ? 1 : 0);
+                const int ta = B.tags[i], tb = B.tags[T.q_src[q] + (u - hq[q])];
+                const int db = ta - tb;
+                return ta / cl == tb / cl && db <= xspan && -db <= xspan ? 0x8000u : 0u;
+            };
+            // entries in windows of W: one window unless a list is longer
+            for (int w0 = 0; __any(tot > w0); w0 += W) {
+                int pos = off - w0;
+#pragma unroll 1
+                for (int dy = 0; dy < 3; ++dy) {
+                    const int q0 = qz + S.H[0] * dy, ub = hq[q0], ue = live ? hq[q0 + 3] : ub;
+                    const uint32_t m0 = ma[0], m1 = ma[1];
+                    ma[0] = mb[0], ma[1] = mb[1];
+                    mb[0] = mc[0], mb[1] = mc[1];
+                    mc[0] = m0, mc[1] = m1;
+#pragma unroll 1
+                    for (int u0 = ub; u0 < ue; u0 += 32) {
+                        uint32_t todo = u0 == ub ? m0 : m1;
+                        if (u0 > ub + 32) todo = segment(u0, min(32, ue - u0), q0);
+                        // a segment with no entry inside the window is passed over
+                        const int pc = __popc(todo);
+                        if (pos + pc <= 0 || pos >= W) {
+                            pos += pc;
+                            todo = 0u;
+                        }
+                        // two entries at a time, so that their reads overlap
+                        while (todo) {
+                            const int k = __builtin_clz(todo);
+                            const uint32_t rest = todo & ~(0x80000000u >> k);
+                            const int k2 = rest ? __builtin_clz(rest) : k;
+                            uint32_t hv = (uint32_t)conv[u0 + k], hv2 = (uint32_t)conv[u0 + k2];
+                            if (xspan > 0) {
+                                hv |= excluded(u0 + k, q0);
+                                hv2 |= excluded(u0 + k2, q0);
+                            }
+                            // entries outside the window go to the spare places behind it; the
+                            // first entry of a chunk stands in its last place
+                            const unsigned p2 = rest ? (unsigned)(pos + 1) : (unsigned)W;
+                            buf[min((unsigned)pos, (unsigned)W) ^ (CHUNK - 1)] = (uint16_t)hv;
+                            buf[min(p2, (unsigned)W) ^ (CHUNK - 1)] = (uint16_t)hv2;
+                            pos += rest ? 2 : 1;
+                            todo = rest & ~(0x80000000u >> k2);
+                        }
+                    }
+                }
+                // pad the last chunk with the dummy staged slot (far away: contributes nothing)
+                const int fill = min(tot - w0, W);
+                for (int k = fill + sub; k < ((fill + CHUNK - 1) & ~(CHUNK - 1)); k += 3)
+                    if (fill > 0) buf[k ^ (CHUNK - 1)] = (uint16_t)P.stage_cap;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                for (int c = sub; c * CHUNK < fill; c += 3) {
+                    const int ch = w0 / CHUNK + c;
+                    if (ch < P.nchunk) B.nl[(size_t)ch * S_ + i] = *(const uint4 *)(buf + c * CHUNK);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            if (live && sub == 0) {
+                if (tot > kmax) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_NLIST_OVERFLOW);
+                B.nn[i] = (uint16_t)min(tot, kmax);
+                atomicAdd(&ent_sum, (unsigned)min(tot, kmax));
+            }
+        }
+    } else {
+        for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
+            const int64_t i = S.base + t;
+            for (int a = 0; a < 3; ++a) {
+                B.x[cur][3 * i + a] = B.xs[3 * i + a];
+                B.v[a * S_ + i] = B.vs[a * S_ + i];
+            }
+            B.tag[i] = B.tags[i];
+            B.type[i] = B.types[i];
+            B.lcell[i] = B.lcells[i];
+            B.nn[i] = 0;
+        }
+        if (threadIdx.x == 0) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_STAGE_OVERFLOW);
+    }
+
+    // next layout's own cell tables -> live
     for (int lc = threadIdx.x; lc < S.ncb; lc += blockDim.x) {
         B.cstart[0][R.c_off + S.rank0 + lc] = B.cstart[1][R.c_off + S.rank0 + lc];
         B.ccnt[0][R.c_off + S.rank0 + lc] = B.ccnt[1][R.c_off + S.rank0 + lc];
     }
-    if (threadIdx.x == 0) B.bcnt[0][b] = S.n_own;
     if (lb == 0) {
         // every particle must have been placed in exactly one brick of the next layout
         unsigned long long placed = 0;
         for (int k = threadIdx.x; k < R.nbrick; k += blockDim.x) placed += B.bcnt[1][R.b_off + k];
         placed = wave_sum(placed);
         if ((threadIdx.x % VBC_WAVE) == 0 && placed) atomicAdd(&lost_sum, placed);
-        __syncthreads();
-        if (threadIdx.x == 0) {
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        B.bcnt[0][b] = S.n_own;
+        B.stotal[b] = S.total;
+        B.bentries[b] = ent_sum;
+        if (lb == 0) {
             B.stats[4 * r + 0] += 1ull;
             if (lost_sum != (unsigned long long)R.n) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_LOST);
         }
     }
-    if (threadIdx.x == 0) B.stotal[b] = S.total;
-    if (S.overflow) {
-        for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) B.nn[S.base + t] = 0;
-        if (threadIdx.x == 0) {
-            atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_STAGE_OVERFLOW);
-            B.bentries[b] = 0u;
-        }
-        return;
-    }
-    int32_t *sm = B.smap + (size_t)b * P.stage_cap;
-    uint8_t *wm = B.wmap + (size_t)b * P.stage_cap;
-    // grid-order offsets: exclusive prefix of every cell's count, the total at hq[nh]
-    for (int q = threadIdx.x; q < S.nh; q += blockDim.x) hq[q] = T.q_cnt[q];
-    __syncthreads();
-    {
-        const int tot = wave0_exclusive_scan(hq, S.nh);
-        if (threadIdx.x == 0) hq[S.nh] = tot;
-    }
-    __syncthreads();
-    {
-        // staging copy (as stage_copy), each particle also placed at its grid-order index
-        // with |p|^2 in the fourth component (brick-centred FP32 coordinates)
-        const int gid = threadIdx.x / VBC_GROUP, gl = threadIdx.x % VBC_GROUP;
-        const int ng = blockDim.x / VBC_GROUP;
-        float pm2 = 0.0f;
-        for (int q = gid; q < S.nh; q += ng) {
-            const int off = T.q_off[q], src0 = T.q_src[q], cnt = T.q_cnt[q], w = T.q_w[q], h0 = hq[q];
-            for (int k = gl; k < cnt; k += VBC_GROUP) {
-                const int t = off + k, src = src0 + k;
-                sm[t] = src;
-                wm[t] = (uint8_t)w;
-                if (S.n_own == 0) continue;  // only the re-sort reads an empty brick's staging
-                float4 p;
-                p.x = (float)((B.xs[3 * src] + R.L[0] * (double)unpack_w(w, 0)) - S.O[0]);
-                p.y = (float)((B.xs[3 * src + 1] + R.L[1] * (double)unpack_w(w, 1)) - S.O[1]);
-                p.z = (float)((B.xs[3 * src + 2] + R.L[2] * (double)unpack_w(w, 2)) - S.O[2]);
-                p.w = fmaf(p.x, p.x, fmaf(p.y, p.y, p.z * p.z));
-                pm2 = fmaxf(pm2, p.w);
-                hpos[h0 + k] = p;
-                conv[h0 + k] = (uint16_t)t;
-            }
-        }
-#pragma unroll
-        for (int o = VBC_WAVE / 2; o > 0; o >>= 1) pm2 = fmaxf(pm2, __shfl_xor(pm2, o, VBC_WAVE));
-        if ((threadIdx.x % VBC_WAVE) == 0) atomicMax(&pmax_bits, __float_as_uint(pm2));  // pm2 >= 0
-        // the scan reads up to SCAN_UNROLL - 1 records past a row's end: far-away padding
-        if ((int)threadIdx.x < SCAN_UNROLL) hpos[S.total + threadIdx.x] = make_float4(1e18f, 1e18f, 1e18f, 3e36f);
-    }
-    __syncthreads();
-
-    const double rl2 = R.rlist2;
-    const float lo2 = (float)(rl2 * (1.0 - 2e-5) - 1e-4), hi2 = (float)(rl2 * (1.0 + 2e-5) + 1e-4);
-    // The pre-filter tests d = (|p_u|^2 - c_i) - 2 p_i.p_u < 0 with c_i = hi2 + margin - |p_i|^2:
-    // one subtraction and three fused steps per candidate.  With P2 the largest staged |p|^2
-    // and u = 2^-24, the rounded squares, the subtractions and the fused steps (whose partial
-    // sums stay below 4 P2 + hi2) err by less than 25 u (P2 + hi2) in total, and the direct
-    // form |p_i - p_u|^2 that decides the list differs from the exact local distance by at
-    // most 5 u hi2; the margin, 128 u (P2 + hi2), is four times their sum.  So every candidate
-    // that the direct form puts below hi2 is marked, and every candidate with d + delta < 0,
-    // delta = (hi2 + margin) - (lo2 - margin), has the direct form below lo2: such a "sure"
-    // candidate is in the list without another test, and the other marked ones are decided
-    // as before (direct form against lo2 and hi2, FP64 in between).
-    const float P2 = __uint_as_float(pmax_bits), marg = 0x1p-17f * (P2 + hi2);
-    const float hi2m = hi2 + marg, delta = hi2m - (lo2 - marg);
-    const int kmax = P.k_max;
-    // read once: the global descriptor cannot be kept in registers across the list stores
-    const int xspan = R.excl_span, cl = R.chain_len;
-    bool ovf = false;
-    unsigned long long entries = 0;
-    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
-        int64_t i = S.base + t;
-        const int ta = xspan > 0 ? B.tags[i] : 0;
-        int loc = B.lcells[i];
-        int lx = loc % S.e[0], ly = (loc / S.e[0]) % S.e[1], lz = loc / (S.e[0] * S.e[1]);
-        const int qs = (lx + 1) + S.H[0] * ((ly + 1) + S.H[1] * (lz + 1));
-        const int hs = hq[qs] + (t - T.q_off[qs]);  // this particle in grid order
-        const float4 pi = hpos[hs];
-        const float mx = -2.0f * pi.x, my = -2.0f * pi.y, mz = -2.0f * pi.z, ci = hi2m - pi.w;
-        int nn = 0, e = 0;
-        // the open chunk as one 128-bit shift register, newest entry in the low half of b0
-        uint32_t b0 = 0u, b1 = 0u, b2 = 0u, b3 = 0u;
-        uint4 *wp = B.nl + i;  // where the open chunk goes
-        for (int dz = 0; dz < 3; ++dz)
-            for (int dy = 0; dy < 3; ++dy) {
-                // the row of three cells along x, one contiguous grid-order range, in segments
-                // of 32 candidates: a tight loop marks the candidates that the FP32 pre-filter
-                // keeps, then a second loop visits only the marked ones in order, repeats the
-                // FP32 test (the few close calls to the list radius are decided in FP64) and
-                // appends.  The wave then pays the longest segment among its lanes only for
-                // the few instructions of the test, and the append only per neighbour.
-                const int q0 = lx + S.H[0] * ((ly + dy) + S.H[1] * (lz + dz));
-                const int ub = hq[q0], u1 = hq[q0 + 1], u2 = hq[q0 + 2], ue = hq[q0 + 3];
-                for (int u0 = ub; u0 < ue; u0 += 32) {
-                    const int n = min(32, ue - u0), cnt = (n + SCAN_UNROLL - 1) & ~(SCAN_UNROLL - 1);
-                    // the sign bit of each candidate's d shifted in from the right: candidate k
-                    // of the segment ends at bit cnt - 1 - k.  Reads past the row (into its
-                    // successors or the padding) are masked below
-                    uint32_t near = 0u, sure = 0u;
-                    for (int k0 = 0; k0 < n; k0 += SCAN_UNROLL) {
-                        const float4 *pp = hpos + (u0 + k0);
-                        float4 pu[SCAN_UNROLL];
-#pragma unroll
-                        for (int j = 0; j < SCAN_UNROLL; ++j) pu[j] = pp[j];
-#pragma unroll
-                        for (int j = 0; j < SCAN_UNROLL; ++j) {
-                            float d = pu[j].w - ci;
-                            d = fmaf(pu[j].x, mx, d);
-                            d = fmaf(pu[j].y, my, d);
-                            d = fmaf(pu[j].z, mz, d);
-                            near = __builtin_amdgcn_alignbit(near, __float_as_uint(d), 31);
-                            sure = __builtin_amdgcn_alignbit(sure, __float_as_uint(d + delta), 31);
-                        }
-                    }
-                    near &= ~((1u << (cnt - n)) - 1u);
-                    if (u0 <= hs && hs < u0 + n) near &= ~(1u << (cnt - 1 - (hs - u0)));  // not itself
-                    uint32_t todo = near;
-                    while (todo) {
-                        const int bit = 31 - __builtin_clz(todo);
-                        todo &= ~(1u << bit);
-                        const int u = u0 + (cnt - 1 - bit);
-                        uint32_t hv = (uint32_t)conv[u];
-                        bool in = (sure >> bit) & 1u;
-                        if (!in) {
-                            const float4 pu = hpos[u];
-                            const float ex = pi.x - pu.x, ey = pi.y - pu.y, ez = pi.z - pu.z;
-                            const float r2f = ex * ex + ey * ey + ez * ez;
-                            in = r2f < lo2;
-                            if (!in && r2f < hi2) {
-                                // near the list radius: decide with the exact FP64 expression
-                                const int q = q0 + (u >= u1 ? 1 : 0) + (u >= u2 ? 1 : 0);
-                                const int w = T.q_w[q];
-                                int64_t js = T.q_src[q] + (u - hq[q]);
-                                double kx = (double)unpack_w(w, 0), ky = (double)unpack_w(w, 1),
-                                       kz = (double)unpack_w(w, 2);
-                                double r2;
-                                {
-#pragma clang fp contract(off)
-                                    double tx = B.xs[3 * i] - B.xs[3 * js];
-                                    double ty = B.xs[3 * i + 1] - B.xs[3 * js + 1];
-                                    double tz = B.xs[3 * i + 2] - B.xs[3 * js + 2];
-                                    double ddx = tx - R.L[0] * kx;
-                                    double ddy = ty - R.L[1] * ky;
-                                    double ddz = tz - R.L[2] * kz;
-                                    r2 = (ddx * ddx + ddy * ddy) + ddz * ddz;
-                                }
-                                in = r2 < rl2;
-                            }
-                        }
-                        if (in) {
-                            if (xspan > 0) {
-                                // chain neighbours up to excl_span beads apart: bit 15
-                                const int q = q0 + (u >= u1 ? 1 : 0) + (u >= u2 ? 1 : 0);
-                                const int tb = B.tags[T.q_src[q] + (u - hq[q])];
-                                const int db = ta - tb;
-                                if (ta / cl == tb / cl && db <= xspan && -db <= xspan) hv |= 0x8000u;
-                            }
-                            b3 = __builtin_amdgcn_alignbit(b3, b2, 16);
-                            b2 = __builtin_amdgcn_alignbit(b2, b1, 16);
-                            b1 = __builtin_amdgcn_alignbit(b1, b0, 16);
-                            b0 = (b0 << 16) | hv;
-                            ++nn;
-                            if (++e == CHUNK) {
-                                if (nn <= kmax) *wp = make_uint4(b0, b1, b2, b3);
-                                wp += S_;
-                                e = 0;
-                            }
-                        }
-                    }
-                }
-            }
-        if (e && nn <= kmax) {
-            // pad the last chunk with the dummy staged slot (far away: contributes nothing)
-            const uint32_t D = (uint32_t)P.stage_cap;
-            for (; e < CHUNK; ++e) {
-                b3 = __builtin_amdgcn_alignbit(b3, b2, 16);
-                b2 = __builtin_amdgcn_alignbit(b2, b1, 16);
-                b1 = __builtin_amdgcn_alignbit(b1, b0, 16);
-                b0 = (b0 << 16) | D;
-            }
-            *wp = make_uint4(b0, b1, b2, b3);
-        }
-        if (nn > kmax) {
-            ovf = true;
-            nn = kmax;
-        }
-        B.nn[i] = (uint16_t)nn;
-        entries += (unsigned long long)nn;
-    }
-    if (ovf) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_NLIST_OVERFLOW);
-    entries = wave_sum(entries);
-    if ((threadIdx.x % VBC_WAVE) == 0 && entries) atomicAdd(&ent_sum, entries);
-    __syncthreads();
-    if (threadIdx.x == 0) B.bentries[b] = (uint32_t)ent_sum;
 }
 
 // ---------------------------------------------------------------------------
@@ -2014,7 +2149,7 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
                 double d2 = 0.0;
                 for (int a = 0; a < 3; ++a) {
                     Xn[3 * i + a] = xx[a];
-                    double dd = xx[a] - B.xref[a * S_ + i];
+                    double dd = xx[a] - B.xs[3 * i + a];
                     d2 += dd * dd;
                 }
                 if (d2 > disp2) mv = true;
@@ -2070,7 +2205,7 @@ __global__ void k_kick_drift(Buffers B, Launch P, int cur, StepArgs st)
         for (int a = 0; a < 3; ++a) {
             B.v[a * S_ + i] = v[a];
             B.x[cur ^ 1][3 * i + a] = x[a];
-            double dd = x[a] - B.xref[a * S_ + i];
+            double dd = x[a] - B.xs[3 * i + a];
             d2 += dd * dd;
         }
         far = far || d2 > R.disp2;
@@ -2454,9 +2589,13 @@ __device__ __forceinline__ void lcc_union(int32_t *lp, int32_t a, int32_t b)
 }
 
 // Bonds that leave a brick, as (own slot, slot in the neighbouring brick) with the smaller
-// slot first, recorded by the sweep of the bonds in the brick's share of the next layout's
-// positions (free between list builds): up to three per slot.
-__device__ __forceinline__ int2 *cross_bonds(const Buffers &B, int64_t base) { return (int2 *)(B.xs + 3 * base); }
+// slot first, recorded by the sweep of the bonds in the brick's share of a space that is free
+// between list builds (a resident replica's reference positions are the layout's, another's
+// the list's): up to three per slot.
+__device__ __forceinline__ int2 *cross_bonds(const Buffers &B, const RepDev &R, int64_t base)
+{
+    return (int2 *)((R.resident ? B.xs : B.xref) + 3 * base);
+}
 __device__ __forceinline__ int cross_cap(const RepDev &R) { return 3 * R.bcap; }
 
 // Bonds of every own particle (the z_i criterion of the observables) from its list.  Bonds
@@ -2507,7 +2646,7 @@ __global__ void k_cc_local(Buffers B, Launch P, int cur, ClusterWork W, int64_t 
     __syncthreads();
     const bool xr = R.excl_span > 0;
     const Band ba0 = make_band(R.pair[0].ra2);
-    int2 *cross = cross_bonds(B, S.base);
+    int2 *cross = cross_bonds(B, R, S.base);
     const int cap = cross_cap(R);
     for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
         const int64_t i = S.base + t;
@@ -2600,7 +2739,7 @@ __global__ void k_cc_hook(Buffers B, Launch P, int cur, ClusterWork W)
         cc_union(W.parent, pa, pb);
     };
     if (nc <= cross_cap(R)) {
-        const int2 *cross = cross_bonds(B, base);
+        const int2 *cross = cross_bonds(B, R, base);
         for (int k = threadIdx.x; k < nc; k += blockDim.x) join(cross[k].x, cross[k].y);
         return;
     }
@@ -3532,6 +3671,11 @@ __global__ void __launch_bounds__(RES_MAX_N) k_resident(Buffers B, Launch P, int
 // ---------------------------------------------------------------------------
 
 static inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
+// Waves of a list build's workgroup, and the LDS up to which its output windows may grow it
+// (two workgroups on a CU); LDS_MAX: what one workgroup can have, less the static part.
+constexpr int LIST_WAVES = 12, LIST_WAVES_ALONE = 16;
+constexpr size_t LIST_LDS = 80 * 1024 - 256, LDS_MAX = 160 * 1024 - 256;
+
 static inline unsigned brick_grid(int nb) { return (unsigned)(((nb + 7) / 8) * 8); }
 
 static size_t tabs_bytes(const Launch &P)
@@ -3546,12 +3690,47 @@ static size_t sort_bytes(const Launch &P)
 }
 
 size_t lds_bytes_sort(const Launch &P) { return tabs_bytes(P) + sort_bytes(P); }
-size_t lds_bytes_nlist(const Launch &P)
+// the list build without its output windows: tables, grid-order positions (16 B), cell
+// offsets, grid -> staging order (2 B)
+static size_t nlist_stage_bytes(const Launch &P)
 {
-    // tables, grid-order positions (16 B), cell offsets, grid -> staging order (2 B)
     const size_t nh_cap = (size_t)((P.nh_max + 3) & ~3);
     return tabs_bytes(P) + (size_t)(P.stage_cap + SCAN_UNROLL) * 16 + (nh_cap + 4) * sizeof(int) +
            (size_t)P.stage_cap * 2;
+}
+static size_t nlist_wave_bytes(int win) { return (size_t)NL_PPW * (win + CHUNK) * sizeof(uint16_t); }
+size_t lds_bytes_nlist(const Launch &P)
+{
+    return nlist_stage_bytes(P) + (size_t)(P.list_block / VBC_WAVE) * nlist_wave_bytes(P.list_win);
+}
+// what the handle's check asks for: the build has hardly any static LDS, and one wave's
+// smallest window fits into the room that the check leaves for it
+size_t lds_need_nlist(const Launch &P)
+{
+    return std::max(nlist_stage_bytes(P), lds_bytes_nlist(P) - nlist_wave_bytes(32));
+}
+
+// The list build's workgroup: a wave for each 21 particles of a mean brick, and one for
+// fluctuations, up to twelve (two such workgroups fill a CU's registers), fewer where the
+// windows would take a second workgroup's LDS.  Where the staging alone leaves room for one
+// workgroup only, as many waves as it can use.  (Passes of ten steps or a tick, us: a million
+// particles, 455 a brick, 1389 with twelve waves, 1484 with six; twenty systems of 4000, 52 a
+// brick, 1150 with three, 1206 with two; a pool laid out for density 1, 416 a brick, 1066 with
+// sixteen, 1095 with eleven, 1254 with four.)  The windows hold a mean list and three standard
+// deviations, in whole chunks between 32 and 64 entries.
+void list_shape(Launch &P)
+{
+    const int win = (int)(P.k_mean + 3.0 * std::sqrt(P.k_mean) + CHUNK) & ~(CHUNK - 1);
+    const size_t base = nlist_stage_bytes(P);
+    P.list_win = std::max(32, std::min(64, win));
+    const size_t wb = nlist_wave_bytes(P.list_win);
+    const int want = std::max(1, std::min(LIST_WAVES_ALONE, (int)(P.own_mean / NL_PPW + 1.5)));
+    int waves = std::min(want, LIST_WAVES);
+    while (waves > 1 && base + waves * wb > LIST_LDS) --waves;
+    if (3 * waves < 2 * std::min(want, LIST_WAVES)) waves = want;
+    while (waves > 1 && base + waves * wb > LDS_MAX) --waves;
+    if (base + waves * wb > LDS_MAX) P.list_win = 32;
+    P.list_block = waves * VBC_WAVE;
 }
 size_t lds_bytes_count(const Launch &P)
 {
@@ -3680,7 +3859,7 @@ hipError_t launch_full_build(const Buffers &B, const Launch &P, int cur, int r, 
 {
     if (n > 0) tlaunch(k_gbin, blocks_for(n, 256), 256, 0, s, B, P.nslots, cur, r);
     tlaunch(k_gsort, brick_grid(P.nb_launch), P.block, sort_bytes(P), s, B, P, cur);
-    tlaunch(k_nlist, brick_grid(P.nb_launch), P.block, lds_bytes_nlist(P), s, B, P, cur);
+    tlaunch(k_nlist, brick_grid(P.nb_launch), P.list_block, lds_bytes_nlist(P), s, B, P, cur);
     return hipGetLastError();
 }
 
@@ -3694,7 +3873,7 @@ hipError_t launch_full_build_all(const Buffers &B, const Launch &P, int cur, hip
     Q.due = FLAG_FULL;  // a replica that is only due for a rebuild has no next layout yet
     tlaunch(k_gbin_all, P.nbrick_tot, P.bcap_max <= 128 ? VBC_WAVE : 256, 0, s, B, cur);
     tlaunch(k_gsort, brick_grid(Q.nb_launch), Q.block, sort_bytes(Q), s, B, Q, cur);
-    tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.block, lds_bytes_nlist(Q), s, B, Q, cur);
+    tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.list_block, lds_bytes_nlist(Q), s, B, Q, cur);
     tlaunch(k_full_done, blocks_for(P.nrep, 256), 256, 0, s, B, P.nrep);
     return hipGetLastError();
 }
@@ -3716,7 +3895,7 @@ hipError_t launch_rebuild(const Buffers &B, const Launch &P, int cur, hipStream_
         Q.list = 1;
     }
     tlaunch(k_resort, brick_grid(Q.nb_launch), Q.block, lds_bytes_sort(Q), s, B, Q, cur);
-    tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.block, lds_bytes_nlist(Q), s, B, Q, cur);
+    tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.list_block, lds_bytes_nlist(Q), s, B, Q, cur);
     return hipGetLastError();
 }
 
