@@ -501,6 +501,7 @@ Launch launch_for(const Caps &C, const vbc_options &opt)
     P.own_mean = C.own_mean;
     P.k_mean = C.k_mean;
     list_shape(P);
+    split_shape(P);
     return P;
 }
 
@@ -1252,6 +1253,7 @@ vbc_status vbc_tune_set(vbc_handle h, const vbc_options *t)
             vbc_status st = check_lds(h, Q);
             if (st != VBC_OK) return st;
             h->P.block = t->block;
+            split_shape(h->P);
             h->opt.block = t->block;
             h->auto_block = false;
             drop_graphs(h);

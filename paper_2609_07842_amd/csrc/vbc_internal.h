@@ -146,6 +146,7 @@ struct Launch {
     int32_t k_max;           // multiple of CHUNK
     int32_t nchunk;          // k_max / CHUNK
     int32_t block;
+    int32_t split;           // log2 of the lanes that share a particle in the count and force passes
     int32_t list_block;      // threads of the list build and entries of its output windows
     int32_t list_win;        // (list_shape)
     int32_t stage_cap;
@@ -263,6 +264,7 @@ bool resident_can(const RepDev &R);
 size_t lds_bytes_sort(const Launch &P);
 size_t lds_bytes_nlist(const Launch &P);
 size_t lds_need_nlist(const Launch &P);
+void split_shape(Launch &P);
 void list_shape(Launch &P);  // the list build's workgroup and windows, by own_mean and k_mean
 size_t lds_bytes_count(const Launch &P);
 size_t lds_bytes_embed(const Launch &P);

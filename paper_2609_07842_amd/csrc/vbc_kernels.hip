@@ -1319,9 +1319,9 @@ __device__ __forceinline__ const RepDev &rep_of(const OneRep<ONE> &R1, const Buf
 // padded with the dummy staged slot, whose terms all vanish), with the next chunk's load
 // issued before the current one is processed.  fn(staged index) is called for every entry
 // of a chunk without a guard, so the eight LDS gathers of a chunk can be in flight together.
-template <class F>
+template <class F, class G>
 __device__ __forceinline__ void for_each_neighbour(const uint4 *__restrict__ nl, int64_t S_,
-                                                   int64_t i, int nn, F &&fn)
+                                                   int64_t i, int nn, F &&fn, G &&done)
 {
     int nch = (nn + CHUNK - 1) / CHUNK;
     if (nch == 0) return;
@@ -1332,6 +1332,55 @@ __device__ __forceinline__ void for_each_neighbour(const uint4 *__restrict__ nl,
         uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
         for (int e = 0; e < CHUNK; ++e) fn((int)((w[e >> 1] >> (16 * (e & 1))) & 0xffffu));
+        done();
+        q = qn;
+    }
+}
+
+template <class F>
+__device__ __forceinline__ void for_each_neighbour(const uint4 *__restrict__ nl, int64_t S_,
+                                                   int64_t i, int nn, F &&fn)
+{
+    for_each_neighbour(nl, S_, i, nn, fn, []() {});
+}
+
+// The value of lane j of each group of two (ls = 1) or four lanes, within the vector unit.
+template <int LS, int J>
+__device__ __forceinline__ double group_lane(double v)
+{
+    constexpr int ctrl = LS == 2 ? J * 0x55 : J * 0x55 + 0xa0;  // quad_perm: jjjj or j,j,2+j,2+j
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// sum + the group's values in the order of its lanes: the order in which one lane adds the
+// chunks of a list.
+__device__ __forceinline__ double add_group(double sum, double v, int ls)
+{
+    if (ls == 1) return (sum + group_lane<1, 0>(v)) + group_lane<1, 1>(v);
+    return (((sum + group_lane<2, 0>(v)) + group_lane<2, 1>(v)) + group_lane<2, 2>(v)) + group_lane<2, 3>(v);
+}
+
+// The list of one particle by the 2^ls lanes that share it: lane `sub` takes every 2^ls-th
+// chunk, and after each round of chunks every lane calls done() (a lane without a chunk left
+// with nothing summed).
+template <class F, class G>
+__device__ __forceinline__ void for_each_neighbour_shared(const uint4 *__restrict__ nl, int64_t S_,
+                                                          int64_t i, int nn, int sub, int ls, F &&fn, G &&done)
+{
+    const int nch = (nn + CHUNK - 1) / CHUNK, dc = 1 << ls;
+    const uint4 *lp = nl + i;
+    uint4 q = lp[(size_t)min(sub, max(nch - 1, 0)) * S_];
+    for (int c0 = 0; c0 < nch; c0 += dc) {
+        const int c = c0 + sub;
+        const uint4 qn = (c + dc < nch) ? lp[(size_t)(c + dc) * S_] : q;
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+        if (c < nch) {
+#pragma unroll
+            for (int e = 0; e < CHUNK; ++e) fn((int)((w[e >> 1] >> (16 * (e & 1))) & 0xffffu));
+        }
+        done();
         q = qn;
     }
 }
@@ -1564,7 +1613,7 @@ __device__ __forceinline__ void thermo_add(const Buffers &B, const RepDev &R, in
 
 // STATS: also count the ordered pairs inside the interaction cutoff (the pair-evaluation
 // statistic); the step loop samples it on one step in eight.
-template <class Real, bool MULTI, bool STATS, bool ONE>
+template <class Real, bool MULTI, bool STATS, bool ONE, bool SPLIT>
 __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launch P, int cur, double *__restrict__ n_out, int advance, OneRep<ONE> R1)
 {
     using R4 = typename V4<Real>::t;
@@ -1645,7 +1694,8 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
     const bool watt = R.pair[0].attract;
     const int64_t o_off = R.o_off;
     unsigned long long evals = 0;
-    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
+    const int ls = SPLIT ? P.split : 0, sub = SPLIT ? threadIdx.x & ((1 << ls) - 1) : 0;
+    for (int t = threadIdx.x >> ls; t < S.n_own; t += blockDim.x >> ls) {
         int64_t i = S.base + t;
         R4 pi;
         if (SOA) {
@@ -1664,7 +1714,7 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
         int e = 0;
         // omega(r, r_l, r_h) = (1 - u^2)^2 with u = clamp((r - r_l)/(r_h - r_l), 0, 1): exactly 1
         // inside r_l and 0 beyond r_h; partial sums of eight terms are added in FP64
-        for_each_neighbour(B.nl, S_, i, B.nn[i], [&](int u) {
+        auto entry = [&](int u) {
             int ex = 0;  // pair excluded from counting and attraction (chain neighbours)
             if (MULTI && xr) {
                 ex = u >> 15;
@@ -1697,13 +1747,20 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
                 Real qq = fma(-uu, uu, Real(1));
                 chunk = fma(qq, qq, chunk);
             }
-            if (++e == CHUNK) {
+            if (!SPLIT && ++e == CHUNK) {
                 n += (double)chunk;
                 chunk = Real(0);
                 e = 0;
             }
-        });
+        };
+        if constexpr (SPLIT)
+            for_each_neighbour_shared(B.nl, S_, i, B.nn[i], sub, ls, entry, [&]() {
+                n = add_group(n, (double)chunk, ls);
+                chunk = Real(0);
+            });
+        else for_each_neighbour(B.nl, S_, i, B.nn[i], entry);
         evals += (unsigned long long)inside;
+        if (SPLIT && sub) continue;
         B.nd[i] = n;
         bool win = false;
         // with FP32 pair arithmetic the window is widened by the margin: the particles
@@ -1947,7 +2004,7 @@ __device__ __forceinline__ void integrate_one(const StepArgs &st, int mode, bool
     }
 }
 
-template <class Real, bool MULTI, bool THERMO, bool ONE>
+template <class Real, bool MULTI, bool THERMO, bool ONE, bool SPLIT>
 __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
                         double *__restrict__ F_out, double *__restrict__ e_out, OneRep<ONE> R1)
 {
@@ -2017,7 +2074,8 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
     // e, -, Wxx, Wyy, Wzz, Wxy, Wxz, Wyz; the scalar virial W is the trace, formed per brick
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     bool bad = false, mv = false;
-    for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
+    const int ls = SPLIT ? P.split : 0, sub = SPLIT ? threadIdx.x & ((1 << ls) - 1) : 0;
+    for (int t = threadIdx.x >> ls; t < S.n_own; t += blockDim.x >> ls) {
         int64_t i = S.base + t;
         R4 pi = spos[t];
         const R2 sai = MULTI ? ssa[t] : R2{pi.w, scA[t]};
@@ -2025,9 +2083,12 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
         const Real cai = p0.c_a * sai.x;
         // ei: pair energies (several types), or with one type sum tc^2 and ea sum s_j q_a^2,
         // which E_r and E_a s_i scale once per particle
+        // FP64 forces are summed chunk by chunk, the order that lanes sharing a list can keep
+        constexpr bool CHUNKED = sizeof(Real) == 8;
         Real fx = 0, fy = 0, fz = 0, ei = 0, ea = 0;
+        Real cx = 0, cy = 0, cz = 0;
         Real wxx = 0, wyy = 0, wzz = 0, wxy = 0, wxz = 0, wyz = 0;
-        for_each_neighbour(B.nl, S_, i, B.nn[i], [&](int u) {
+        auto entry = [&](int u) {
             int ex = 0;  // pair excluded from counting and attraction (chain neighbours)
             if (MULTI && xr) {
                 ex = u >> 15;
@@ -2076,9 +2137,15 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
                     ea = fma(sj * qq, qq, ea);
                 }
             }
-            fx -= phr * dx;
-            fy -= phr * dy;
-            fz -= phr * dz;
+            if (CHUNKED) {
+                cx -= phr * dx;
+                cy -= phr * dy;
+                cz -= phr * dz;
+            } else {
+                fx -= phr * dx;
+                fy -= phr * dy;
+                fz -= phr * dz;
+            }
             if (THERMO) {
                 if (MULTI) ei += ep;
                 wxx -= phr * dx * dx;
@@ -2088,7 +2155,26 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
                 wxz -= phr * dx * dz;
                 wyz -= phr * dy * dz;
             }
-        });
+        };
+        if constexpr (SPLIT) {
+            static_assert(CHUNKED && !THERMO, "only forces are shared between lanes");
+            for_each_neighbour_shared(B.nl, S_, i, B.nn[i], sub, ls, entry, [&]() {
+                fx = add_group(fx, cx, ls);
+                fy = add_group(fy, cy, ls);
+                fz = add_group(fz, cz, ls);
+                cx = cy = cz = Real(0);
+            });
+            if (sub) continue;
+        } else {
+            for_each_neighbour(B.nl, S_, i, B.nn[i], entry, [&]() {
+                if (CHUNKED) {
+                    fx += cx;
+                    fy += cy;
+                    fz += cz;
+                    cx = cy = cz = Real(0);
+                }
+            });
+        }
         double F[3] = {(double)fx, (double)fy, (double)fz};
         double eb = 0.0, wb[7] = {0, 0, 0, 0, 0, 0, 0};
         double xi_[3] = {X[3 * i], X[3 * i + 1], X[3 * i + 2]};
@@ -3710,6 +3796,27 @@ size_t lds_need_nlist(const Launch &P)
     return std::max(nlist_stage_bytes(P), lds_bytes_nlist(P) - nlist_wave_bytes(32));
 }
 
+// Lanes per particle (2^split) of the FP64 count and force passes of a single replica.  A small
+// or mid-sized system leaves each SIMD a wave or two, and the pass then takes the length of one
+// particle's chain of list chunks (with FP64 square roots and divisions); two or four lanes take
+// every second or fourth chunk, and the staging is spread over as many more threads.  The
+// chunks' sums are added in the list's order, so results do not depend on the lanes.  Us a step at density 0.3 with one, two, four lanes:
+// 1000 particles 27.3, 25.8, 24.6; 20,000 28.9, 27.1, 25.9; 100,000 67.7, 63.0, 61.8;
+// 200,000 85.1, 75.5, 92.7.  At density 0.5 (four waves a brick) 20,000 32.1, 31.2, 33.5 and
+// 50,000 40.0, 41.5, 47.9.  Lists of less than a chunk have nothing to share (22.7, 22.0, 23.4
+// at 10,000 and 0.05).  FP32 passes gain 3 % at most and lose 2 % at density 0.5; the force
+// pass with energies holds too many registers for the extra waves (31.9 to 32.0).
+void split_shape(Launch &P)
+{
+    auto fits = [&](int l, int threads, int64_t waves) {
+        return (P.block << l) <= threads && (int64_t)P.nbrick_tot * ((P.block << l) / VBC_WAVE) <= waves;
+    };
+    P.split = 0;
+    if (P.precision != VBC_FP64 || P.k_mean < CHUNK) return;
+    if (fits(2, 768, 12288)) P.split = 2;
+    else if (fits(1, 384, INT64_MAX) || fits(1, 768, 2048)) P.split = 1;
+}
+
 // The list build's workgroup: a wave for each 21 particles of a mean brick, and one for
 // fluctuations, up to twelve (two such workgroups fill a CU's registers), fewer where the
 // windows would take a second workgroup's LDS.  Where the staging alone leaves room for one
@@ -3899,21 +4006,23 @@ hipError_t launch_rebuild(const Buffers &B, const Launch &P, int cur, hipStream_
     return hipGetLastError();
 }
 
+template <class Real, bool MULTI, bool STATS>
+static void launch_count_t(const Buffers &B, const Launch &P, int cur, double *n_out, int advance, hipStream_t s)
+{
+    const size_t lds = lds_bytes_count(P);
+    const unsigned g = brick_grid(P.nb_launch);
+    if (!P.one) tlaunch(k_count<Real, MULTI, STATS, false, false>, g, P.block, lds, s, B, P, cur, n_out, advance, OneRep<false>{0});
+    else if (!P.split) tlaunch(k_count<Real, MULTI, STATS, true, false>, g, P.block, lds, s, B, P, cur, n_out, advance, OneRep<true>{*P.one});
+    else if constexpr (sizeof(Real) == 8)
+        tlaunch(k_count<Real, MULTI, STATS, true, true>, g, P.block << P.split, lds, s, B, P, cur, n_out, advance, OneRep<true>{*P.one});
+}
+
 template <class Real, bool MULTI>
 static void launch_count_t(const Buffers &B, const Launch &P, int cur, double *n_out, int advance,
                            bool stats, hipStream_t s)
 {
-    size_t lds = lds_bytes_count(P);
-    unsigned g = brick_grid(P.nb_launch);
-    if (P.one) {
-        const OneRep<true> R1{*P.one};
-        if (stats) tlaunch(k_count<Real, MULTI, true, true>, g, P.block, lds, s, B, P, cur, n_out, advance, R1);
-        else tlaunch(k_count<Real, MULTI, false, true>, g, P.block, lds, s, B, P, cur, n_out, advance, R1);
-    } else {
-        const OneRep<false> R1{0};
-        if (stats) tlaunch(k_count<Real, MULTI, true, false>, g, P.block, lds, s, B, P, cur, n_out, advance, R1);
-        else tlaunch(k_count<Real, MULTI, false, false>, g, P.block, lds, s, B, P, cur, n_out, advance, R1);
-    }
+    if (stats) launch_count_t<Real, MULTI, true>(B, P, cur, n_out, advance, s);
+    else launch_count_t<Real, MULTI, false>(B, P, cur, n_out, advance, s);
 }
 
 hipError_t launch_count(const Buffers &B, const Launch &P, int cur, double *n_out, int advance,
@@ -3946,25 +4055,25 @@ hipError_t launch_embed(const Buffers &B, const Launch &P, int cur, hipStream_t 
     return hipGetLastError();
 }
 
+template <class Real, bool MULTI, bool THERMO>
+static void launch_force_t(const Buffers &B, const Launch &P, int cur, Mode mode, const StepArgs &st,
+                           double *F_out, double *e_out, hipStream_t s)
+{
+    const size_t lds = lds_bytes_force(P);
+    const unsigned g = brick_grid(P.nb_launch);
+    const int m = (int)mode;
+    if (!P.one) tlaunch(k_force<Real, MULTI, THERMO, false, false>, g, P.block, lds, s, B, P, cur, m, st, F_out, e_out, OneRep<false>{0});
+    else if (THERMO || !P.split) tlaunch(k_force<Real, MULTI, THERMO, true, false>, g, P.block, lds, s, B, P, cur, m, st, F_out, e_out, OneRep<true>{*P.one});
+    else if constexpr (sizeof(Real) == 8 && !THERMO)
+        tlaunch(k_force<Real, MULTI, false, true, true>, g, P.block << P.split, lds, s, B, P, cur, m, st, F_out, e_out, OneRep<true>{*P.one});
+}
+
 template <class Real, bool MULTI>
 static void launch_force_t(const Buffers &B, const Launch &P, int cur, Mode mode, bool thermo,
                            const StepArgs &st, double *F_out, double *e_out, hipStream_t s)
 {
-    size_t lds = lds_bytes_force(P);
-    unsigned g = brick_grid(P.nb_launch);
-    if (P.one) {
-        const OneRep<true> R1{*P.one};
-        if (thermo)
-            tlaunch(k_force<Real, MULTI, true, true>, g, P.block, lds, s, B, P, cur, (int)mode, st, F_out, e_out, R1);
-        else
-            tlaunch(k_force<Real, MULTI, false, true>, g, P.block, lds, s, B, P, cur, (int)mode, st, F_out, e_out, R1);
-    } else {
-        const OneRep<false> R1{0};
-        if (thermo)
-            tlaunch(k_force<Real, MULTI, true, false>, g, P.block, lds, s, B, P, cur, (int)mode, st, F_out, e_out, R1);
-        else
-            tlaunch(k_force<Real, MULTI, false, false>, g, P.block, lds, s, B, P, cur, (int)mode, st, F_out, e_out, R1);
-    }
+    if (thermo) launch_force_t<Real, MULTI, true>(B, P, cur, mode, st, F_out, e_out, s);
+    else launch_force_t<Real, MULTI, false>(B, P, cur, mode, st, F_out, e_out, s);
 }
 
 hipError_t launch_force(const Buffers &B, const Launch &P, int cur, Mode mode, bool thermo,
