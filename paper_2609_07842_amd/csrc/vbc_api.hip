@@ -37,6 +37,7 @@ struct Caps {
     int64_t ntot = 0, nslots = 0;
     int32_t nbrick = 0, ncell = 0;
     double own_mean = 0.0, k_mean = 0.0;  // of the densest replica
+    int32_t cap_usual = 0;
 };
 
 struct Offsets {
@@ -500,8 +501,13 @@ Launch launch_for(const Caps &C, const vbc_options &opt)
     P.precision = opt.precision;
     P.own_mean = C.own_mean;
     P.k_mean = C.k_mean;
+    P.cap_usual = C.cap_usual;
+    P.lds_cap = opt.stage_cap;
+    P.t_lo = -1;
+    P.t_hi = INT32_MAX;
     list_shape(P);
     split_shape(P);
+    part_shape(P);
     return P;
 }
 
@@ -586,6 +592,7 @@ vbc_status make_handle(const Caps &C, const vbc_options &opt, bool pool, void *d
     // a fixed single replica (not a pool): count and force take its descriptor as a kernel
     // argument (h->reps is sized once here, so the pointer stays valid)
     h->P.one = (!pool && C.nrep == 1) ? h->reps.data() : nullptr;
+    part_shape(h->P);
     h->a_slot.init(C.nslots);
     h->a_brick.init(C.nbrick);
     h->a_cell.init(C.ncell);
@@ -984,6 +991,7 @@ static vbc_status plan_set(const vbc_replica_desc *reps, int32_t nrep, const vbc
     }
     C.own_mean = own_mean_max;
     C.k_mean = k_mean_max;
+    C.cap_usual = stage_cap_for(rho_cell_max, C.nh_max);
     if (!opt.block) opt.block = block_for(own_mean_max);
     int k_auto = k_max_for(k_mean_max), s_auto = stage_cap_for(rho_cell_max, C.nh_max);
     for (const RepPlan &p : plans) {
@@ -1172,8 +1180,11 @@ vbc_status vbc_admit(vbc_handle h, const vbc_replica_desc *d, const double *d_x,
     if (h->auto_block) Q.block = std::max(Q.block, block_for(rp.own_mean));
     Q.own_mean = std::max(Q.own_mean, rp.own_mean);
     Q.k_mean = std::max(Q.k_mean, rp.k_mean);
+    Q.cap_usual = std::max(Q.cap_usual, stage_cap_for(rp.rho_cell, rp.nh));
     list_shape(Q);
-    const bool resized = Q.block != h->P.block || Q.list_block != h->P.list_block || Q.list_win != h->P.list_win;
+    part_shape(Q);
+    const bool resized = Q.block != h->P.block || Q.list_block != h->P.list_block || Q.list_win != h->P.list_win ||
+                         Q.cap_usual != h->P.cap_usual;
     h->P = Q;
     if (resized) {
         h->opt.block = Q.block;
@@ -1254,6 +1265,7 @@ vbc_status vbc_tune_set(vbc_handle h, const vbc_options *t)
             if (st != VBC_OK) return st;
             h->P.block = t->block;
             split_shape(h->P);
+            part_shape(h->P);
             h->opt.block = t->block;
             h->auto_block = false;
             drop_graphs(h);

@@ -150,6 +150,8 @@ struct Launch {
     int32_t list_block;      // threads of the list build and entries of its output windows
     int32_t list_win;        // (list_shape)
     int32_t stage_cap;
+    int32_t lds_cap;         // staged particles that this launch has LDS for
+    int32_t t_lo, t_hi;      // the launch covers bricks of t_lo < staged <= t_hi
     int32_t nh_max;          // max halo-grid cells of any brick
     int32_t bcap_max;
     int32_t ncb_max;         // max cells of one brick
@@ -162,6 +164,9 @@ struct Launch {
     const RepDev *one;
     // host side only: largest mean number of own particles of a brick and of list entries
     double own_mean, k_mean;
+    int32_t cap_usual;  // staging capacity for the mean density
+    // the staged particles up to which a brick goes into the first of two launches; 0: one launch
+    int32_t small_count, small_force, small_list;
 };
 
 // The replica descriptor as a kernel argument (ONE) or nothing.
@@ -264,6 +269,7 @@ bool resident_can(const RepDev &R);
 size_t lds_bytes_sort(const Launch &P);
 size_t lds_bytes_nlist(const Launch &P);
 size_t lds_need_nlist(const Launch &P);
+void part_shape(Launch &P);
 void split_shape(Launch &P);
 void list_shape(Launch &P);  // the list build's workgroup and windows, by own_mean and k_mean
 size_t lds_bytes_count(const Launch &P);

@@ -80,6 +80,27 @@ __device__ __forceinline__ bool resolve_brick(const Launch &P, const Buffers &B,
     return r >= 0;
 }
 
+// The second of two launches of a pass (see parts): a workgroup looks at DENSE bricks, far
+// apart, and does those with more than t_lo staged particles one after the other.  A grid of a
+// workgroup per brick, with the full capacity's LDS, would need as many rounds of the chip to
+// find nothing to do as the pass takes in all.  The mask is a scalar, the same in every wave.
+constexpr int DENSE = 8, DENSE_BLOCK = 512;  // at most so many threads: their registers are not what limits them
+template <class F>
+__device__ __forceinline__ void each_dense(const Launch &P, const Buffers &B, F &&body)
+{
+    const int T = P.list < 0 ? P.nb_launch : B.wl_n[P.list];
+    const int lane = threadIdx.x % VBC_WAVE, kl = blockIdx.x + lane * gridDim.x;
+    bool dense = false;
+    if (lane < DENSE && kl < T) dense = B.stotal[P.list < 0 ? P.b_lo + kl : B.wl[P.list][kl]] > P.t_lo;
+    uint64_t mask = __ballot(dense);
+    while (mask) {
+        const int k = blockIdx.x + __builtin_ctzll(mask) * gridDim.x;
+        mask &= mask - 1;
+        body(P.list < 0 ? P.b_lo + k : B.wl[P.list][k]);
+        __syncthreads();
+    }
+}
+
 // Smooth step of eq. (omega) and its derivative, in FP64 (used for the switching factor).
 __device__ __forceinline__ double omega_d64(double x, double x1, double x2)
 {
@@ -949,22 +970,23 @@ __global__ void k_resort(Buffers B, Launch P, int cur)
 #endif
 constexpr int NL_PPW = VBC_WAVE / 3;  // particles of one wave (its last lane idles)
 
-__global__ void __launch_bounds__(1024) NLIST_ATTR k_nlist(Buffers B, Launch P, int cur)
+template <bool LARGE>
+__device__ __forceinline__ void nlist_brick(const Buffers &B, const Launch &P, int cur, int b)
 {
     extern __shared__ __align__(32) unsigned char smem[];
     __shared__ unsigned long long lost_sum;
     __shared__ unsigned ent_sum;
     __shared__ int halo_s;          // staged particles of the halo cells
-    int b, r;
     const uint32_t fl0 = B.flags[0];  // as in k_resort
-    if (!resolve_brick(P, B, b, r)) return;
+    const int r = B.brick_rep[b];
+    if (r < 0) return;
     if (!((r == 0 ? fl0 : B.flags[r]) & P.due)) return;
     const RepDev &R = B.reps[r];
     const int lb = b - R.b_off;
     const int nh_cap = (P.nh_max + 3) & ~3;
     StageTabs T = carve_tabs(smem, nh_cap);
     float4 *hpos = (float4 *)after_tabs(smem, nh_cap);    // staged positions, grid order
-    int *hq = (int *)(hpos + P.stage_cap + SCAN_UNROLL);  // first grid-order index of each cell
+    int *hq = (int *)(hpos + P.lds_cap + SCAN_UNROLL);  // first grid-order index of each cell
     uint16_t *wbuf = (uint16_t *)(hq + nh_cap + 4);       // entries on their way out, per particle
     const int bstride = P.list_win + CHUNK;
     uint16_t *conv = wbuf + (blockDim.x / VBC_WAVE) * (NL_PPW * bstride);  // grid order -> staging order
@@ -996,6 +1018,10 @@ __global__ void __launch_bounds__(1024) NLIST_ATTR k_nlist(Buffers B, Launch P, 
     __syncthreads();
     S.total = S.n_own + halo_s;
     S.overflow = S.total > P.stage_cap;
+    if (!LARGE && S.total > P.t_hi) {
+        if (threadIdx.x == 0) B.stotal[b] = S.total;  // the second launch takes it
+        return;
+    }
 
     if (!S.overflow) {
         // the brick's staging map and, at each particle's grid-order index, a record of where
@@ -1245,7 +1271,7 @@ __global__ void __launch_bounds__(1024) NLIST_ATTR k_nlist(Buffers B, Launch P, 
                 // pad the last chunk with the dummy staged slot (far away: contributes nothing)
                 const int fill = min(tot - w0, W);
                 for (int k = fill + sub; k < ((fill + CHUNK - 1) & ~(CHUNK - 1)); k += 3)
-                    if (fill > 0) buf[k ^ (CHUNK - 1)] = (uint16_t)P.stage_cap;
+                    if (fill > 0) buf[k ^ (CHUNK - 1)] = (uint16_t)S.total;
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1300,6 +1326,17 @@ __global__ void __launch_bounds__(1024) NLIST_ATTR k_nlist(Buffers B, Launch P, 
             if (lost_sum != (unsigned long long)R.n) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_LOST);
         }
     }
+}
+
+__global__ void __launch_bounds__(1024) NLIST_ATTR k_nlist(Buffers B, Launch P, int cur)
+{
+    int b;
+    if (brick_of_block(P, B, b)) nlist_brick<false>(B, P, cur, b);
+}
+
+__global__ void __launch_bounds__(DENSE_BLOCK) k_nlist_dense(Buffers B, Launch P, int cur)
+{
+    each_dense(P, B, [&](int b) { nlist_brick<true>(B, P, cur, b); });
 }
 
 // ---------------------------------------------------------------------------
@@ -1532,7 +1569,7 @@ constexpr double COUNT_MARGIN = 1e-4;
 // several types) and, if asked, the caller-order count.
 template <class Real, bool MULTI, int LANES, int CP>
 __device__ __forceinline__ void recount_window(const Buffers &B, const Launch &P, const RepDev &R, int b,
-                               int64_t base, int nw, const double *__restrict__ X,
+                               int total, int64_t base, int nw, const double *__restrict__ X,
                                double *__restrict__ n_out)
 {
     using R2 = typename V2<Real>::t;
@@ -1570,7 +1607,7 @@ __device__ __forceinline__ void recount_window(const Buffers &B, const Launch &P
                     ok = ok && !(u >> 15);  // excluded pair: not counted
                     u &= 0x7fff;
                 }
-                vj[j] = ok && u != P.stage_cap;  // padding of the last chunk
+                vj[j] = ok && u < total;  // else padding of the last chunk
                 uj[j] = vj[j] ? u : 0;
             }
 #pragma unroll
@@ -1613,8 +1650,9 @@ __device__ __forceinline__ void thermo_add(const Buffers &B, const RepDev &R, in
 
 // STATS: also count the ordered pairs inside the interaction cutoff (the pair-evaluation
 // statistic); the step loop samples it on one step in eight.
-template <class Real, bool MULTI, bool STATS, bool ONE, bool SPLIT>
-__global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launch P, int cur, double *__restrict__ n_out, int advance, OneRep<ONE> R1)
+template <class Real, bool MULTI, bool STATS, bool ONE, bool SPLIT, bool LARGE>
+__device__ __forceinline__ void count_brick(const Buffers &B, const Launch &P, int cur, double *__restrict__ n_out,
+                                            int advance, const OneRep<ONE> &R1, int b)
 {
     using R4 = typename V4<Real>::t;
     using R2 = typename V2<Real>::t;
@@ -1623,22 +1661,22 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
     __shared__ unsigned long long ev_sum;
     __shared__ PairR<Real> pt[1];
     __shared__ PairM<Real> pm[MULTI ? MAXT * MAXT : 1];
-    int b;
-    if (!brick_of_block(P, B, b)) return;
     const MapFirst mf = map_prefetch(B, b, P.stage_cap);
     // one fixed replica: its descriptor comes with the launch, no owner lookup
     const int r = ONE ? 0 : B.brick_rep[b];
     if (r < 0) return;
     const RepDev &R = rep_of<ONE>(R1, B, r);
     int lb = b - R.b_off;
-    if (lb == 0 && threadIdx.x == 0) atomicAnd(&B.flags[r], ~(uint32_t)VBC_FLAG_REBUILD);
     // the replica's first brick adds the energy and virial sums the last time step's force
     // pass left (with the sums on), after its own work
     const int pend = lb == 0 ? B.tpend[r] : 0;
     R4 *spos = (R4 *)smem;
     constexpr bool SOA = !MULTI && sizeof(Real) == 4;
     float2 *sxy = (float2 *)smem;
-    float *sza = (float *)(sxy + P.stage_cap + 1);
+    // a pass over one replica in one launch has the whole capacity
+    constexpr bool WHOLE = ONE && !SPLIT;
+    const int cap = WHOLE ? P.stage_cap : P.lds_cap;
+    float *sza = (float *)(sxy + cap + 1);
     const int64_t S_ = P.nslots;
     load_pairs<Real>(R, pt);
     if (MULTI) load_pairs_m<Real>(R, pm, threadIdx.x);
@@ -1650,6 +1688,8 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
     // need not wait for a barrier; the staging barrier orders pt, nwin and ev_sum
     StageHdr S;
     pass_header(R, B, b, lb, P.stage_cap, S);
+    if (!LARGE && !WHOLE && S.total > P.t_hi) return;
+    if (lb == 0 && threadIdx.x == 0) atomicAnd(&B.flags[r], ~(uint32_t)VBC_FLAG_REBUILD);
     R2 *sA = (R2 *)B.sA;
     if (S.overflow) {
         for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
@@ -1679,10 +1719,10 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
     });
     if (threadIdx.x == 0) {
         if (SOA) {
-            sxy[P.stage_cap] = make_float2(1.0e6f, 1.0e6f);
-            sza[P.stage_cap] = 1.0e6f;
+            sxy[S.total] = make_float2(1.0e6f, 1.0e6f);
+            sza[S.total] = 1.0e6f;
         } else {
-            spos[P.stage_cap] = dummy_pos<R4>();
+            spos[S.total] = dummy_pos<R4>();
         }
     }
     __syncthreads();
@@ -1792,11 +1832,11 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
         // as many lanes per listed particle (32, 16 or 8) as one round of the workgroup
         // allows: 32 take a list of up to 32 entries in one phase, 16 in two, 8 in four
         if (nwv > 0 && nwv * 32 <= (int)blockDim.x)
-            recount_window<Real, MULTI, 32, 1>(B, P, R, b, S.base, nwv, X, n_out);
+            recount_window<Real, MULTI, 32, 1>(B, P, R, b, S.total, S.base, nwv, X, n_out);
         else if (nwv > 0 && nwv * 16 <= (int)blockDim.x)
-            recount_window<Real, MULTI, 16, 1>(B, P, R, b, S.base, nwv, X, n_out);
+            recount_window<Real, MULTI, 16, 1>(B, P, R, b, S.total, S.base, nwv, X, n_out);
         else if (nwv > 0)
-            recount_window<Real, MULTI, CHUNK, 1>(B, P, R, b, S.base, nwv, X, n_out);
+            recount_window<Real, MULTI, CHUNK, 1>(B, P, R, b, S.total, S.base, nwv, X, n_out);
     }
     if (threadIdx.x == 0) {
         B.wcnt[b] = nwin;
@@ -1811,6 +1851,21 @@ __global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launc
     if (pend) thermo_add<1>(B, R, r);
 }
 
+template <class Real, bool MULTI, bool STATS, bool ONE, bool SPLIT>
+__global__ void __attribute__((amdgpu_waves_per_eu(8))) k_count(Buffers B, Launch P, int cur, double *__restrict__ n_out, int advance, OneRep<ONE> R1)
+{
+    int b;
+    if (brick_of_block(P, B, b)) count_brick<Real, MULTI, STATS, ONE, SPLIT, false>(B, P, cur, n_out, advance, R1, b);
+}
+
+template <class Real, bool MULTI, bool STATS>
+__global__ void __launch_bounds__(DENSE_BLOCK) k_count_dense(Buffers B, Launch P, int cur, double *__restrict__ n_out, int advance)
+{
+    each_dense(P, B, [&](int b) {
+        count_brick<Real, MULTI, STATS, false, false, true>(B, P, cur, n_out, advance, OneRep<false>{0}, b);
+    });
+}
+
 // ---------------------------------------------------------------------------
 // pass 2a: dU/dn for particles inside a switching window
 // ---------------------------------------------------------------------------
@@ -1823,7 +1878,7 @@ constexpr int EMBED_WAVES = 4;
 // group if already read, else -1.
 template <int LPP, class Real, bool MULTI>
 __device__ __forceinline__ void embed_brick(const Buffers &B, const Launch &P, const RepDev &R,
-                                            const PairM<Real> *pm, int b, int64_t base, int nw,
+                                            const PairM<Real> *pm, int b, int total, int64_t base, int nw,
                                             int lane, int g, int ng, int t_first, int cur)
 {
     using R4 = typename V4<Real>::t;
@@ -1875,7 +1930,7 @@ __device__ __forceinline__ void embed_brick(const Buffers &B, const Launch &P, c
                         ok = ok && !(u >> 15);  // excluded pair: no attraction between them
                         u &= 0x7fff;
                     }
-                    vj[j] = ok && u != P.stage_cap;
+                    vj[j] = ok && u < total;
                     uj[j] = vj[j] ? u : 0;
                 }
 #pragma unroll
@@ -1963,16 +2018,16 @@ __global__ void k_embed(Buffers B, Launch P, int cur)
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     if (one) {
-        embed_brick<CHUNK, Real, MULTI>(B, P, R, pm, b, base, nw, lane, lane / CHUNK, VBC_WAVE / CHUNK,
+        embed_brick<CHUNK, Real, MULTI>(B, P, R, pm, b, tot, base, nw, lane, lane / CHUNK, VBC_WAVE / CHUNK,
                                         t_first, cur);
     } else if (nw <= EMBED_WAVES * (VBC_WAVE / CHUNK)) {
         // up to 32: eight lanes each over every wave, all of them in one round
         constexpr int G = VBC_WAVE / CHUNK;
-        embed_brick<CHUNK, Real, MULTI>(B, P, R, pm, b, base, nw, lane, wv * G + lane / CHUNK,
+        embed_brick<CHUNK, Real, MULTI>(B, P, R, pm, b, tot, base, nw, lane, wv * G + lane / CHUNK,
                                         EMBED_WAVES * G, -1, cur);
     } else {
         constexpr int G = VBC_WAVE / 4;  // groups of four lanes per wave
-        embed_brick<4, Real, MULTI>(B, P, R, pm, b, base, nw, lane, wv * G + lane / 4, EMBED_WAVES * G,
+        embed_brick<4, Real, MULTI>(B, P, R, pm, b, tot, base, nw, lane, wv * G + lane / 4, EMBED_WAVES * G,
                                     -1, cur);
     }
 }
@@ -2004,9 +2059,10 @@ __device__ __forceinline__ void integrate_one(const StepArgs &st, int mode, bool
     }
 }
 
-template <class Real, bool MULTI, bool THERMO, bool ONE, bool SPLIT>
-__global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
-                        double *__restrict__ F_out, double *__restrict__ e_out, OneRep<ONE> R1)
+template <class Real, bool MULTI, bool THERMO, bool ONE, bool SPLIT, bool LARGE>
+__device__ __forceinline__ void force_brick(const Buffers &B, const Launch &P, int cur, int mode, const StepArgs &st,
+                                            double *__restrict__ F_out, double *__restrict__ e_out,
+                                            const OneRep<ONE> &R1, int b)
 {
     using R4 = typename V4<Real>::t;
     using R2 = typename V2<Real>::t;
@@ -2015,8 +2071,6 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
     __shared__ PairM<Real> pm[MULTI ? MAXT * MAXT : 1];
     __shared__ double red[8][1024 / VBC_WAVE];
     __shared__ int moved;
-    int b;
-    if (!brick_of_block(P, B, b)) return;
     const MapFirst mf = map_prefetch(B, b, P.stage_cap);
     const int r = ONE ? 0 : B.brick_rep[b];
     if (r < 0) return;
@@ -2026,8 +2080,10 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
     // c_c A in a separate array (20 bytes in FP32); with several types the type in .w and
     // (s or n, A) beside it
     R4 *spos = (R4 *)smem;
-    R2 *ssa = (R2 *)(spos + P.stage_cap + 1);
-    Real *scA = (Real *)(spos + P.stage_cap + 1);
+    constexpr bool WHOLE = ONE && !SPLIT;  // as in the count pass
+    const int cap = WHOLE ? P.stage_cap : P.lds_cap;
+    R2 *ssa = (R2 *)(spos + cap + 1);
+    Real *scA = (Real *)(spos + cap + 1);
     const int64_t S_ = P.nslots;
     const int64_t ntot = P.ntot;
     load_pairs<Real>(R, pt);
@@ -2037,6 +2093,7 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
     // orders pt and moved
     StageHdr S;
     pass_header(R, B, b, lb, P.stage_cap, S);
+    if (!LARGE && !WHOLE && S.total > P.t_hi) return;
     const R2 *sA = (const R2 *)B.sA;
     if (S.overflow) {
         if (threadIdx.x == 0) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_STAGE_OVERFLOW);
@@ -2057,9 +2114,9 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
         }
     });
     if (threadIdx.x == 0) {
-        spos[P.stage_cap] = dummy_pos<R4>();
-        if (MULTI) ssa[P.stage_cap] = R2{Real(0), Real(0)};
-        else scA[P.stage_cap] = Real(0);
+        spos[S.total] = dummy_pos<R4>();
+        if (MULTI) ssa[S.total] = R2{Real(0), Real(0)};
+        else scA[S.total] = Real(0);
     }
     __syncthreads();
 
@@ -2266,6 +2323,24 @@ __global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
     }
 }
 
+template <class Real, bool MULTI, bool THERMO, bool ONE, bool SPLIT>
+__global__ void k_force(Buffers B, Launch P, int cur, int mode, StepArgs st,
+                        double *__restrict__ F_out, double *__restrict__ e_out, OneRep<ONE> R1)
+{
+    int b;
+    if (brick_of_block(P, B, b))
+        force_brick<Real, MULTI, THERMO, ONE, SPLIT, false>(B, P, cur, mode, st, F_out, e_out, R1, b);
+}
+
+template <class Real, bool MULTI, bool THERMO>
+__global__ void __launch_bounds__(DENSE_BLOCK) k_force_dense(Buffers B, Launch P, int cur, int mode, StepArgs st,
+                                                             double *__restrict__ F_out, double *__restrict__ e_out)
+{
+    each_dense(P, B, [&](int b) {
+        force_brick<Real, MULTI, THERMO, false, false, true>(B, P, cur, mode, st, F_out, e_out, OneRep<false>{0}, b);
+    });
+}
+
 // Opening half-kick and drift of the first step of a call, from the forces kept in Fst;
 // one workgroup per brick.
 __global__ void k_kick_drift(Buffers B, Launch P, int cur, StepArgs st)
@@ -2407,7 +2482,7 @@ __global__ void k_export_nlist(Buffers B, Launch P, int rep, int32_t *__restrict
         int64_t i = S.base + t;
         for_each_neighbour(B.nl, P.nslots, i, B.nn[i], [&](int u) {
             if (R.excl_span > 0) u &= 0x7fff;
-            if (u == P.stage_cap) return;  // padding
+            if (u == S.total) return;  // padding
             unsigned long long k = atomicAdd(count, 1ull);
             if ((int64_t)k < cap) {
                 pairs[2 * k] = B.tag[i];
@@ -2485,9 +2560,9 @@ __device__ __forceinline__ void stage_bonds(const Buffers &B, const Launch &P, c
         }
     });
     if (threadIdx.x == 0) {
-        T.xy[P.stage_cap] = make_float2(1.0e6f, 1.0e6f);
-        T.z[P.stage_cap] = 1.0e6f;
-        if (MULTI) T.type[P.stage_cap] = 0;
+        T.xy[S.total] = make_float2(1.0e6f, 1.0e6f);
+        T.z[S.total] = 1.0e6f;
+        if (MULTI) T.type[S.total] = 0;
     }
 }
 
@@ -2801,7 +2876,8 @@ __global__ void k_cc_hook(Buffers B, Launch P, int cur, ClusterWork W)
     if (!resolve_brick(P, B, b, r)) return;
     const RepDev &R = B.reps[r];
     const int lb = b - R.b_off, n_own = B.bcnt[0][b];
-    if (n_own == 0 || B.stotal[b] > P.stage_cap) return;
+    const int total = B.stotal[b];
+    if (n_own == 0 || total > P.stage_cap) return;
     const int64_t base = R.p_off + (int64_t)lb * R.bcap;
     const int nc = W.z[base];
     for (int k = threadIdx.x; k < CC_SET; k += blockDim.x) set[k] = ~0ull;
@@ -2838,7 +2914,7 @@ __global__ void k_cc_hook(Buffers B, Launch P, int cur, ClusterWork W)
         for (int a = 0; a < 3; ++a) wi[a] = wrap1(X[3 * i + a], R.L[a]);
         for_each_neighbour(B.nl, P.nslots, i, B.nn[i], [&](int u) {
             if (R.excl_span > 0) u &= 0x7fff;
-            if (u < n_own || u == P.stage_cap) return;  // inside the brick, or padding
+            if (u < n_own || u == total) return;  // inside the brick, or padding
             const int j = sm[u];
             if (j < (int)i || !(obs_r2(R, X, P.nslots, wi, j) < R.pair[ti * MAXT + B.type[j]].ra2)) return;
             join((int)i, j);
@@ -3762,6 +3838,7 @@ static inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs
 constexpr int LIST_WAVES = 12, LIST_WAVES_ALONE = 16;
 constexpr size_t LIST_LDS = 80 * 1024 - 256, LDS_MAX = 160 * 1024 - 256;
 
+static inline unsigned dense_grid(int nb) { return (unsigned)((nb + DENSE - 1) / DENSE); }
 static inline unsigned brick_grid(int nb) { return (unsigned)(((nb + 7) / 8) * 8); }
 
 static size_t tabs_bytes(const Launch &P)
@@ -3781,8 +3858,8 @@ size_t lds_bytes_sort(const Launch &P) { return tabs_bytes(P) + sort_bytes(P); }
 static size_t nlist_stage_bytes(const Launch &P)
 {
     const size_t nh_cap = (size_t)((P.nh_max + 3) & ~3);
-    return tabs_bytes(P) + (size_t)(P.stage_cap + SCAN_UNROLL) * 16 + (nh_cap + 4) * sizeof(int) +
-           (size_t)P.stage_cap * 2;
+    return tabs_bytes(P) + (size_t)(P.lds_cap + SCAN_UNROLL) * 16 + (nh_cap + 4) * sizeof(int) +
+           (size_t)P.lds_cap * 2;
 }
 static size_t nlist_wave_bytes(int win) { return (size_t)NL_PPW * (win + CHUNK) * sizeof(uint16_t); }
 size_t lds_bytes_nlist(const Launch &P)
@@ -3841,7 +3918,7 @@ void list_shape(Launch &P)
 }
 size_t lds_bytes_count(const Launch &P)
 {
-    return (size_t)(P.stage_cap + 1) * (P.precision == VBC_FP64 ? 32 : (P.multi ? 16 : 12));
+    return (size_t)(P.lds_cap + 1) * (P.precision == VBC_FP64 ? 32 : (P.multi ? 16 : 12));
 }
 size_t lds_bytes_embed(const Launch &P) { (void)P; return 0; }
 // bond tests (observables, clusters, bond tracker): FP32 staging, and the brick's forest
@@ -3853,7 +3930,41 @@ size_t lds_bytes_bonds(const Launch &P)
 size_t lds_bytes_force(const Launch &P)
 {
     const size_t real = P.precision == VBC_FP64 ? 8 : 4;
-    return (size_t)(P.stage_cap + 1) * real * (P.multi ? 6 : 5);
+    return (size_t)(P.lds_cap + 1) * real * (P.multi ? 6 : 5);
+}
+
+// Whether a pass is two launches (parts).  A layout that holds local densities far above the
+// mean reserves LDS for them in every workgroup, so that one to three workgroups of a few waves
+// stand on a CU and a pass takes many rounds of the chip.  The bricks of usual density (as many
+// staged as a layout without a stated maximum has room for) go first, with LDS for those, then
+// the others.  Worth it where it saves two rounds: an idle second launch costs 1.6 us and its
+// bricks wait for the first (100,000 particles of density 0.3, force pass of FP64, two rounds or
+// one: 60.3 us a step in one launch, 61.9 in two).  Laid out for density 1, us a step in one and
+// two launches: 100,000 at 0.05 59.2 and 39.9 (FP64 128 and 62), 400,000 199.6 and 95.1,
+// 200,000 at 0.15 72.3 and 60.0; ten steps of twenty tracked systems of 4000 at 0.05 1151 and
+// 788, a tick of a pool of 24 at 0.3 1057 and 894.
+void part_shape(Launch &P)
+{
+    const int small = P.cap_usual;
+    P.small_count = P.small_force = P.small_list = 0;
+    if (small <= 0 || small >= P.stage_cap) return;
+    auto rounds = [&](int64_t nb, size_t lds, int threads, int waves_cu) {
+        const int64_t n = std::min<int64_t>((LDS_MAX + 256) / (lds + 1024), waves_cu / (threads / VBC_WAVE));
+        return (nb + 256 * std::max<int64_t>(n, 1) - 1) / (256 * std::max<int64_t>(n, 1));
+    };
+    Launch F = P, Q = P;
+    Q.lds_cap = small;
+    const int64_t nb = P.nbrick_tot;
+    const int threads = P.block << (P.one ? P.split : 0);
+    auto saves = [&](int64_t n, size_t (*lds)(const Launch &), int tf, int tq, int waves) {
+        return rounds(n, lds(F), tf, waves) >= rounds(n, lds(Q), tq, waves) + 2 ? small : 0;
+    };
+    P.small_count = saves(nb, lds_bytes_count, threads, threads, 32);
+    P.small_force = saves(nb, lds_bytes_force, threads, threads, P.precision == VBC_FP64 ? 20 : 24);
+    list_shape(F);
+    list_shape(Q);
+    // of several replicas, some are due for a build at a time
+    P.small_list = saves(P.lists ? (nb + 1) / 2 : nb, lds_bytes_nlist, F.list_block, Q.list_block, 24);
 }
 
 namespace {
@@ -3958,6 +4069,30 @@ hipError_t launch_stamp(const Buffers &B, hipStream_t s)
     return hipGetLastError();
 }
 
+// A pass over P's bricks in one launch, or in two: with LDS for `small` staged particles over the
+// bricks that have no more, then with the full capacity over the others.
+template <class F>
+static void parts(const Launch &P, int small, F &&launch)
+{
+    if (!small) return launch(P);
+    Launch Q = P;
+    Q.lds_cap = Q.t_hi = small;
+    launch(Q);
+    Q = P;
+    Q.t_lo = small;
+    launch(Q);
+}
+
+static void launch_nlist(const Buffers &B, const Launch &P, int cur, hipStream_t s)
+{
+    parts(P, P.small_list, [&](Launch Q) {
+        list_shape(Q);
+        if (Q.t_lo >= 0) Q.list_block = std::min(Q.list_block, DENSE_BLOCK);
+        if (Q.t_lo >= 0) tlaunch(k_nlist_dense, dense_grid(Q.nb_launch), Q.list_block, lds_bytes_nlist(Q), s, B, Q, cur);
+        else tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.list_block, lds_bytes_nlist(Q), s, B, Q, cur);
+    });
+}
+
 // Full build of replica r (P covering its bricks): bin and sort it from caller-order
 // input, then build its list.  k_resort skips FULL replicas, so the same two-kernel tail
 // as an incremental rebuild serves.
@@ -3966,7 +4101,7 @@ hipError_t launch_full_build(const Buffers &B, const Launch &P, int cur, int r, 
 {
     if (n > 0) tlaunch(k_gbin, blocks_for(n, 256), 256, 0, s, B, P.nslots, cur, r);
     tlaunch(k_gsort, brick_grid(P.nb_launch), P.block, sort_bytes(P), s, B, P, cur);
-    tlaunch(k_nlist, brick_grid(P.nb_launch), P.list_block, lds_bytes_nlist(P), s, B, P, cur);
+    launch_nlist(B, P, cur, s);
     return hipGetLastError();
 }
 
@@ -3980,7 +4115,7 @@ hipError_t launch_full_build_all(const Buffers &B, const Launch &P, int cur, hip
     Q.due = FLAG_FULL;  // a replica that is only due for a rebuild has no next layout yet
     tlaunch(k_gbin_all, P.nbrick_tot, P.bcap_max <= 128 ? VBC_WAVE : 256, 0, s, B, cur);
     tlaunch(k_gsort, brick_grid(Q.nb_launch), Q.block, sort_bytes(Q), s, B, Q, cur);
-    tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.list_block, lds_bytes_nlist(Q), s, B, Q, cur);
+    launch_nlist(B, Q, cur, s);
     tlaunch(k_full_done, blocks_for(P.nrep, 256), 256, 0, s, B, P.nrep);
     return hipGetLastError();
 }
@@ -4002,7 +4137,7 @@ hipError_t launch_rebuild(const Buffers &B, const Launch &P, int cur, hipStream_
         Q.list = 1;
     }
     tlaunch(k_resort, brick_grid(Q.nb_launch), Q.block, lds_bytes_sort(Q), s, B, Q, cur);
-    tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.list_block, lds_bytes_nlist(Q), s, B, Q, cur);
+    launch_nlist(B, Q, cur, s);
     return hipGetLastError();
 }
 
@@ -4011,7 +4146,8 @@ static void launch_count_t(const Buffers &B, const Launch &P, int cur, double *n
 {
     const size_t lds = lds_bytes_count(P);
     const unsigned g = brick_grid(P.nb_launch);
-    if (!P.one) tlaunch(k_count<Real, MULTI, STATS, false, false>, g, P.block, lds, s, B, P, cur, n_out, advance, OneRep<false>{0});
+    if (P.t_lo >= 0) tlaunch(k_count_dense<Real, MULTI, STATS>, dense_grid(P.nb_launch), std::min(P.block, DENSE_BLOCK), lds, s, B, P, cur, n_out, advance);
+    else if (!P.one || (P.t_hi != INT32_MAX && !P.split)) tlaunch(k_count<Real, MULTI, STATS, false, false>, g, P.block, lds, s, B, P, cur, n_out, advance, OneRep<false>{0});
     else if (!P.split) tlaunch(k_count<Real, MULTI, STATS, true, false>, g, P.block, lds, s, B, P, cur, n_out, advance, OneRep<true>{*P.one});
     else if constexpr (sizeof(Real) == 8)
         tlaunch(k_count<Real, MULTI, STATS, true, true>, g, P.block << P.split, lds, s, B, P, cur, n_out, advance, OneRep<true>{*P.one});
@@ -4028,14 +4164,15 @@ static void launch_count_t(const Buffers &B, const Launch &P, int cur, double *n
 hipError_t launch_count(const Buffers &B, const Launch &P, int cur, double *n_out, int advance,
                         bool stats, hipStream_t s)
 {
-    bool multi = P.multi != 0;
-    if (P.precision == VBC_FP64) {
-        if (multi) launch_count_t<double, true>(B, P, cur, n_out, advance, stats, s);
-        else launch_count_t<double, false>(B, P, cur, n_out, advance, stats, s);
-    } else {
-        if (multi) launch_count_t<float, true>(B, P, cur, n_out, advance, stats, s);
-        else launch_count_t<float, false>(B, P, cur, n_out, advance, stats, s);
-    }
+    parts(P, P.small_count, [&](const Launch &Q) {
+        if (Q.precision == VBC_FP64) {
+            if (Q.multi) launch_count_t<double, true>(B, Q, cur, n_out, advance, stats, s);
+            else launch_count_t<double, false>(B, Q, cur, n_out, advance, stats, s);
+        } else {
+            if (Q.multi) launch_count_t<float, true>(B, Q, cur, n_out, advance, stats, s);
+            else launch_count_t<float, false>(B, Q, cur, n_out, advance, stats, s);
+        }
+    });
     return hipGetLastError();
 }
 
@@ -4062,7 +4199,8 @@ static void launch_force_t(const Buffers &B, const Launch &P, int cur, Mode mode
     const size_t lds = lds_bytes_force(P);
     const unsigned g = brick_grid(P.nb_launch);
     const int m = (int)mode;
-    if (!P.one) tlaunch(k_force<Real, MULTI, THERMO, false, false>, g, P.block, lds, s, B, P, cur, m, st, F_out, e_out, OneRep<false>{0});
+    if (P.t_lo >= 0) tlaunch(k_force_dense<Real, MULTI, THERMO>, dense_grid(P.nb_launch), std::min(P.block, DENSE_BLOCK), lds, s, B, P, cur, m, st, F_out, e_out);
+    else if (!P.one || (P.t_hi != INT32_MAX && (THERMO || !P.split))) tlaunch(k_force<Real, MULTI, THERMO, false, false>, g, P.block, lds, s, B, P, cur, m, st, F_out, e_out, OneRep<false>{0});
     else if (THERMO || !P.split) tlaunch(k_force<Real, MULTI, THERMO, true, false>, g, P.block, lds, s, B, P, cur, m, st, F_out, e_out, OneRep<true>{*P.one});
     else if constexpr (sizeof(Real) == 8 && !THERMO)
         tlaunch(k_force<Real, MULTI, false, true, true>, g, P.block << P.split, lds, s, B, P, cur, m, st, F_out, e_out, OneRep<true>{*P.one});
@@ -4079,14 +4217,15 @@ static void launch_force_t(const Buffers &B, const Launch &P, int cur, Mode mode
 hipError_t launch_force(const Buffers &B, const Launch &P, int cur, Mode mode, bool thermo,
                         const StepArgs &st, double *F_out, double *e_out, hipStream_t s)
 {
-    bool multi = P.multi != 0;
-    if (P.precision == VBC_FP64) {
-        if (multi) launch_force_t<double, true>(B, P, cur, mode, thermo, st, F_out, e_out, s);
-        else launch_force_t<double, false>(B, P, cur, mode, thermo, st, F_out, e_out, s);
-    } else {
-        if (multi) launch_force_t<float, true>(B, P, cur, mode, thermo, st, F_out, e_out, s);
-        else launch_force_t<float, false>(B, P, cur, mode, thermo, st, F_out, e_out, s);
-    }
+    parts(P, P.small_force, [&](const Launch &Q) {
+        if (Q.precision == VBC_FP64) {
+            if (Q.multi) launch_force_t<double, true>(B, Q, cur, mode, thermo, st, F_out, e_out, s);
+            else launch_force_t<double, false>(B, Q, cur, mode, thermo, st, F_out, e_out, s);
+        } else {
+            if (Q.multi) launch_force_t<float, true>(B, Q, cur, mode, thermo, st, F_out, e_out, s);
+            else launch_force_t<float, false>(B, Q, cur, mode, thermo, st, F_out, e_out, s);
+        }
+    });
     return hipGetLastError();
 }
 
