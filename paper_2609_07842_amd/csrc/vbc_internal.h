@@ -166,7 +166,7 @@ struct Launch {
     double own_mean, k_mean;
     int32_t cap_usual;  // staging capacity for the mean density
     // the staged particles up to which a brick goes into the first of two launches; 0: one launch
-    int32_t small_count, small_force, small_list;
+    int32_t small_count, small_force, small_list, small_bonds;
 };
 
 // The replica descriptor as a kernel argument (ONE) or nothing.

@@ -2605,14 +2605,12 @@ __device__ __forceinline__ bool within(float r2f, const Band &bd, const RepDev &
 // decided by `within` (exactly as the plain FP64 definition on the wrapped positions), plus
 // per-replica sums {sum z, #(z > f), sum p}.  The list holds every pair within the
 // interaction cutoff.
-template <bool MULTI>
-__global__ void k_observe(Buffers B, Launch P, int cur, int32_t *__restrict__ z_out,
-                          int32_t *__restrict__ pen_out, int64_t *__restrict__ sums)
+template <bool MULTI, bool LARGE>
+__device__ __forceinline__ void observe_brick(const Buffers &B, const Launch &P, int cur, int32_t *__restrict__ z_out,
+                                              int32_t *__restrict__ pen_out, int64_t *__restrict__ sums, int b)
 {
     extern __shared__ __align__(16) unsigned char smem[];  // Staged
     __shared__ unsigned long long tot[3];
-    int b;
-    if (!brick_of_block(P, B, b)) return;
     const MapFirst mf = map_prefetch(B, b, P.stage_cap);
     const int r = B.brick_rep[b];
     if (r < 0) return;
@@ -2621,11 +2619,11 @@ __global__ void k_observe(Buffers B, Launch P, int cur, int32_t *__restrict__ z_
     if (threadIdx.x == 0) tot[0] = tot[1] = tot[2] = 0ull;
     StageHdr S;
     pass_header(R, B, b, lb, P.stage_cap, S);
-    if (S.overflow) return;
+    if (S.overflow || (!LARGE && S.total > P.t_hi)) return;
     const int64_t S_ = P.nslots;
     const double *X = B.x[cur];
     const int32_t *sm = B.smap + (size_t)b * P.stage_cap;
-    const Staged T = carve_staged(smem, P.stage_cap);
+    const Staged T = carve_staged(smem, P.lds_cap);
     stage_bonds<MULTI>(B, P, R, S, b, X, T, mf);
     __syncthreads();
     const bool xr = R.excl_span > 0;
@@ -2668,6 +2666,21 @@ __global__ void k_observe(Buffers B, Launch P, int cur, int32_t *__restrict__ z_
     __syncthreads();
     if (sums && threadIdx.x < 3 && tot[threadIdx.x])
         atomicAdd((unsigned long long *)&sums[3 * r + threadIdx.x], tot[threadIdx.x]);
+}
+
+template <bool MULTI>
+__global__ void k_observe(Buffers B, Launch P, int cur, int32_t *__restrict__ z_out,
+                          int32_t *__restrict__ pen_out, int64_t *__restrict__ sums)
+{
+    int b;
+    if (brick_of_block(P, B, b)) observe_brick<MULTI, false>(B, P, cur, z_out, pen_out, sums, b);
+}
+
+template <bool MULTI>
+__global__ void __launch_bounds__(DENSE_BLOCK) k_observe_dense(Buffers B, Launch P, int cur, int32_t *__restrict__ z_out,
+                                                               int32_t *__restrict__ pen_out, int64_t *__restrict__ sums)
+{
+    each_dense(P, B, [&](int b) { observe_brick<MULTI, true>(B, P, cur, z_out, pen_out, sums, b); });
 }
 
 // ---------------------------------------------------------------------------
@@ -2765,19 +2778,11 @@ __device__ __forceinline__ int cross_cap(const RepDev &R) { return 3 * R.bcap; }
 // size, bond ends and smallest tag summed in LDS at that slot (size 0 marks the others).
 // Bonds that leave the brick are recorded for the next kernel, so that the lists are swept
 // once, not twice.  Also clears the statistics that the labelling adds to.
-template <bool MULTI>
-__global__ void k_cc_local(Buffers B, Launch P, int cur, ClusterWork W, int64_t *__restrict__ stats,
-                           int64_t *__restrict__ hist, int64_t nhist)
+template <bool MULTI, bool LARGE>
+__device__ __forceinline__ void cc_local_brick(const Buffers &B, const Launch &P, int cur, const ClusterWork &W, int b)
 {
     extern __shared__ __align__(16) unsigned char smem[];  // Staged, then lp[bcap]
     __shared__ int ncross;
-    const int64_t g0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gn = (int64_t)gridDim.x * blockDim.x;
-    if (stats)
-        for (int64_t k = g0; k < 5 * (int64_t)P.nrep; k += gn) stats[k] = 0;
-    if (hist)
-        for (int64_t k = g0; k < nhist; k += gn) hist[k] = 0;
-    int b;
-    if (!brick_of_block(P, B, b)) return;
     const MapFirst mf = map_prefetch(B, b, P.stage_cap);
     const int r = B.brick_rep[b];
     if (r < 0) return;
@@ -2786,6 +2791,7 @@ __global__ void k_cc_local(Buffers B, Launch P, int cur, ClusterWork W, int64_t 
     if (threadIdx.x == 0) ncross = 0;
     StageHdr S;
     pass_header(R, B, b, lb, P.stage_cap, S);
+    if (!LARGE && S.total > P.t_hi) return;
     if (S.overflow) {
         // no lists: its particles stay single, uncounted, and may be joined from outside
         for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) {
@@ -2800,8 +2806,8 @@ __global__ void k_cc_local(Buffers B, Launch P, int cur, ClusterWork W, int64_t 
     const int64_t S_ = P.nslots;
     const double *X = B.x[cur];
     const int32_t *sm = B.smap + (size_t)b * P.stage_cap;
-    const Staged T = carve_staged(smem, P.stage_cap);
-    int32_t *lp = T.type + (MULTI ? P.stage_cap + 1 : 0);
+    const Staged T = carve_staged(smem, P.lds_cap);
+    int32_t *lp = T.type + (MULTI ? P.lds_cap + 1 : 0);
     stage_bonds<MULTI>(B, P, R, S, b, X, T, mf);
     for (int t = threadIdx.x; t < S.n_own; t += blockDim.x) lp[t] = t;
     __syncthreads();
@@ -2859,6 +2865,25 @@ __global__ void k_cc_local(Buffers B, Launch P, int cur, ClusterWork W, int64_t 
         W.mintag[i] = cmin[t];
     }
     if (threadIdx.x == 0) W.z[S.base] = ncross;  // bond counts are summed: their first word counts these
+}
+
+template <bool MULTI>
+__global__ void k_cc_local(Buffers B, Launch P, int cur, ClusterWork W, int64_t *__restrict__ stats,
+                           int64_t *__restrict__ hist, int64_t nhist)
+{
+    const int64_t g0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, gn = (int64_t)gridDim.x * blockDim.x;
+    if (stats)
+        for (int64_t k = g0; k < 5 * (int64_t)P.nrep; k += gn) stats[k] = 0;
+    if (hist)
+        for (int64_t k = g0; k < nhist; k += gn) hist[k] = 0;
+    int b;
+    if (brick_of_block(P, B, b)) cc_local_brick<MULTI, false>(B, P, cur, W, b);
+}
+
+template <bool MULTI>
+__global__ void __launch_bounds__(DENSE_BLOCK) k_cc_local_dense(Buffers B, Launch P, int cur, ClusterWork W)
+{
+    each_dense(P, B, [&](int b) { cc_local_brick<MULTI, true>(B, P, cur, W, b); });
 }
 
 // Bonds that leave the brick join the global forest.  A bond is taken between the current
@@ -3094,15 +3119,13 @@ __global__ void k_cc_label(Buffers B, Launch P, ClusterWork W, int32_t *__restri
 // born now.  Each event is counted at the end with the smaller tag, once per bond.
 // stats per replica: {formed, broken with a lifetime, broken without one, partners that did
 // not fit, bonds now}.
-template <bool MULTI>
-__global__ void k_bond_track(Buffers B, Launch P, int cur, BondTrack T, int reset,
-                             int64_t *__restrict__ hist, int hist_len, int64_t bin_steps,
-                             int64_t *__restrict__ stats)
+template <bool MULTI, bool LARGE>
+__device__ __forceinline__ void bond_track_brick(const Buffers &B, const Launch &P, int cur, const BondTrack &T, int reset,
+                                                 int64_t *__restrict__ hist, int hist_len, int64_t bin_steps,
+                                                 int64_t *__restrict__ stats, int b)
 {
     extern __shared__ __align__(16) unsigned char smem[];  // Staged
     __shared__ unsigned long long tot[5];
-    int b;
-    if (!brick_of_block(P, B, b)) return;
     const MapFirst mf = map_prefetch(B, b, P.stage_cap);
     const int r = B.brick_rep[b];
     if (r < 0) return;
@@ -3111,11 +3134,11 @@ __global__ void k_bond_track(Buffers B, Launch P, int cur, BondTrack T, int rese
     if (threadIdx.x < 5) tot[threadIdx.x] = 0ull;
     StageHdr S;
     pass_header(R, B, b, lb, P.stage_cap, S);
-    if (S.overflow) return;
+    if (S.overflow || (!LARGE && S.total > P.t_hi)) return;
     const int64_t S_ = P.nslots;
     const double *X = B.x[cur];
     const int32_t *sm = B.smap + (size_t)b * P.stage_cap;
-    const Staged G = carve_staged(smem, P.stage_cap);
+    const Staged G = carve_staged(smem, P.lds_cap);
     stage_bonds<MULTI>(B, P, R, S, b, X, G, mf);
     __syncthreads();
     const bool xr = MULTI && R.excl_span > 0;
@@ -3210,6 +3233,25 @@ __global__ void k_bond_track(Buffers B, Launch P, int cur, BondTrack T, int rese
     __syncthreads();
     if (stats && threadIdx.x < 5 && tot[threadIdx.x])
         atomicAdd((unsigned long long *)(stats + 5 * (size_t)r + threadIdx.x), tot[threadIdx.x]);
+}
+
+template <bool MULTI>
+__global__ void k_bond_track(Buffers B, Launch P, int cur, BondTrack T, int reset,
+                             int64_t *__restrict__ hist, int hist_len, int64_t bin_steps,
+                             int64_t *__restrict__ stats)
+{
+    int b;
+    if (brick_of_block(P, B, b)) bond_track_brick<MULTI, false>(B, P, cur, T, reset, hist, hist_len, bin_steps, stats, b);
+}
+
+template <bool MULTI>
+__global__ void __launch_bounds__(DENSE_BLOCK) k_bond_track_dense(Buffers B, Launch P, int cur, BondTrack T, int reset,
+                                                                  int64_t *__restrict__ hist, int hist_len,
+                                                                  int64_t bin_steps, int64_t *__restrict__ stats)
+{
+    each_dense(P, B, [&](int b) {
+        bond_track_brick<MULTI, true>(B, P, cur, T, reset, hist, hist_len, bin_steps, stats, b);
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -3922,7 +3964,7 @@ size_t lds_bytes_count(const Launch &P)
 }
 size_t lds_bytes_embed(const Launch &P) { (void)P; return 0; }
 // bond tests (observables, clusters, bond tracker): FP32 staging, and the brick's forest
-static size_t staged_bytes(const Launch &P) { return (size_t)(P.stage_cap + 1) * (P.multi ? 16 : 12); }
+static size_t staged_bytes(const Launch &P) { return (size_t)(P.lds_cap + 1) * (P.multi ? 16 : 12); }
 size_t lds_bytes_bonds(const Launch &P)
 {
     return staged_bytes(P) + (size_t)P.bcap_max * sizeof(int32_t) + 16;
@@ -3937,34 +3979,37 @@ size_t lds_bytes_force(const Launch &P)
 // mean reserves LDS for them in every workgroup, so that one to three workgroups of a few waves
 // stand on a CU and a pass takes many rounds of the chip.  The bricks of usual density (as many
 // staged as a layout without a stated maximum has room for) go first, with LDS for those, then
-// the others.  Worth it where it saves two rounds: an idle second launch costs 1.6 us and its
-// bricks wait for the first (100,000 particles of density 0.3, force pass of FP64, two rounds or
-// one: 60.3 us a step in one launch, 61.9 in two).  Laid out for density 1, us a step in one and
-// two launches: 100,000 at 0.05 59.2 and 39.9 (FP64 128 and 62), 400,000 199.6 and 95.1,
-// 200,000 at 0.15 72.3 and 60.0; ten steps of twenty tracked systems of 4000 at 0.05 1151 and
-// 788, a tick of a pool of 24 at 0.3 1057 and 894.
+// the others.  Worth it where it saves rounds enough: an idle second launch costs 1.6 us and
+// its bricks wait for the first.  The force pass gains from half a round (30,000 particles at
+// density 0.05 27.6 and 26.1 us a step; with none saved, FP64 at 0.3, 60.3 and 61.9), the count
+// pass from one (0.7 saved: 88.6 and 90.1), the list pass, not due in most steps, from two (1.9
+// saved: 49.2 and 51.1).  Laid out for density 1, all passes in one and two launches:
+// 100,000 particles at 0.05 59.2 and 39.9 (FP64 128 and 62), 400,000 199.6 and 95.1, 200,000
+// at 0.15 72.3 and 60.0; ten steps of twenty tracked systems of 4000 at 0.05 1151 and 766, a
+// tick of a pool of 24 at 0.3 1057 and 872.
 void part_shape(Launch &P)
 {
     const int small = P.cap_usual;
-    P.small_count = P.small_force = P.small_list = 0;
+    P.small_count = P.small_force = P.small_list = P.small_bonds = 0;
     if (small <= 0 || small >= P.stage_cap) return;
     auto rounds = [&](int64_t nb, size_t lds, int threads, int waves_cu) {
         const int64_t n = std::min<int64_t>((LDS_MAX + 256) / (lds + 1024), waves_cu / (threads / VBC_WAVE));
-        return (nb + 256 * std::max<int64_t>(n, 1) - 1) / (256 * std::max<int64_t>(n, 1));
+        return std::max(1.0, (double)nb / (double)(256 * std::max<int64_t>(n, 1)));
     };
     Launch F = P, Q = P;
     Q.lds_cap = small;
     const int64_t nb = P.nbrick_tot;
     const int threads = P.block << (P.one ? P.split : 0);
-    auto saves = [&](int64_t n, size_t (*lds)(const Launch &), int tf, int tq, int waves) {
-        return rounds(n, lds(F), tf, waves) >= rounds(n, lds(Q), tq, waves) + 2 ? small : 0;
+    auto saves = [&](int64_t n, size_t (*lds)(const Launch &), int tf, int tq, int waves, double least) {
+        return rounds(n, lds(F), tf, waves) - rounds(n, lds(Q), tq, waves) >= least ? small : 0;
     };
-    P.small_count = saves(nb, lds_bytes_count, threads, threads, 32);
-    P.small_force = saves(nb, lds_bytes_force, threads, threads, P.precision == VBC_FP64 ? 20 : 24);
+    P.small_count = saves(nb, lds_bytes_count, threads, threads, 32, 1.0);
+    P.small_force = saves(nb, lds_bytes_force, threads, threads, P.precision == VBC_FP64 ? 20 : 24, 0.5);
+    P.small_bonds = saves(nb, lds_bytes_bonds, P.block, P.block, 32, 1.0);
     list_shape(F);
     list_shape(Q);
     // of several replicas, some are due for a build at a time
-    P.small_list = saves(P.lists ? (nb + 1) / 2 : nb, lds_bytes_nlist, F.list_block, Q.list_block, 24);
+    P.small_list = saves(P.lists ? (nb + 1) / 2 : nb, lds_bytes_nlist, F.list_block, Q.list_block, 24, 2.0);
 }
 
 namespace {
@@ -4287,9 +4332,14 @@ hipError_t launch_observe(const Buffers &B, const Launch &P, int cur, int32_t *z
                           int32_t *pen_out, int64_t *sums, hipStream_t s)
 {
     if (sums) k_zero_i64<<<blocks_for(3 * P.nrep, 256), 256, 0, s>>>(sums, 3 * P.nrep);
-    const unsigned g = brick_grid(P.nb_launch);
-    if (P.multi) k_observe<true><<<g, P.block, staged_bytes(P), s>>>(B, P, cur, z_out, pen_out, sums);
-    else k_observe<false><<<g, P.block, staged_bytes(P), s>>>(B, P, cur, z_out, pen_out, sums);
+    parts(P, P.small_bonds, [&](const Launch &Q) {
+        const bool dense = Q.t_lo >= 0;
+        const unsigned g = dense ? dense_grid(Q.nb_launch) : brick_grid(Q.nb_launch);
+        const int bs = dense ? std::min(Q.block, DENSE_BLOCK) : Q.block;
+        auto k = dense ? (Q.multi ? k_observe_dense<true> : k_observe_dense<false>)
+                       : (Q.multi ? k_observe<true> : k_observe<false>);
+        k<<<g, bs, staged_bytes(Q), s>>>(B, Q, cur, z_out, pen_out, sums);
+    });
     return hipGetLastError();
 }
 
@@ -4298,8 +4348,16 @@ hipError_t launch_clusters(const Buffers &B, const Launch &P, int cur, const Clu
 {
     const unsigned g = brick_grid(P.nb_launch);
     const int64_t nhist = 2 * (int64_t)P.nrep * hist_len;
-    if (P.multi) k_cc_local<true><<<g, P.block, lds_bytes_bonds(P), s>>>(B, P, cur, W, stats, hist, nhist);
-    else k_cc_local<false><<<g, P.block, lds_bytes_bonds(P), s>>>(B, P, cur, W, stats, hist, nhist);
+    parts(P, P.small_bonds, [&](const Launch &Q) {
+        const size_t lds = lds_bytes_bonds(Q);
+        if (Q.t_lo >= 0) {
+            auto k = Q.multi ? k_cc_local_dense<true> : k_cc_local_dense<false>;
+            k<<<dense_grid(Q.nb_launch), std::min(Q.block, DENSE_BLOCK), lds, s>>>(B, Q, cur, W);
+        } else {
+            auto k = Q.multi ? k_cc_local<true> : k_cc_local<false>;
+            k<<<g, Q.block, lds, s>>>(B, Q, cur, W, stats, hist, nhist);
+        }
+    });
     k_cc_hook<<<g, 256, 0, s>>>(B, P, cur, W);
     k_cc_count<<<g, 256, 0, s>>>(B, P, W);
     const size_t lh = hist && hist_len <= CC_HIST ? (size_t)2 * hist_len * sizeof(uint32_t) : 0;
@@ -4312,11 +4370,14 @@ hipError_t launch_bond_track(const Buffers &B, const Launch &P, int cur, const B
 {
     if (reset && stats) k_zero_i64<<<blocks_for(5 * P.nrep, 256), 256, 0, s>>>(stats, 5 * P.nrep);
     if (reset && hist) k_zero_i64<<<blocks_for((int64_t)P.nrep * hist_len, 256), 256, 0, s>>>(hist, P.nrep * hist_len);
-    const unsigned g = brick_grid(P.nb_launch);
-    if (P.multi)
-        k_bond_track<true><<<g, P.block, staged_bytes(P), s>>>(B, P, cur, T, reset, hist, hist_len, bin_steps, stats);
-    else
-        k_bond_track<false><<<g, P.block, staged_bytes(P), s>>>(B, P, cur, T, reset, hist, hist_len, bin_steps, stats);
+    parts(P, P.small_bonds, [&](const Launch &Q) {
+        const bool dense = Q.t_lo >= 0;
+        const unsigned g = dense ? dense_grid(Q.nb_launch) : brick_grid(Q.nb_launch);
+        const int bs = dense ? std::min(Q.block, DENSE_BLOCK) : Q.block;
+        auto k = dense ? (Q.multi ? k_bond_track_dense<true> : k_bond_track_dense<false>)
+                       : (Q.multi ? k_bond_track<true> : k_bond_track<false>);
+        k<<<g, bs, staged_bytes(Q), s>>>(B, Q, cur, T, reset, hist, hist_len, bin_steps, stats);
+    });
     return hipGetLastError();
 }
 

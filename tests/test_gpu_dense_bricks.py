@@ -48,7 +48,10 @@ def test_two_launches_give_the_results_of_one(reps, ball, precision):
         z, pen, _ = s.observables()
         got[block] = [n, F.cpu().numpy(), e.cpu().numpy()]
         ints = [z.cpu().numpy(), pen.cpu().numpy(), s.clusters()[0].cpu().numpy()]
+        tr = s.bond_tracker(max_partners=64, hist_len=16, bin_steps=1)
         s.step(3, integrator="nve", dt=0.0002)
+        tr.sample()
+        ints += [tr.stats.cpu().numpy(), tr.hist.cpu().numpy()]
         got[block].append(s.get_state()[0].cpu().numpy())
         got[block].append(ints)
         s.check()
