@@ -1352,18 +1352,28 @@ __device__ __forceinline__ const RepDev &rep_of(const OneRep<ONE> &R1, const Buf
     else return B.reps[r];
 }
 
+// Length and first chunk of a particle's list (the chunk row 0 exists for every slot).  The
+// count and force passes of a single replica read a thread's first one before the staging,
+// whose latency then covers it (10 to 12 us of ten steps of 100,000 and of a million
+// particles; in a set of mostly empty bricks the reads would cost as much as they save).
+struct ListHead {
+    int nn;
+    uint4 q;
+};
+__device__ __forceinline__ ListHead list_head(const Buffers &B, int64_t i) { return ListHead{(int)B.nn[i], B.nl[i]}; }
+
 // Visit the list of one own particle in whole chunks of eight entries (the last chunk is
 // padded with the dummy staged slot, whose terms all vanish), with the next chunk's load
 // issued before the current one is processed.  fn(staged index) is called for every entry
 // of a chunk without a guard, so the eight LDS gathers of a chunk can be in flight together.
 template <class F, class G>
 __device__ __forceinline__ void for_each_neighbour(const uint4 *__restrict__ nl, int64_t S_,
-                                                   int64_t i, int nn, F &&fn, G &&done)
+                                                   int64_t i, const ListHead &head, F &&fn, G &&done)
 {
-    int nch = (nn + CHUNK - 1) / CHUNK;
+    int nch = (head.nn + CHUNK - 1) / CHUNK;
     if (nch == 0) return;
     const uint4 *lp = nl + i;
-    uint4 q = lp[0];
+    uint4 q = head.q;
     for (int c = 0; c < nch; ++c) {
         uint4 qn = (c + 1 < nch) ? lp[(size_t)(c + 1) * S_] : q;
         uint32_t w[4] = {q.x, q.y, q.z, q.w};
@@ -1378,7 +1388,7 @@ template <class F>
 __device__ __forceinline__ void for_each_neighbour(const uint4 *__restrict__ nl, int64_t S_,
                                                    int64_t i, int nn, F &&fn)
 {
-    for_each_neighbour(nl, S_, i, nn, fn, []() {});
+    if (nn > 0) for_each_neighbour(nl, S_, i, ListHead{nn, nl[i]}, fn, []() {});
 }
 
 // The value of lane j of each group of two (ls = 1) or four lanes, within the vector unit.
@@ -1705,6 +1715,9 @@ __device__ __forceinline__ void count_brick(const Buffers &B, const Launch &P, i
         return;
     }
     const double *X = B.x[cur];
+    constexpr bool AHEAD = ONE && !SPLIT && !MULTI;
+    ListHead head;
+    if (AHEAD) head = list_head(B, S.base + min((int)threadIdx.x, R.bcap - 1));
     // an empty brick stages nothing (many small replicas; a single one has few)
     if (ONE || S.n_own > 0) stage_map4(B, b, P.stage_cap, S, mf, [&](int t, int src, int w, bool ok) {
         const R4 p = local_pos<Real>(R, S, X, S_, src, w, MULTI ? B.type[src] : 0);
@@ -1798,7 +1811,7 @@ __device__ __forceinline__ void count_brick(const Buffers &B, const Launch &P, i
                 n = add_group(n, (double)chunk, ls);
                 chunk = Real(0);
             });
-        else for_each_neighbour(B.nl, S_, i, B.nn[i], entry);
+        else for_each_neighbour(B.nl, S_, i, AHEAD && t == (int)threadIdx.x ? head : list_head(B, i), entry, []() {});
         evals += (unsigned long long)inside;
         if (SPLIT && sub) continue;
         B.nd[i] = n;
@@ -2103,6 +2116,9 @@ __device__ __forceinline__ void force_brick(const Buffers &B, const Launch &P, i
     }
     const double *X = B.x[cur];
     const Real cc0 = pair_r<Real>(R.pair[0], R.rc2).c_c;
+    constexpr bool AHEAD = ONE && !SPLIT && !MULTI;
+    ListHead head;
+    if (AHEAD) head = list_head(B, S.base + min((int)threadIdx.x, R.bcap - 1));
     if (ONE || S.n_own > 0) stage_map4(B, b, P.stage_cap, S, mf, [&](int t, int src, int w, bool ok) {
         R4 p = local_pos<Real>(R, S, X, S_, src, w, MULTI ? B.type[src] : 0);
         const R2 sa = sA[src];
@@ -2223,7 +2239,7 @@ __device__ __forceinline__ void force_brick(const Buffers &B, const Launch &P, i
             });
             if (sub) continue;
         } else {
-            for_each_neighbour(B.nl, S_, i, B.nn[i], entry, [&]() {
+            for_each_neighbour(B.nl, S_, i, AHEAD && t == (int)threadIdx.x ? head : list_head(B, i), entry, [&]() {
                 if (CHUNKED) {
                     fx += cx;
                     fy += cy;
