@@ -2991,7 +2991,10 @@ __global__ void k_cc_count(Buffers B, Launch P, ClusterWork W)
         const int64_t i = base + t;
         const int32_t sz = W.size[i];
         if (sz == 0) continue;  // not a component's root
-        const int32_t root = cc_find(W.parent, (int32_t)i);
+        // no path halving here: another thread's halving of slot i, from what it read before
+        // the line below, could put an ancestor short of the root back
+        int32_t root = (int32_t)i;
+        for (int32_t p = cc_ld(W.parent + root); p != root; p = cc_ld(W.parent + root)) root = p;
         if (root == (int32_t)i) continue;
         cc_st(W.parent + i, root);
         const uint32_t en = W.ends[i];
