@@ -1315,7 +1315,7 @@ vbc_status vbc_get_state(vbc_handle h, int32_t rep, double *d_x, double *d_v, hi
         if (!h->live[r] || (rep >= 0 && r != rep)) continue;
         const RepDev &R = h->reps[r];
         int64_t off = rep < 0 ? R.o_off : 0, stride = rep < 0 ? h->P.ntot : R.n;
-        VBC_TRY(h, launch_get_state(h->B, h->P, h->cur, r, (int64_t)R.nbrick * R.bcap, off, stride, d_x, d_v, s),
+        VBC_TRY(h, launch_get_state(h->B, h->P, h->cur, r, R.n, (int64_t)R.nbrick * R.bcap, off, stride, d_x, d_v, s),
                 "get_state");
     }
     return VBC_OK;

@@ -209,7 +209,7 @@ hipError_t launch_events_error();
 hipError_t launch_set_state(const Buffers &B, const Launch &P, int cur, int r, int64_t n,
                             const double *x, const double *v, const int32_t *type,
                             int64_t in_off, int64_t in_stride, uint64_t step0, hipStream_t s);
-hipError_t launch_get_state(const Buffers &B, const Launch &P, int cur, int r, int64_t nslot,
+hipError_t launch_get_state(const Buffers &B, const Launch &P, int cur, int r, int64_t n, int64_t nslot,
                             int64_t out_off, int64_t out_stride, double *x, double *v,
                             hipStream_t s);
 hipError_t launch_set_state_all(const Buffers &B, const Launch &P, int cur, const double *x, const double *v,
