@@ -80,18 +80,19 @@ __device__ __forceinline__ bool resolve_brick(const Launch &P, const Buffers &B,
     return r >= 0;
 }
 
-// The second of two launches of a pass (see parts): a workgroup looks at DENSE bricks, far
-// apart, and does those with more than t_lo staged particles one after the other.  A grid of a
-// workgroup per brick, with the full capacity's LDS, would need as many rounds of the chip to
-// find nothing to do as the pass takes in all.  The mask is a scalar, the same in every wave.
-constexpr int DENSE = 8, DENSE_BLOCK = 512;  // at most so many threads: their registers are not what limits them
+// The second of two launches of a pass (see parts): a workgroup looks at up to 64 bricks, far
+// apart, and does those with more than t_lo staged particles one after the other.  The grid is
+// as many workgroups as the chip holds at once (dense_grid): one per brick, with the full
+// capacity's LDS, would need as many rounds of the chip to find nothing to do as the pass takes
+// in all.  The mask is a scalar, the same in every wave.
+constexpr int DENSE_BLOCK = 512;  // at most so many threads: their registers are not what limits them
 template <class F>
 __device__ __forceinline__ void each_dense(const Launch &P, const Buffers &B, F &&body)
 {
     const int T = P.list < 0 ? P.nb_launch : B.wl_n[P.list];
     const int lane = threadIdx.x % VBC_WAVE, kl = blockIdx.x + lane * gridDim.x;
     bool dense = false;
-    if (lane < DENSE && kl < T) dense = B.stotal[P.list < 0 ? P.b_lo + kl : B.wl[P.list][kl]] > P.t_lo;
+    if (kl < T) dense = B.stotal[P.list < 0 ? P.b_lo + kl : B.wl[P.list][kl]] > P.t_lo;
     uint64_t mask = __ballot(dense);
     while (mask) {
         const int k = blockIdx.x + __builtin_ctzll(mask) * gridDim.x;
@@ -3938,7 +3939,11 @@ static inline unsigned blocks_for(int64_t n, int bs) { return (unsigned)((n + bs
 constexpr int LIST_WAVES = 12, LIST_WAVES_ALONE = 16;
 constexpr size_t LIST_LDS = 80 * 1024 - 256, LDS_MAX = 160 * 1024 - 256;
 
-static inline unsigned dense_grid(int nb) { return (unsigned)((nb + DENSE - 1) / DENSE); }
+static inline unsigned dense_grid(int nb, size_t lds)
+{
+    const int n = std::max(1, std::min(8, (int)((LDS_MAX + 256) / (lds + 1024))));
+    return (unsigned)std::min(nb, std::max(256 * n, (nb + VBC_WAVE - 1) / VBC_WAVE));
+}
 static inline unsigned brick_grid(int nb) { return (unsigned)(((nb + 7) / 8) * 8); }
 
 static size_t tabs_bytes(const Launch &P)
@@ -4202,7 +4207,7 @@ static void launch_nlist(const Buffers &B, const Launch &P, int cur, hipStream_t
     parts(P, P.small_list, [&](Launch Q) {
         list_shape(Q);
         if (Q.t_lo >= 0) Q.list_block = std::min(Q.list_block, DENSE_BLOCK);
-        if (Q.t_lo >= 0) tlaunch(k_nlist_dense, dense_grid(Q.nb_launch), Q.list_block, lds_bytes_nlist(Q), s, B, Q, cur);
+        if (Q.t_lo >= 0) tlaunch(k_nlist_dense, dense_grid(Q.nb_launch, lds_bytes_nlist(Q)), Q.list_block, lds_bytes_nlist(Q), s, B, Q, cur);
         else tlaunch(k_nlist, brick_grid(Q.nb_launch), Q.list_block, lds_bytes_nlist(Q), s, B, Q, cur);
     });
 }
@@ -4260,7 +4265,7 @@ static void launch_count_t(const Buffers &B, const Launch &P, int cur, double *n
 {
     const size_t lds = lds_bytes_count(P);
     const unsigned g = brick_grid(P.nb_launch);
-    if (P.t_lo >= 0) tlaunch(k_count_dense<Real, MULTI, STATS>, dense_grid(P.nb_launch), std::min(P.block, DENSE_BLOCK), lds, s, B, P, cur, n_out, advance);
+    if (P.t_lo >= 0) tlaunch(k_count_dense<Real, MULTI, STATS>, dense_grid(P.nb_launch, lds), std::min(P.block, DENSE_BLOCK), lds, s, B, P, cur, n_out, advance);
     else if (!P.one || (P.t_hi != INT32_MAX && !P.split)) tlaunch(k_count<Real, MULTI, STATS, false, false>, g, P.block, lds, s, B, P, cur, n_out, advance, OneRep<false>{0});
     else if (!P.split) tlaunch(k_count<Real, MULTI, STATS, true, false>, g, P.block, lds, s, B, P, cur, n_out, advance, OneRep<true>{*P.one});
     else if constexpr (sizeof(Real) == 8)
@@ -4313,7 +4318,7 @@ static void launch_force_t(const Buffers &B, const Launch &P, int cur, Mode mode
     const size_t lds = lds_bytes_force(P);
     const unsigned g = brick_grid(P.nb_launch);
     const int m = (int)mode;
-    if (P.t_lo >= 0) tlaunch(k_force_dense<Real, MULTI, THERMO>, dense_grid(P.nb_launch), std::min(P.block, DENSE_BLOCK), lds, s, B, P, cur, m, st, F_out, e_out);
+    if (P.t_lo >= 0) tlaunch(k_force_dense<Real, MULTI, THERMO>, dense_grid(P.nb_launch, lds), std::min(P.block, DENSE_BLOCK), lds, s, B, P, cur, m, st, F_out, e_out);
     else if (!P.one || (P.t_hi != INT32_MAX && (THERMO || !P.split))) tlaunch(k_force<Real, MULTI, THERMO, false, false>, g, P.block, lds, s, B, P, cur, m, st, F_out, e_out, OneRep<false>{0});
     else if (THERMO || !P.split) tlaunch(k_force<Real, MULTI, THERMO, true, false>, g, P.block, lds, s, B, P, cur, m, st, F_out, e_out, OneRep<true>{*P.one});
     else if constexpr (sizeof(Real) == 8 && !THERMO)
@@ -4403,7 +4408,7 @@ hipError_t launch_observe(const Buffers &B, const Launch &P, int cur, int32_t *z
     if (sums) k_zero_i64<<<blocks_for(3 * P.nrep, 256), 256, 0, s>>>(sums, 3 * P.nrep);
     parts(P, P.small_bonds, [&](const Launch &Q) {
         const bool dense = Q.t_lo >= 0;
-        const unsigned g = dense ? dense_grid(Q.nb_launch) : brick_grid(Q.nb_launch);
+        const unsigned g = dense ? dense_grid(Q.nb_launch, staged_bytes(Q)) : brick_grid(Q.nb_launch);
         const int bs = dense ? std::min(Q.block, DENSE_BLOCK) : Q.block;
         auto k = dense ? (Q.multi ? k_observe_dense<true> : k_observe_dense<false>)
                        : (Q.multi ? k_observe<true> : k_observe<false>);
@@ -4421,7 +4426,7 @@ hipError_t launch_clusters(const Buffers &B, const Launch &P, int cur, const Clu
         const size_t lds = lds_bytes_bonds(Q);
         if (Q.t_lo >= 0) {
             auto k = Q.multi ? k_cc_local_dense<true> : k_cc_local_dense<false>;
-            k<<<dense_grid(Q.nb_launch), std::min(Q.block, DENSE_BLOCK), lds, s>>>(B, Q, cur, W);
+            k<<<dense_grid(Q.nb_launch, lds), std::min(Q.block, DENSE_BLOCK), lds, s>>>(B, Q, cur, W);
         } else {
             auto k = Q.multi ? k_cc_local<true> : k_cc_local<false>;
             k<<<g, Q.block, lds, s>>>(B, Q, cur, W, stats, hist, nhist);
@@ -4441,7 +4446,7 @@ hipError_t launch_bond_track(const Buffers &B, const Launch &P, int cur, const B
     if (reset && hist) k_zero_i64<<<blocks_for((int64_t)P.nrep * hist_len, 256), 256, 0, s>>>(hist, P.nrep * hist_len);
     parts(P, P.small_bonds, [&](const Launch &Q) {
         const bool dense = Q.t_lo >= 0;
-        const unsigned g = dense ? dense_grid(Q.nb_launch) : brick_grid(Q.nb_launch);
+        const unsigned g = dense ? dense_grid(Q.nb_launch, staged_bytes(Q)) : brick_grid(Q.nb_launch);
         const int bs = dense ? std::min(Q.block, DENSE_BLOCK) : Q.block;
         auto k = dense ? (Q.multi ? k_bond_track_dense<true> : k_bond_track_dense<false>)
                        : (Q.multi ? k_bond_track<true> : k_bond_track<false>);
