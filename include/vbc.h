@@ -183,7 +183,8 @@ vbc_status vbc_force(vbc_handle h, double *d_F, double *d_e, double *d_UW, hipSt
  * calls replay graphs of 8 steps.  A set of eight or more small replicas (vbc_create; one type,
  * at most 1024 particles each) may run as one launch of one workgroup per replica instead,
  * whose trajectories differ from the others' in the rounding of sums only; its passes are not
- * told apart by vbc_profile. */
+ * told apart by vbc_profile.  A replica admitted into such a set steps the same way; one that
+ * cannot (more than 1024 particles) takes the whole set to the other passes from then on. */
 vbc_status vbc_step(vbc_handle h, int32_t nsteps, const vbc_integrator *it, hipStream_t s);
 
 /* Capture, without launching anything, the step graphs that vbc_step(h, nsteps, it, ...)

@@ -666,6 +666,18 @@ vbc_status make_handle(const Caps &C, const vbc_options &opt, bool pool, void *d
     return VBC_OK;
 }
 
+// Upload the host's copy of replica r's descriptor.
+vbc_status upload(vbc_handle h, int r, hipStream_t s)
+{
+    if (h->up_pending[r]) VBC_TRY(h, hipEventSynchronize(h->up_ev[r]), "upload wait");
+    h->up[r] = h->reps[r];
+    VBC_TRY(h, hipMemcpyAsync(h->B.reps + r, h->up + r, sizeof(RepDev), hipMemcpyHostToDevice, s),
+            "descriptor upload");
+    VBC_TRY(h, hipEventRecord(h->up_ev[r], s), "upload event");
+    h->up_pending[r] = 1;
+    return VBC_OK;
+}
+
 // Place a planned replica in a free slot: take its ranges, upload its descriptor and
 // write its tables (stream-ordered after all earlier work on s).
 vbc_status place(vbc_handle h, const RepPlan &rp, hipStream_t s, int32_t *rep_out)
@@ -690,20 +702,35 @@ vbc_status place(vbc_handle h, const RepPlan &rp, hipStream_t s, int32_t *rep_ou
     R.b_off = (int32_t)b;
     R.c_off = (int32_t)c;
     R.o_off = o;
-    if (h->up_pending[r]) VBC_TRY(h, hipEventSynchronize(h->up_ev[r]), "upload wait");
-    h->up[r] = R;
-    VBC_TRY(h, hipMemcpyAsync(h->B.reps + r, h->up + r, sizeof(RepDev), hipMemcpyHostToDevice, s),
-            "descriptor upload");
-    VBC_TRY(h, hipEventRecord(h->up_ev[r], s), "upload event");
-    h->up_pending[r] = 1;
-    VBC_TRY(h, launch_admit(h->B, r, std::max<int64_t>(R.nbrick, R.ncell), s), "admit");
     h->reps[r] = R;
+    const vbc_status st = upload(h, r, s);
+    if (st != VBC_OK) return st;
+    VBC_TRY(h, launch_admit(h->B, r, std::max<int64_t>(R.nbrick, R.ncell), s), "admit");
     h->live[r] = 1;
     h->has_state[r] = 0;
     h->need_full[r] = 0;
     h->fvalid[r] = 0;
     h->res[r] = 0;
     *rep_out = r;
+    return VBC_OK;
+}
+
+// A set whose steps run in one workgroup per replica (k_resident) goes over to the brick
+// passes, which take every replica.  Replicas in caller order get their layout as after
+// vbc_set_state; the others' reference positions may have served as the cluster analysis'
+// space, so their lists are due, and forces are evaluated anew.
+vbc_status leave_resident(vbc_handle h, hipStream_t s)
+{
+    for (int r = 0; r < h->P.nrep; ++r) {
+        h->fvalid[r] = 0;
+        if (!h->live[r] || !h->reps[r].resident) continue;
+        h->reps[r].resident = 0;
+        const vbc_status st = upload(h, r, s);
+        if (st != VBC_OK) return st;
+    }
+    VBC_TRY(h, launch_flags(h->B, 0, h->P.nrep, VBC_FLAG_REBUILD, true, s), "flags");
+    h->resident = 0;
+    h->maybe_due = true;
     return VBC_OK;
 }
 
@@ -1171,9 +1198,16 @@ vbc_status vbc_admit(vbc_handle h, const vbc_replica_desc *d, const double *d_x,
         return hfail(h, VBC_ERR_CAPACITY, "replica too dense for the pool: needs k_max " +
                                               std::to_string(rp.k_max_auto) + ", stage_cap " +
                                               std::to_string(rp.stage_cap_auto));
+    rp.R.resident = h->resident && resident_can(R) ? 1 : 0;
     int32_t r = -1;
     st = place(h, rp, s, &r);
     if (st != VBC_OK) return st;
+    if (h->resident && R.resident) {
+        h->resident = std::max(h->resident, (int)R.n);
+    } else if (h->resident) {
+        st = leave_resident(h, s);
+        if (st != VBC_OK) return st;
+    }
     // the first replicas of a pool set its workgroup sizes (they never shrink, so a stream of
     // requests recaptures the step graphs once or twice); results do not depend on them
     Launch Q = h->P;
