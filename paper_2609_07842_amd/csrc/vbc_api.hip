@@ -68,6 +68,7 @@ struct vbc_handle_s {
     int cur = 0;            // which position buffer holds the current positions
     bool maybe_due = false; // steps were taken since the last rebuild launch over all bricks
     bool replayed = false;  // steps were captured into a caller's graph: they may run unseen
+    bool res_replayed = false;  // the same for resident steps
     std::string err;
     // kernel timing (vbc_profile)
     bool prof = false;
@@ -715,25 +716,6 @@ vbc_status place(vbc_handle h, const RepPlan &rp, hipStream_t s, int32_t *rep_ou
     return VBC_OK;
 }
 
-// A set whose steps run in one workgroup per replica (k_resident) goes over to the brick
-// passes, which take every replica.  Replicas in caller order get their layout as after
-// vbc_set_state; the others' reference positions may have served as the cluster analysis'
-// space, so their lists are due, and forces are evaluated anew.
-vbc_status leave_resident(vbc_handle h, hipStream_t s)
-{
-    for (int r = 0; r < h->P.nrep; ++r) {
-        h->fvalid[r] = 0;
-        if (!h->live[r] || !h->reps[r].resident) continue;
-        h->reps[r].resident = 0;
-        const vbc_status st = upload(h, r, s);
-        if (st != VBC_OK) return st;
-    }
-    VBC_TRY(h, launch_flags(h->B, 0, h->P.nrep, VBC_FLAG_REBUILD, true, s), "flags");
-    h->resident = 0;
-    h->maybe_due = true;
-    return VBC_OK;
-}
-
 bool any_live(vbc_handle h)
 {
     for (char l : h->live)
@@ -763,32 +745,51 @@ bool all_have_state(vbc_handle h)
         if (!all_have_state(h)) return hfail(h, VBC_ERR_STATE, "no state set"); \
     } while (0)
 
+static bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &st);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e != hipSuccess || st != hipStreamCaptureStatusNone;
+}
+
+// Whether only the device knows which replicas stand in caller order: steps of a resident set
+// put them there, so a graph that holds such steps moves them at every replay, and a pass
+// captured now may be replayed before or after steps.
+static bool device_decides(vbc_handle h, hipStream_t s)
+{
+    return h->res_replayed || (h->resident && capturing(s));
+}
+
 // Replicas whose state was set from caller-order input get a full build (bin, sort,
 // list) of their own bricks before anything reads their layout.
 // Several of them are built together, over all bricks (a handle of 1024 replicas: 0.2 ms
 // instead of 28 ms for four launches each); one alone over its own bricks only, as when a
-// request enters a running pool.
+// request enters a running pool.  The builds take the replicas whose FLAG_FULL is set, so
+// that where only the device knows which those are, the launches always go out.
 static vbc_status ensure_layout(vbc_handle h, hipStream_t s)
 {
+    const bool any = device_decides(h, s);
     int pending = 0, one = -1;
     for (int r = 0; r < h->P.nrep; ++r)
         if (h->live[r] && h->need_full[r]) {
             ++pending;
             one = r;
         }
-    if (!pending) return VBC_OK;
-    if (pending == 1) {
+    if (!pending && !any) return VBC_OK;
+    if (pending == 1 && !any) {
         const RepDev &R = h->reps[one];
         Launch Q = restrict_to(h->P, R);
         VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_full_build(h->B, Q, h->cur, one, R.n, s); }),
                 "full build");
-        VBC_TRY(h, launch_flags(h->B, one, 1, VBC_FLAG_REBUILD | FLAG_FULL | FLAG_RES, false, s), "flags");
     } else {
         VBC_TRY(h, timed(h, VBC_K_BUILD, s, [&] { return launch_full_build_all(h->B, h->P, h->cur, s); }),
                 "full builds");
     }
+    // a captured build has not run yet, and may run after further steps
+    if (any && capturing(s)) return VBC_OK;
     for (int r = 0; r < h->P.nrep; ++r)
-        if (h->live[r] && h->need_full[r]) h->need_full[r] = h->fvalid[r] = h->res[r] = 0;
+        if (h->live[r] && (any || h->need_full[r])) h->need_full[r] = h->fvalid[r] = h->res[r] = 0;
     return VBC_OK;
 }
 
@@ -798,17 +799,31 @@ static vbc_status ensure_layout(vbc_handle h, hipStream_t s)
         if (_st != VBC_OK) return _st;            \
     } while (0)
 
+// A set whose steps run in one workgroup per replica (k_resident) goes over to the brick
+// passes, which take every replica.  Replicas in caller order get their layout as after
+// vbc_set_state; the others' reference positions may have served as the cluster analysis'
+// space, so their lists are due, and forces are evaluated anew.  Captured resident steps do
+// nothing from then on.
+static vbc_status leave_resident(vbc_handle h, hipStream_t s)
+{
+    for (int r = 0; r < h->P.nrep; ++r) {
+        h->fvalid[r] = 0;
+        if (!h->live[r] || !h->reps[r].resident) continue;
+        h->reps[r].resident = 0;
+        const vbc_status st = upload(h, r, s);
+        if (st != VBC_OK) return st;
+    }
+    VBC_TRY(h, launch_flags(h->B, 0, h->P.nrep, VBC_FLAG_REBUILD, true, s), "flags");
+    if (h->res_replayed) VBC_LAYOUT(h, s);
+    h->resident = 0;
+    h->res_replayed = false;
+    h->maybe_due = true;
+    return VBC_OK;
+}
+
 // The rebuild kernels before a pass over the current positions.  Without steps since they last
 // ran no list can be due, and a fixed set leaves the two idle launches (10 us) out; a pool's
 // passes need the work list they make, and a call being captured may be replayed after steps.
-static bool capturing(hipStream_t s)
-{
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    const hipError_t e = hipStreamIsCapturing(s, &st);
-    if (e != hipSuccess) (void)hipGetLastError();
-    return e != hipSuccess || st != hipStreamCaptureStatusNone;
-}
-
 static hipError_t rebuild_if_due(vbc_handle h, hipStream_t s)
 {
     if (!h->maybe_due && !h->replayed && h->P.list < 0 && !capturing(s)) return hipSuccess;
@@ -1339,7 +1354,8 @@ vbc_status vbc_get_state(vbc_handle h, int32_t rep, double *d_x, double *d_v, hi
     if (rep >= 0 ? !h->has_state[rep] : !all_have_state(h)) return hfail(h, VBC_ERR_STATE, "no state set");
     // resident replicas are read from caller order; the others need their layout
     bool layout = false;
-    for (int r = 0; r < h->P.nrep; ++r) layout = layout || (h->live[r] && h->need_full[r] && !h->res[r]);
+    if (!device_decides(h, s))
+        for (int r = 0; r < h->P.nrep; ++r) layout = layout || (h->live[r] && h->need_full[r] && !h->res[r]);
     if (layout) VBC_LAYOUT(h, s);
     if (rep < 0 && live_count(h) > 1) {
         VBC_TRY(h, launch_get_state_all(h->B, h->P, h->cur, d_x, d_v, s), "get_state");
@@ -1360,7 +1376,7 @@ vbc_status vbc_build_nlist(vbc_handle h, hipStream_t s)
     Range range_("vbc_build_nlist");
     if (!h) return fail(VBC_ERR_ARG, "NULL handle");
     VBC_NEED_STATE(h);
-    bool full = true;
+    bool full = !device_decides(h, s);  // every list is built by the full builds
     for (int r = 0; r < h->P.nrep; ++r) full = full && (!h->live[r] || h->need_full[r]);
     VBC_LAYOUT(h, s);
     // resident replicas too build their lists from here on
@@ -1451,14 +1467,19 @@ vbc_status vbc_step(vbc_handle h, int32_t nsteps, const vbc_integrator *it, hipS
     if (h->resident) {
         StepArgs sr = st;
         sr.acc = h->thermo ? 1 : 0;
+        // a graph of the caller's may be replayed with larger replicas admitted since
+        const bool cap = capturing(s);
+        const int max_n = cap ? RES_MAX_N : h->resident;
         // with time stamps, each step is a launch with its stamp
         const int each = h->stamps ? 1 : nsteps;
         for (int k = 0; k < nsteps; k += each) {
-            VBC_TRY(h, launch_resident(h->B, h->P, h->cur, each, k, h->resident, sr, s), "resident steps");
+            VBC_TRY(h, launch_resident(h->B, h->P, h->cur, each, k, max_n, sr, s), "resident steps");
             if (h->stamps) VBC_TRY(h, launch_stamp(h->B, s), "stamp");
         }
-        for (int k = 0; k < h->P.nrep; ++k)
-            if (h->live[k]) h->need_full[k] = h->res[k] = 1;
+        if (cap) h->res_replayed = true;
+        else
+            for (int k = 0; k < h->P.nrep; ++k)
+                if (h->live[k]) h->need_full[k] = h->res[k] = 1;
         return VBC_OK;
     }
     VBC_LAYOUT(h, s);

@@ -266,6 +266,7 @@ hipError_t launch_clusters(const Buffers &B, const Launch &P, int cur, const Clu
 hipError_t launch_resident(const Buffers &B, const Launch &P, int cur, int nsteps, int k0, int max_n,
                            const StepArgs &st, hipStream_t s);
 bool resident_can(const RepDev &R);
+constexpr int RES_MAX_N = 1024;  // particles of a resident replica, one thread each
 size_t lds_bytes_sort(const Launch &P);
 size_t lds_bytes_nlist(const Launch &P);
 size_t lds_need_nlist(const Launch &P);

@@ -533,8 +533,8 @@ __global__ void k_get_state(Buffers B, int64_t S_, int cur, int r, int64_t out_o
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= (int64_t)R.nbrick * R.bcap) return;
     int lb = (int)(k / R.bcap);
-    // after resident steps the particles stand in caller order
-    if (B.flags[r] & FLAG_RES) {
+    // before a full build and after resident steps the particles stand in caller order
+    if (B.flags[r] & FLAG_FULL) {
         if (k >= R.n) return;
     } else if (k - (int64_t)lb * R.bcap >= B.bcnt[0][R.b_off + lb]) {
         return;
@@ -591,7 +591,7 @@ __global__ void k_get_state_all(Buffers B, int64_t S_, int cur, int64_t out_stri
     if (r < 0) return;
     const RepDev &R = B.reps[r];
     const int64_t k0 = (int64_t)(b - R.b_off) * R.bcap, base = R.p_off + k0;
-    if (B.flags[r] & FLAG_RES) n = (int)min((int64_t)R.bcap, R.n - k0);  // caller order
+    if (B.flags[r] & FLAG_FULL) n = (int)min((int64_t)R.bcap, R.n - k0);  // caller order
     for (int t = threadIdx.x; t < n; t += blockDim.x)
         take_state(B, R, S_, cur, base + t, R.o_off, out_stride, x, v);
 }
@@ -604,11 +604,11 @@ __global__ void k_flags(Buffers B, int r_lo, int r_n, uint32_t bits, int set)
     if (set) B.flags[r] |= bits; else B.flags[r] &= ~bits;
 }
 
-// The replicas that a full build of all bricks has just built are no longer due.
-__global__ void k_full_done(Buffers B, int nrep)
+// The replicas that a full build has just built are no longer due.
+__global__ void k_full_done(Buffers B, int r_lo, int r_n)
 {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < nrep && (B.flags[r] & FLAG_FULL)) B.flags[r] &= ~(uint32_t)(VBC_FLAG_REBUILD | FLAG_FULL | FLAG_RES);
+    const int k = blockIdx.x * blockDim.x + threadIdx.x, r = r_lo + k;
+    if (k < r_n && (B.flags[r] & FLAG_FULL)) B.flags[r] &= ~(uint32_t)(VBC_FLAG_REBUILD | FLAG_FULL | FLAG_RES);
 }
 
 // Rank of a cell in the brick-major order (bricks x-fastest, cells x-fastest inside a
@@ -3343,7 +3343,6 @@ __global__ void __launch_bounds__(DENSE_BLOCK) k_bond_track_dense(Buffers B, Lau
 //
 // A thread owns the particle of its index: position, velocity, force and reference position
 // stay in registers through a call, and only the list is read from memory.
-constexpr int RES_MAX_N = 1024;
 constexpr double RES_MAX_L = 512.0;
 
 template <class Real> struct ResLds;
@@ -4212,15 +4211,19 @@ static void launch_nlist(const Buffers &B, const Launch &P, int cur, hipStream_t
     });
 }
 
-// Full build of replica r (P covering its bricks): bin and sort it from caller-order
-// input, then build its list.  k_resort skips FULL replicas, so the same two-kernel tail
-// as an incremental rebuild serves.
+// Full build of replica r (P covering its bricks) if its input is unsorted: bin and sort it
+// from caller order, then build its list.  k_resort skips FULL replicas, so the same kernel as
+// in an incremental rebuild serves (due: a replica that is only due for a rebuild has no next
+// layout yet).
 hipError_t launch_full_build(const Buffers &B, const Launch &P, int cur, int r, int64_t n,
                              hipStream_t s)
 {
-    if (n > 0) tlaunch(k_gbin, blocks_for(n, 256), 256, 0, s, B, P.nslots, cur, r);
-    tlaunch(k_gsort, brick_grid(P.nb_launch), P.block, sort_bytes(P), s, B, P, cur);
-    launch_nlist(B, P, cur, s);
+    Launch Q = P;
+    Q.due = FLAG_FULL;
+    if (n > 0) tlaunch(k_gbin, blocks_for(n, 256), 256, 0, s, B, Q.nslots, cur, r);
+    tlaunch(k_gsort, brick_grid(Q.nb_launch), Q.block, sort_bytes(Q), s, B, Q, cur);
+    launch_nlist(B, Q, cur, s);
+    tlaunch(k_full_done, 1, 64, 0, s, B, r, 1);
     return hipGetLastError();
 }
 
@@ -4231,11 +4234,11 @@ hipError_t launch_full_build_all(const Buffers &B, const Launch &P, int cur, hip
     Q.b_lo = 0;
     Q.nb_launch = P.nbrick_tot;
     Q.list = -1;
-    Q.due = FLAG_FULL;  // a replica that is only due for a rebuild has no next layout yet
+    Q.due = FLAG_FULL;
     tlaunch(k_gbin_all, P.nbrick_tot, P.bcap_max <= 128 ? VBC_WAVE : 256, 0, s, B, cur);
     tlaunch(k_gsort, brick_grid(Q.nb_launch), Q.block, sort_bytes(Q), s, B, Q, cur);
     launch_nlist(B, Q, cur, s);
-    tlaunch(k_full_done, blocks_for(P.nrep, 256), 256, 0, s, B, P.nrep);
+    tlaunch(k_full_done, blocks_for(P.nrep, 256), 256, 0, s, B, 0, P.nrep);
     return hipGetLastError();
 }
 

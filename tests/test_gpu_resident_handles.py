@@ -1,5 +1,5 @@
 """Handles whose steps run in one workgroup per replica, used in other ways than step after step:
-replicas that retire and enter."""
+replicas that retire and enter, analyses and steps captured into graphs of the caller's."""
 import numpy as np
 import pytest
 
@@ -108,3 +108,96 @@ def test_a_replica_too_large_takes_the_set_to_the_bricks(precision, between):
             _close_to_oracle(_state(s, 1, 1100), 1100, 13, 82, 20, precision)
         elif r != 2:
             _close_to_oracle(_state(s, r, n), n, r, r + 5, 40, precision)
+
+
+def _analysis(s):
+    z, pen, sums = s.observables()
+    label, stats, hist = s.clusters(hist_len=16)
+    F, e, UW = s.force()
+    return z, pen, sums, label, stats, hist, F, e, UW
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_captured_analysis_replays_after_steps(precision):
+    """Analyses and forces captured while the replicas stand in their brick layout, replayed after
+    steps that took them out of it: the results and the further trajectory of a set that ran the
+    same calls without a graph."""
+    from paper_2609_07842_amd import vbc
+    print(f"[resident captured analysis] {precision}", flush=True)
+    s, ref = _set(vbc, SIZES, precision), _set(vbc, SIZES, precision)
+    for h in (s, ref):
+        h.step(10, **INTEG)
+        _analysis(h)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = _analysis(s)
+    for k in range(4):
+        for h in (s, ref):
+            h.step(15, **INTEG)
+        g.replay()
+        torch.cuda.synchronize()
+        want = _analysis(ref)
+        assert all(torch.equal(a, b) for a, b in zip(out, want)), k
+        if k == 1:  # and an eager one between two replays
+            assert all(torch.equal(a, b) for a, b in zip(_analysis(s), want))
+        assert all(torch.equal(a, b) for a, b in zip(s.get_state(), ref.get_state())), k
+    s.check()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_captured_steps_replay_between_analyses(precision):
+    """Steps captured into a graph, replayed with reads, analyses, list builds and eager steps in
+    between: the results of a set that ran the same calls without a graph.  Capturing itself
+    changes nothing.  Then a replica admitted since is stepped by the same graph."""
+    from paper_2609_07842_amd import vbc
+    print(f"[resident captured steps] {precision}", flush=True)
+    s, ref = _set(vbc, SIZES, precision), _set(vbc, SIZES, precision)
+    for h in (s, ref):
+        h.step(10, **INTEG)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        s.step(12, **INTEG)
+    same = lambda a, b: all(torch.equal(p, q) for p, q in zip(a, b))
+    assert same(s.get_state(), ref.get_state())
+    assert same(_analysis(s), _analysis(ref))
+    for k in range(5):
+        g.replay()
+        ref.step(12, **INTEG)
+        torch.cuda.synchronize()
+        if k != 2:
+            assert same(_analysis(s), _analysis(ref)), k
+        if k == 3:
+            s.build_nlist()
+            ref.build_nlist()
+        if k == 4:
+            s.step(3, **INTEG)
+            ref.step(3, **INTEG)
+        assert same(s.get_state(), ref.get_state()), k
+    s.check()
+    for h in (s, ref):
+        for r in (0, 1):
+            vbc.Pool.retire(h, r)
+        assert vbc.Pool.admit(h, vbc.replica(1024, L, PARAMS, seed=9), *_inputs(1024, 12)) == 0
+    g.replay()
+    ref.step(12, **INTEG)
+    torch.cuda.synchronize()
+    for r, n in [(0, 1024), (3, SIZES[3]), (7, SIZES[7])]:
+        a, b = _state(s, r, n), _state(ref, r, n)
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), r
+    # a replica too large for the route: the set goes on by bricks, from where the graph left it
+    for h in (s, ref):
+        vbc.Pool.retire(h, 2)
+        vbc.Pool.retire(h, 3)
+    g.replay()
+    ref.step(12, **INTEG)
+    x, v = _inputs(1100, 13)
+    for h in (s, ref):
+        vbc.Pool.retire(h, 0)
+        vbc.Pool.admit(h, vbc.replica(1100, L, PARAMS, seed=77), x, v)
+        h.step(16, **INTEG)
+        h.check()
+    for r, n in [(0, 1100), (4, SIZES[4]), (7, SIZES[7])]:
+        a, b = _state(s, r, n), _state(ref, r, n)
+        assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), r
