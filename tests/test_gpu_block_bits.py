@@ -1,0 +1,65 @@
+"""Results that do not depend on the workgroup size, hence not on what else a pool holds (fuller
+replicas raise its automatic workgroup size): bit for bit, at valencies with few and many
+particles per brick in a switching window."""
+import numpy as np
+import pytest
+
+from paper_2609_07842_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+INTEG = dict(integrator="langevin", dt=0.005, kT=1.0, gamma=0.1, seed=5)
+OPTS = dict(k_max=96, stage_cap=2624)
+
+
+def _state(n, rho, k):
+    return W.uniform_positions(n, W.box_length(n, rho), 30 + k), W.maxwell_boltzmann(n, 1.0, 60 + k)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("f", [2.0, 3.0, 4.0])
+def test_counts_in_a_pool_equal_those_alone(f, precision):
+    """A request of 290 particles per brick alone and beside one of 530, which widens the
+    workgroup: its counts and trajectory.  (Lists of more than sixteen entries: a recount of
+    fewer adds the same terms in the same order whatever its lanes.)"""
+    from paper_2609_07842_amd import vbc
+    print(f"[pool counts] f {f} {precision}", flush=True)
+    reqs = [(6000, 0.3), (6000, 0.5)]
+    descs = [vbc.replica(n, W.box_length(n, r), W.vbc_params(E_a=4.0, f=f), seed=n) for n, r in reqs]
+    fps = [vbc.footprint(d, precision, brick=4, **OPTS) for d in descs]
+    caps = dict(max_replicas=2, max_types=1, max_particles=sum(n for n, _ in reqs),
+                max_slots=sum(q["slots"] for q in fps), max_bricks=sum(q["bricks"] for q in fps),
+                max_cells=sum(q["cells"] for q in fps), max_bcap=max(q["bcap"] for q in fps), chains=False)
+    got, blocks = [], []
+    for mix in (False, True):
+        pool = vbc.Pool(caps, precision=precision, brick=4, **OPTS)
+        r = pool.admit(descs[0], *_state(*reqs[0], 0))
+        if mix:
+            pool.admit(descs[1], *_state(*reqs[1], 1))
+        blocks.append(pool.options()["block"])
+        off = pool.info(r)[1]
+        out = []
+        for _ in range(3):
+            out.append(pool.count().cpu().numpy()[off:off + 6000].copy())
+            pool.step(20, **INTEG)
+            out += [t.cpu().numpy().copy() for t in pool.get_state(r)]
+        pool.check()
+        got.append(out)
+    assert blocks[0] < 512 < blocks[1]
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("f", [2.0, 4.0])
+def test_counts_do_not_depend_on_the_workgroup(f):
+    from paper_2609_07842_amd import vbc
+    n, rho = 6000, 0.3
+    s = vbc.System(vbc.replica(n, W.box_length(n, rho), W.vbc_params(E_a=4.0, f=f)), precision="fp32", block=64)
+    s.set_state(*_state(n, rho, 3))
+    out = []
+    for block in (64, 128, 256, 320, 512, 1024):
+        s.tune_set(block=block)
+        out.append(s.count().cpu().numpy().copy())
+    assert all(np.array_equal(a, out[0]) for a in out)
