@@ -352,6 +352,7 @@ vbc_status plan_replica(const vbc_replica_desc &d, int brick_target, double rho_
     out.rho_cell = per_cell;
     out.k_mean = (double)d.n / vol * 4.18879020478639 * rl * rl * rl;
     out.k_max_auto = k_max_for(out.k_mean);
+    R.recount_round = out.k_mean >= 2 * CHUNK ? 512 : out.k_mean >= CHUNK ? 256 : 128;
     out.stage_cap_auto = stage_cap_for(out.rho_cell, out.nh);
     if (rho_max > 0.0) {
         // hold local densities up to rho_max (clustering, phase separation) anywhere

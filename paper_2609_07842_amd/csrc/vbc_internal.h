@@ -63,6 +63,7 @@ struct RepDev {
     int32_t ntypes;
     int32_t chain_len;
     int32_t resident;      // time steps run in one workgroup that keeps the replica in LDS
+    int32_t recount_round; // threads whose one round sets the lanes of the FP64 recount
     int32_t excl_span;     // > 0: chain neighbours up to this many beads apart neither count
                            // nor attract each other (list entries carry bit 15)
     uint32_t mask[MAXT];

@@ -1607,7 +1607,6 @@ __device__ __forceinline__ double count_term64(double r2, const PairDev &p)
 // lies within this margin of a switching window (the FP32 count is within about 1e-5 of
 // the exact one), so that every particle whose exact count lies inside a window is listed.
 constexpr double COUNT_MARGIN = 1e-4;
-constexpr int RECOUNT_ROUND = 256;
 
 // Counts in FP64 of the particles the FP32 count pass listed (brick b, its first nw
 // entries of wlst): their switching factor s and dU/dn depend steeply on n (eq. (Psi),
@@ -1883,13 +1882,18 @@ __device__ __forceinline__ void count_brick(const Buffers &B, const Launch &P, i
     if (sizeof(Real) == 4) {
         // the listed entries are in global memory, written by this workgroup before the barrier
         const int nwv = nwin;
-        // as many lanes per listed particle (32, 16 or 8) as one round of 256 threads allows: 32
+        // as many lanes per listed particle (32, 16 or 8) as one round of some threads allows: 32
         // take a list of up to 32 entries in one phase, 16 in two, 8 in four.  The lanes order
-        // the sum, so their number follows the brick's particles alone, not the workgroup: a
-        // count has the same bits at every workgroup size, alone and in a pool
-        if (nwv > 0 && nwv <= RECOUNT_ROUND / 32)
+        // the sum, so their number follows the brick's particles and the replica alone, not the
+        // workgroup: a count has the same bits at every workgroup size, alone and in a pool.
+        // Longer lists are worth more lanes and a further round of a small workgroup (us for ten
+        // steps and a frame: melt of 250,000, lists of 49, 1035 at a round of 256 and 1021 at
+        // 512; dilute 10,000, lists of 3, 246 at 256 and 254 at 512; twenty tracked sets of 4000
+        // alike 784 at 256 and 795 at 512, and 778 at the 128 threads that they have)
+        const int round = R.recount_round;
+        if (nwv > 0 && nwv * 32 <= round)
             recount_window<Real, MULTI, 32, 1>(B, P, R, b, S.total, S.base, nwv, X, n_out);
-        else if (nwv > 0 && nwv <= RECOUNT_ROUND / 16)
+        else if (nwv > 0 && nwv * 16 <= round)
             recount_window<Real, MULTI, 16, 1>(B, P, R, b, S.total, S.base, nwv, X, n_out);
         else if (nwv > 0)
             recount_window<Real, MULTI, CHUNK, 1>(B, P, R, b, S.total, S.base, nwv, X, n_out);
