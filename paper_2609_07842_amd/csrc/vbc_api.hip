@@ -1225,7 +1225,8 @@ vbc_status vbc_admit(vbc_handle h, const vbc_replica_desc *d, const double *d_x,
         if (st != VBC_OK) return st;
     }
     // the first replicas of a pool set its workgroup sizes (they never shrink, so a stream of
-    // requests recaptures the step graphs once or twice); results do not depend on them
+    // requests recaptures the step graphs once or twice); results do not depend on them: every
+    // sum has an order that the workgroup's size does not change
     Launch Q = h->P;
     if (h->auto_block) Q.block = std::max(Q.block, block_for(rp.own_mean));
     Q.own_mean = std::max(Q.own_mean, rp.own_mean);

@@ -2195,7 +2195,7 @@ __device__ __forceinline__ void force_brick(const Buffers &B, const Launch &P, i
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     bool bad = false, mv = false;
     const int ls = SPLIT ? P.split : 0, sub = SPLIT ? threadIdx.x & ((1 << ls) - 1) : 0;
-    for (int t = threadIdx.x >> ls; t < S.n_own; t += blockDim.x >> ls) {
+    auto particle = [&](int t) __attribute__((always_inline)) {
         int64_t i = S.base + t;
         R4 pi = spos[t];
         const R2 sai = MULTI ? ssa[t] : R2{pi.w, scA[t]};
@@ -2284,7 +2284,7 @@ __device__ __forceinline__ void force_brick(const Buffers &B, const Launch &P, i
                 fz = add_group(fz, cz, ls);
                 cx = cy = cz = Real(0);
             });
-            if (sub) continue;
+            if (sub) return;
         } else {
             for_each_neighbour(B.nl, S_, i, AHEAD && t == (int)threadIdx.x ? head : list_head(B, i), entry, [&]() {
                 if (CHUNKED) {
@@ -2361,29 +2361,45 @@ __device__ __forceinline__ void force_brick(const Buffers &B, const Launch &P, i
                 if (d2 > disp2) mv = true;
             }
         }
-    }
-    if (bad) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_NONFINITE);
-    if (mv) moved = 1;
-    if (THERMO) {
-        int wv = threadIdx.x / VBC_WAVE, ln = threadIdx.x % VBC_WAVE;
-        const double v = wave_sum8(acc);
-        if ((ln & 7) == 0) red[ln >> 3][wv] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && moved) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_REBUILD);
-    if (THERMO && threadIdx.x < 8) {
-        int nw = blockDim.x / VBC_WAVE;
+    };
+    if constexpr (THERMO) {
+        // the sums of 64 consecutive particles (a wave's) are added in their order, round after
+        // round of the workgroup: the same bits at every workgroup size.  The first round, with
+        // which nearly every brick ends, stands by itself (an evaluation of 200,000 particles in
+        // FP64: 175 us, 179 with it in the loop, 176 before)
+        const int n_own = __builtin_amdgcn_readfirstlane(S.n_own);  // a scalar: barriers below
+        const int wv = threadIdx.x / VBC_WAVE, ln = threadIdx.x % VBC_WAVE, nw = blockDim.x / VBC_WAVE;
         double s = 0.0;
-        if (threadIdx.x == 1) {
-            // W = W_xx + W_yy + W_zz, summed per wave in the same fixed order
-            for (int w = 0; w < nw; ++w) s += (red[2][w] + red[3][w]) + red[4][w];
-        } else {
-            for (int w = 0; w < nw; ++w) s += red[threadIdx.x][w];
+        auto add = [&]() __attribute__((always_inline)) {
+            const double v = wave_sum8(acc);
+            if ((ln & 7) == 0) red[ln >> 3][wv] = v;
+            if (mv) moved = 1;
+            __syncthreads();
+            if (threadIdx.x == 1) {
+                // W = W_xx + W_yy + W_zz, summed per wave in the same fixed order
+                for (int w = 0; w < nw; ++w) s += (red[2][w] + red[3][w]) + red[4][w];
+            } else if (threadIdx.x < 8) {
+                for (int w = 0; w < nw; ++w) s += red[threadIdx.x][w];
+            }
+        };
+        if ((int)threadIdx.x < n_own) particle(threadIdx.x);
+        add();
+        for (int t0 = blockDim.x; t0 < n_own; t0 += blockDim.x) {
+            for (int k = 0; k < 8; ++k) acc[k] = 0.0;
+            if (t0 + (int)threadIdx.x < n_own) particle(t0 + threadIdx.x);
+            __syncthreads();  // red was read
+            add();
         }
-        B.part[(size_t)b * 8 + threadIdx.x] = s;
+        if (threadIdx.x < 8) B.part[(size_t)b * 8 + threadIdx.x] = s;
         // a time step's sums: added by the next count pass or the call's closing reduction
         if (st.acc && lb == 0 && threadIdx.x == 0) B.tpend[r] = 1;
+    } else {
+        for (int t = threadIdx.x >> ls; t < S.n_own; t += blockDim.x >> ls) particle(t);
+        if (mv) moved = 1;
+        __syncthreads();
     }
+    if (bad) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_NONFINITE);
+    if (threadIdx.x == 0 && moved) atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_REBUILD);
 }
 
 template <class Real, bool MULTI, bool THERMO, bool ONE, bool SPLIT>

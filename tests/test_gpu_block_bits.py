@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 INTEG = dict(integrator="langevin", dt=0.005, kT=1.0, gamma=0.1, seed=5)
-OPTS = dict(k_max=96, stage_cap=2624)
+OPTS = dict(k_max=96, stage_cap=2720)
 
 
 def _state(n, rho, k):
@@ -63,3 +63,36 @@ def test_counts_do_not_depend_on_the_workgroup(f):
         s.tune_set(block=block)
         out.append(s.count().cpu().numpy().copy())
     assert all(np.array_equal(a, out[0]) for a in out)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_energies_in_a_pool_equal_those_alone(precision):
+    """Per-system energy and virial, of an evaluation and summed over steps, of a request whose
+    particles fill half of its box: its bricks of up to 600 particles take two rounds of the
+    workgroup that its mean density asks for, one of the wider one it gets beside the other."""
+    from paper_2609_07842_amd import vbc
+    print(f"[pool energies] {precision}", flush=True)
+    reqs = [(6000, 0.3), (6000, 0.5)]
+    descs = [vbc.replica(n, W.box_length(n, r), W.vbc_params(E_a=4.0, f=4.0), seed=n) for n, r in reqs]
+    fps = [vbc.footprint(d, precision, brick=4, rho_max=0.7, **OPTS) for d in descs]
+    caps = dict(max_replicas=2, max_types=1, max_particles=sum(n for n, _ in reqs),
+                max_slots=sum(q["slots"] for q in fps), max_bricks=sum(q["bricks"] for q in fps),
+                max_cells=sum(q["cells"] for q in fps), max_bcap=max(q["bcap"] for q in fps), chains=False)
+    x, v = _state(*reqs[0], 0)
+    x[:, 0] *= 0.5
+    got, blocks = [], []
+    for mix in (False, True):
+        pool = vbc.Pool(caps, precision=precision, brick=4, rho_max=0.7, **OPTS)
+        r = pool.admit(descs[0], x, v)
+        if mix:
+            pool.admit(descs[1], *_state(*reqs[1], 1))
+        blocks.append(pool.options()["block"])
+        pool.thermo(True)
+        UW = pool.force()[2][r].cpu().numpy().copy()
+        pool.step(20, **INTEG)
+        th = pool.thermo_read()[r]
+        pool.check()
+        got.append([UW, th["last"], th["sum"]])
+    assert blocks[0] < 512 < blocks[1]
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
