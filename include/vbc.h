@@ -181,7 +181,8 @@ vbc_status vbc_force(vbc_handle h, double *d_F, double *d_e, double *d_UW, hipSt
  * so that the others are not touched.  Calls of up to 64 steps run as one captured HIP
  * graph launch (captured once per step count, integrator and buffer parity); longer
  * calls replay graphs of 8 steps.  A set of eight or more small replicas (vbc_create; one type,
- * at most 1024 particles each) may run as one launch of one workgroup per replica instead,
+ * at most 1024 particles each) may run as one launch of one workgroup per replica for up to
+ * 1024 steps instead,
  * whose trajectories differ from the others' in the rounding of sums only; its passes are not
  * told apart by vbc_profile.  A replica admitted into such a set steps the same way; one that
  * cannot (more than 1024 particles) takes the whole set to the other passes from then on. */

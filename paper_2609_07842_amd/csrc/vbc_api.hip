@@ -111,6 +111,9 @@ struct vbc_handle_s {
 static constexpr int GRAPH_STEPS = 8;
 static constexpr int CALL_GRAPH_MAX = 64;
 static constexpr size_t GRAPH_CACHE = 16;
+// Steps of one launch of a resident set: a kernel holds its compute units until it ends, and a
+// launch costs some 9 us, of steps of 10 to 65 us each.
+static constexpr int RES_STEPS = 1024;
 
 // Forget the captured step graphs (the launches changed): the next call captures its own.
 static void drop_graphs(vbc_handle h)
@@ -1473,9 +1476,10 @@ vbc_status vbc_step(vbc_handle h, int32_t nsteps, const vbc_integrator *it, hipS
         const bool cap = capturing(s);
         const int max_n = cap ? RES_MAX_N : h->resident;
         // with time stamps, each step is a launch with its stamp
-        const int each = h->stamps ? 1 : nsteps;
+        const int each = h->stamps ? 1 : RES_STEPS;
         for (int k = 0; k < nsteps; k += each) {
-            VBC_TRY(h, launch_resident(h->B, h->P, h->cur, each, k, max_n, sr, s), "resident steps");
+            VBC_TRY(h, launch_resident(h->B, h->P, h->cur, std::min(each, nsteps - k), k, max_n, sr, s),
+                    "resident steps");
             if (h->stamps) VBC_TRY(h, launch_stamp(h->B, s), "stamp");
         }
         if (cap) h->res_replayed = true;

@@ -201,3 +201,34 @@ def test_captured_steps_replay_between_analyses(precision):
     for r, n in [(0, 1100), (4, SIZES[4]), (7, SIZES[7])]:
         a, b = _state(s, r, n), _state(ref, r, n)
         assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1]), r
+
+
+@pytest.mark.parametrize("nsteps,launches", [(1, 1), (1024, 1), (1025, 2), (2500, 3)])
+def test_long_calls_are_several_launches(nsteps, launches):
+    """A call of many steps is a launch per 1024 (counted as nodes of a captured call), with the
+    bits, sums and samples of short calls."""
+    import ctypes as C
+
+    from paper_2609_07842_amd import vbc
+    sizes, out = [60, 64, 40, 127, 30, 50, 20, 10], []
+    for split in ([nsteps], [500] * (nsteps // 500) + [nsteps % 500]):
+        s = _set(vbc, sizes, "fp32")
+        s.thermo(True)
+        for n in split:
+            s.step(n, **INTEG)
+        th = s.thermo_read()
+        s.check()
+        out.append([t.cpu().numpy() for t in s.get_state()] + [np.concatenate([q["last"], q["sum"]]) for q in th])
+        assert all(q["steps"] == nsteps for q in th)
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
+    hip, graph, nodes = vbc.lib(), C.c_void_p(), C.c_size_t(0)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        h = C.c_void_p(stream.cuda_stream)
+        torch.cuda.synchronize()
+        assert hip.hipStreamBeginCapture(h, 1) == 0  # this thread's calls only
+        s.step(nsteps, **INTEG)
+        assert hip.hipStreamEndCapture(h, C.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, C.byref(nodes)) == 0
+    assert hip.hipGraphDestroy(graph) == 0
+    assert nodes.value == launches
