@@ -3362,7 +3362,11 @@ __global__ void __launch_bounds__(DENSE_BLOCK) k_bond_track_dense(Buffers B, Lau
 // FP32 pair arithmetic: positions are 64-bit fractions of the box, and a distance starts from
 // the wrapped integer difference of their upper halves: the minimum image without a test, and
 // an error of L 2^-32 where a staged FP32 coordinate has up to 5e-7.  The FP64 recount of
-// particles near a switching window takes the whole 64 bits.
+// particles near a switching window takes the whole 64 bits, and so does dU/dn, whose
+// distances are rounded once (a box of 500: rms force error of window particles 3.6e-7 with
+// upper halves, 3.3e-7 so, 7.9e-7 by bricks; same time).  The list takes every pair below the list radius: its FP32 test
+// allows a millionth more than that, so that it may hold a pair that the bricks' lists do not,
+// beyond every cutoff.
 //
 // A thread owns the particle of its index: position, velocity, force and reference position
 // stay in registers through a call, and only the list is read from memory.
@@ -3437,18 +3441,30 @@ template <> struct ResLds<float> {
         sub(p, v.x, v.y, v.z, H, d);
         return v.w;
     }
-    // squared distance in FP64 from the whole fractions
-    __device__ double r2_64(int i, int j, const double L[3]) const
+    // d = x_i - x_j in FP64 from the whole fractions, minimum image
+    __device__ void diff64(int i, int j, const double L[3], double d[3]) const
     {
         const uint32_t hi[3] = {(uint32_t)xy[i].x, (uint32_t)xy[i].y, (uint32_t)zs[i].x};
         const uint32_t hj[3] = {(uint32_t)xy[j].x, (uint32_t)xy[j].y, (uint32_t)zs[j].x};
-        double d[3];
         for (int a = 0; a < 3; ++a) {
             const uint64_t u = (((uint64_t)hi[a] << 32) | lo[a][i]) - (((uint64_t)hj[a] << 32) | lo[a][j]);
             const double f = (double)(int)(uint32_t)(u >> 32) + (double)(uint32_t)u * 0x1p-32;
             d[a] = f * (L[a] * 0x1p-32);
         }
+    }
+    __device__ double r2_64(int i, int j, const double L[3]) const
+    {
+        double d[3];
+        diff64(i, j, L, d);
         return (d[0] * d[0] + d[1] * d[1]) + d[2] * d[2];
+    }
+    // the distance rounded once, with the neighbour's s, for the window particle i at p
+    __device__ void diff_w(int i, const Pos &, int j, const Scale &, const double L[3], float d[3], float &s) const
+    {
+        double q[3];
+        diff64(i, j, L, q);
+        for (int a = 0; a < 3; ++a) d[a] = (float)q[a];
+        s = __int_as_float(zs[j].y);
     }
     __device__ void set_s(int k, float v) { zs[k].y = __float_as_int(v); }
     __device__ float get_s(int k) const { return __int_as_float(zs[k].y); }
@@ -3497,6 +3513,10 @@ template <> struct ResLds<double> {
     {
         diff(p, j, H, d);
         sj = s[j];
+    }
+    __device__ void diff_w(int, const Pos &p, int j, const Scale &H, const double[3], double d[3], double &sj) const
+    {
+        diff_s(p, j, H, d, sj);
     }
     __device__ int diff_sorted(const Pos &p, int q, const Scale &H, double d[3]) const
     {
@@ -3849,7 +3869,7 @@ __global__ void __launch_bounds__(RES_MAX_N) k_resident(Buffers B, Launch P, int
                     if (c * CHUNK + e < nj) {
                         const int j = ((const uint16_t *)(B.nl + (size_t)c * S_ + base + kw))[e];
                         Real d[3], sj;
-                        T.diff_s(pw, j, H, d, sj);
+                        T.diff_w(kw, pw, j, H, L, d, sj);
                         const Real r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
                         const Real uu = (sqrt_r(r2) - p0.m) * p0.inv_w;
                         const Real qq = Real(1) - uu * uu;

@@ -232,3 +232,33 @@ def test_long_calls_are_several_launches(nsteps, launches):
     assert hip.hipGraphGetNodes(graph, None, C.byref(nodes)) == 0
     assert hip.hipGraphDestroy(graph) == 0
     assert nodes.value == launches
+
+
+def test_precision_in_a_large_box():
+    """FP32 pair arithmetic of a step in a box of 500 (positions as fractions of the box): no
+    further from the oracle than the brick passes, over the particles in a switching window."""
+    from paper_2609_07842_amd import vbc
+    n, box, rho = 1000, 500.0, 0.3
+    p = W.vbc_params(E_a=5.0, f=4.0)
+    x = W.uniform_positions(n, W.box_length(n, rho), 3) + 311.0
+    v = np.zeros((n, 3))
+    win = oracle.evaluate(x, box, p)["n"]
+    win = (win > 4.0) & (win < 5.0)
+    assert win.sum() > 100
+    ref = oracle.run(x, v, box, p, 1, kind=oracle.NVE, dt=0.005)["v"]
+    err = {}
+    for k, m in ((8, 1), (1, 1)):  # a set that steps in one workgroup per replica; bricks
+        small = [vbc.replica(10, 24.0, p) for _ in range(k - 1)]
+        s = vbc.System([vbc.replica(n, box, p)] + small, precision="fp32", brick=6, k_max=96, stage_cap=4096,
+                       rho_max=0.0 if k == 8 else 0.4)
+        xs = np.concatenate([x] + [W.uniform_positions(10, 24.0, j) for j in range(k - 1)])
+        s.set_state(xs, np.zeros_like(xs))
+        s.profile(True, 8)
+        s.step(1, integrator="nve", dt=0.005)
+        assert (s.profile_read()["force"][1] == 0) == (k == 8)
+        s.check()
+        got = s.get_state()[1].cpu().numpy()[:n]
+        err[k] = np.sqrt(((got - ref)[win] ** 2).mean() / (ref[win] ** 2).mean())
+        print(f"[large box] {k} replicas: rms error {err[k]:.2e}", flush=True)
+        s.close()
+    assert err[8] <= err[1]
