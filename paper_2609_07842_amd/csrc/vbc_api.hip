@@ -1321,9 +1321,9 @@ vbc_status vbc_tune_set(vbc_handle h, const vbc_options *t)
             split_shape(h->P);
             part_shape(h->P);
             h->opt.block = t->block;
-            h->auto_block = false;
             drop_graphs(h);
         }
+        h->auto_block = false;
     }
     return VBC_OK;
 }

@@ -96,3 +96,21 @@ def test_energies_in_a_pool_equal_those_alone(precision):
     assert blocks[0] < 512 < blocks[1]
     for a, b in zip(*got):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("block", [256, 128])
+def test_a_set_block_stays(block):
+    """A pool's workgroup size, once set, does not follow the admitted replicas, also when it was
+    set to the size that the pool had (256)."""
+    from paper_2609_07842_amd import vbc
+    d = vbc.replica(6000, W.box_length(6000, 0.5), W.vbc_params(E_a=4.0, f=4.0))
+    fp = vbc.footprint(d, "fp32", brick=4, **OPTS)
+    caps = dict(max_replicas=1, max_types=1, max_particles=6000, max_slots=fp["slots"], max_bricks=fp["bricks"],
+                max_cells=fp["cells"], max_bcap=fp["bcap"], chains=False)
+    pool = vbc.Pool(caps, precision="fp32", brick=4, **OPTS)
+    assert pool.options()["block"] == 256
+    pool.tune_set(block=block)
+    pool.admit(d, *_state(6000, 0.5, 1))
+    assert pool.options()["block"] == block
+    pool.step(2, **INTEG)
+    pool.check()
