@@ -1240,8 +1240,9 @@ vbc_status vbc_admit(vbc_handle h, const vbc_replica_desc *d, const double *d_x,
     const bool resized = Q.block != h->P.block || Q.list_block != h->P.list_block || Q.list_win != h->P.list_win ||
                          Q.cap_usual != h->P.cap_usual;
     h->P = Q;
-    if (resized) {
-        h->opt.block = Q.block;
+    h->opt.block = Q.block;
+    // the graphs of a single-replica handle hold its descriptor
+    if (resized || Q.one) {
         for (auto &g : h->graphs) h->retired.push_back(g.exec);  // other replicas' steps may be running
         h->graphs.clear();
     }

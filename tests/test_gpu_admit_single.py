@@ -1,0 +1,37 @@
+"""A handle of one replica whose replica retires and is followed by another: the captured steps,
+which take the descriptor as a kernel argument, are those of the new one."""
+import numpy as np
+import pytest
+
+from paper_2609_07842_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+N, RHO = 2000, 0.3
+INTEG = dict(integrator="langevin", dt=0.005, kT=1.0, gamma=0.1, seed=5)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("nsteps", [20, 90])
+def test_admitted_replica_runs_with_its_own_parameters(nsteps, precision):
+    from paper_2609_07842_amd import vbc
+    L = W.box_length(N, RHO)
+    print(f"[admit single] {nsteps} {precision}", flush=True)
+    states = [(W.uniform_positions(N, L, 30 + k), W.maxwell_boltzmann(N, 1.0, 60 + k)) for k in range(2)]
+    reps = [vbc.replica(N, L, W.vbc_params(E_a=E, f=f), seed=sd) for E, f, sd in [(5.0, 2.0, 1), (2.0, 5.0, 7)]]
+    s = vbc.System(reps[0], precision=precision)
+    s._keep_admit = {}
+    s.set_state(*states[0])
+    for _ in range(2):
+        s.step(nsteps, **INTEG)
+    vbc.Pool.retire(s, 0)
+    assert vbc.Pool.admit(s, reps[1], *states[1]) == 0
+    fresh = vbc.System(reps[1], precision=precision)
+    fresh.set_state(*states[1])
+    for h in (s, fresh):
+        h.step(nsteps, **INTEG)
+        h.check()
+    for a, b in zip(s.get_state(), fresh.get_state()):
+        assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
