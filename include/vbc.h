@@ -327,8 +327,10 @@ vbc_status vbc_profile_read(vbc_handle h, hipStream_t s, double *ms /* [VBC_NK] 
  * A pool is a handle of fixed capacity into which replicas are admitted and from which
  * they retire while others keep running; every launch covers the whole capacity (bricks
  * of free or retired replicas exit at once), so the captured step graphs stay valid as the
- * replica set changes.  The use case is the paper's own way of working: its results are
- * sweeps over many independent state points (valency, temperature, density, well depth;
+ * replica set changes, unless an admitted replica is fuller or its lists longer than all
+ * before and widens an automatic workgroup: then the next call captures its graph anew.  The
+ * use case is the paper's own way of working: its results are sweeps over many independent
+ * state points (valency, temperature, density, well depth;
  * Sections 3 to 5), each a separate simulation. */
 
 /* Fixed capacity of a pool. */

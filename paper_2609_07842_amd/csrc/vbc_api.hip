@@ -385,12 +385,17 @@ bool partial_mask(const RepDev &R)
 
 // Whether a fixed set of replicas steps with one workgroup per replica: sets of at least eight,
 // all of which can, where the slowest replica's workgroup is estimated faster than the set's
-// bricks.  (A set and a single replica then differ in the rounding of FP32 sums only; smaller
-// sets keep the bits that each replica has alone.)  Measured on sets of replicas with one
-// common size: a resident step takes about 9 us + 0.8 us per 1000 particles times (mean list
-// length + 8) (9.8 at 2,700, 25 at 21,800, 43 at 43,600 of them; 1.3 us per 1000 in FP64), a
-// step of bricks 25 us + 0.025 us per brick (20 replicas of 4000 at density 0.05, 2500
-// bricks: 130 us; 32 of 1000 in bricks of 2^3 cells, 6912 bricks: 190 us).
+// bricks.  Measured on sets of replicas with one common size: a resident step takes about 9 us
+// + 0.8 us per 1000 particles times (mean list length + 8) (9.8 at 2,700, 25 at 21,800, 43 at
+// 43,600 of them; 1.3 us per 1000 in FP64), a step of bricks 25 us + 0.025 us per brick (20
+// replicas of 4000 at density 0.05, 2500 bricks: 130 us; 32 of 1000 in bricks of 2^3 cells,
+// 6912 bricks: 190 us).  Lists and bricks are those of a uniform gas; both routes slow down when
+// replicas collapse, and the order stays (us a step by the one and the other after 20,000 steps
+// or more at density 0.05: 8 of 1000 33.7 and 49.8 in bricks of 4^3 cells, 33.2 and 63.9 in 2^3,
+// 79 and 217 with lists of 78; 8 of 500 25.7 and 53.0; 32 of 1000 33.7 and 148; FP64, 8 of 1000
+// 55 and 94).  Eight is no line of speed (sets of 2, 4 and 7 of 1000 at 0.05: 13.7, 14.0, 14.3
+// against 23.8, 27.0, 31.2): a resident set and a single replica differ in the rounding of sums,
+// and a set below it keeps the bits that its replicas have alone.
 constexpr int RES_MIN_SET = 8;
 bool resident_set(const std::vector<RepPlan> &plans, int precision)
 {

@@ -95,13 +95,15 @@ struct Buffers {
                              // halo are one contiguous run), double-buffered by step parity
     double *v;               // velocities SoA [3][nslots]
     double *Fst;             // forces kept between calls SoA [3][nslots]
-    double *xref;            // resident replicas: positions at the last build SoA [3][nslots];
-                             // the others have those in xs, and this is scratch
+    double *xref;            // [3][nslots] positions at the last list build of a replica stepped
+                             // in one workgroup (k_resident), kept through its brick layouts;
+                             // of the others, which have those in xs, scratch between builds
     int32_t *tag;            // [nslots]
     int32_t *type;           // [nslots]
     uint8_t *lcell;          // [nslots] cell of the particle inside its brick
-    double *xs;              // next layout: positions [nslots][3]
-    double *vs;              // next layout: velocities
+    double *xs;              // next layout: positions [nslots][3]; between list builds those of
+                             // the last one, and scratch of a replica that has them in xref
+    double *vs;              // next layout: velocities [3][nslots]; scratch between list builds
     int32_t *tags, *types;   // next layout
     uint8_t *lcells;         // next layout
     int32_t *src;            // [nslots] full build: members of each brick (dense index)

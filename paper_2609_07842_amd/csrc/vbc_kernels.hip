@@ -209,8 +209,6 @@ __device__ __forceinline__ double wave_sum8(const double (&a)[8])
     return u;
 }
 
-// Exclusive scan of a[0..n) in place by the first wave; returns the total (valid in the
-// first wave).  Call from all threads of the block between barriers.
 // Sum of v over this and the lower lanes of the wave: shifts within rows of sixteen, then the
 // last lane of each row and of the lower half handed up, all in the vector unit (the same by
 // lane shuffles through LDS took 1.2 us for 216 cells).
@@ -225,7 +223,7 @@ __device__ __forceinline__ int wave_inclusive_sum(int v)
     return v;
 }
 
-// Exclusive scan of a[0..n) by one whole wave; the total.
+// Exclusive scan of a[0..n) in place by one whole wave; the total.
 __device__ __forceinline__ int wave_exclusive_scan(int *a, int n)
 {
     const int lane = threadIdx.x % VBC_WAVE;
@@ -240,6 +238,8 @@ __device__ __forceinline__ int wave_exclusive_scan(int *a, int n)
     return carry;
 }
 
+// The same by the first wave, which gets the total.  Call from all threads of the block between
+// barriers.
 __device__ __forceinline__ int wave0_exclusive_scan(int *a, int n)
 {
     return threadIdx.x < VBC_WAVE ? wave_exclusive_scan(a, n) : 0;
@@ -322,9 +322,6 @@ __device__ __forceinline__ void brick_geometry(const RepDev &R, int lb, StageHdr
     S.base = R.p_off + (int64_t)lb * R.bcap;
 }
 
-// Lay out the staging of brick b (local index lb) of replica R from a set of cell tables:
-// own particles first (the brick's slot range), then every halo cell of the (e+2)^3 grid
-// in x-fastest order.  All threads of the block call this.
 // The cells of a brick's halo grid: first slot, count, image shift, staged offset of the own
 // ones (-1: halo) and the halo counts; all: every cell's count, if asked.
 __device__ __forceinline__ void stage_cells(const RepDev &R, const StageHdr &S, const int32_t *cell_rank,
@@ -354,6 +351,9 @@ __device__ __forceinline__ void stage_cells(const RepDev &R, const StageHdr &S, 
     }
 }
 
+// Lay out the staging of brick b (local index lb) of replica R from a set of cell tables:
+// own particles first (the brick's slot range), then every halo cell of the (e+2)^3 grid
+// in x-fastest order.  All threads of the block call this.
 __device__ void stage_tables(const RepDev &R, int b, int lb, const int32_t *brick_rank0,
                              const int32_t *cell_rank, const int32_t *cstart,
                              const int32_t *ccnt, const int32_t *bcnt, StageHdr &S,
@@ -545,9 +545,8 @@ __global__ void k_get_state(Buffers B, int64_t S_, int cur, int r, int64_t out_o
 // The state of one large replica by way of records in caller order.  A particle's six
 // coordinates go to six places far apart in the caller's arrays, a line of memory each; with
 // hundreds of thousands of particles that bounds the read (a million: 83 us for 100 MB).
-// Written as two records of 24 bytes into space that is free between list builds (the next
-// layout's velocities and the scratch beside the reference positions), a third as many lines
-// are touched, and a second pass spreads the records into the arrays in order.
+// Written as two records of 24 bytes into space that a brick replica leaves free between list
+// builds (xref, and vs, the next layout's velocities), a third as many lines are touched, and a second pass spreads the records into the arrays in order.
 __global__ void k_get_records(Buffers B, int64_t S_, int cur, int r)
 {
     const RepDev &R = B.reps[r];
@@ -1491,12 +1490,10 @@ __device__ __forceinline__ R4 dummy_pos()
 // Pair constants converted to the pair-arithmetic precision.
 template <class Real>
 struct PairR {
-    Real E_r, c_r, inv_rr2, E_a, c_a, m, inv_w, r_l, inv_dw, c_c, rl2, rh2, rc2;
-    Real x1, x2;
+    Real E_r, c_r, inv_rr2, E_a, c_a, m, inv_w, inv_dw, c_c, rc2;
     Real k_r;      // -c_r / r_r^2: V_r'(r)/r = c_r + k_r r^2 inside the core
     Real nm_w;     // -m / w:  u_a = r / w + nm_w
     Real nrl_dw;   // -r_l / (r_h - r_l):  u_c = r / (r_h - r_l) + nrl_dw
-    int attract;
 };
 
 template <class Real>
@@ -1510,18 +1507,12 @@ __device__ __forceinline__ PairR<Real> pair_r(const PairDev &p, double rc2)
     q.c_a = (Real)p.c_a;
     q.m = (Real)p.m;
     q.inv_w = (Real)p.inv_w;
-    q.r_l = (Real)p.r_l;
     q.inv_dw = (Real)p.inv_dw;
     q.c_c = (Real)p.c_c;
-    q.rl2 = (Real)p.rl2;
-    q.rh2 = (Real)p.rh2;
     q.rc2 = (Real)rc2;
-    q.x1 = (Real)p.x1;
-    q.x2 = (Real)p.x2;
     q.k_r = (Real)(-p.c_r * p.inv_rr2);
     q.nm_w = (Real)(-p.m * p.inv_w);
     q.nrl_dw = (Real)(-p.r_l * p.inv_dw);
-    q.attract = p.attract;
     return q;
 }
 
@@ -1574,14 +1565,14 @@ __device__ __forceinline__ PairM<Real> pair_m(const RepDev &R, int a, int c)
     return q;
 }
 
-// One thread per type pair writes its record (the general path), or thread 0 the constants of
-// the only one.
+// Thread 0 writes the constants of the only type pair.
 template <class Real>
 __device__ __forceinline__ void load_pairs(const RepDev &R, PairR<Real> *pt)
 {
     if (threadIdx.x == 0) pt[0] = pair_r<Real>(R.pair[0], R.rc2);
 }
 
+// One thread per type pair writes its record (the general path).
 template <class Real>
 __device__ __forceinline__ void load_pairs_m(const RepDev &R, PairM<Real> *pm, int tid)
 {
@@ -1962,75 +1953,73 @@ __device__ __forceinline__ void embed_brick(const Buffers &B, const Launch &P, c
         const double xi0 = X[3 * i], xi1 = X[3 * i + 1], xi2 = X[3 * i + 2];
         int nch = (B.nn[i] + CHUNK - 1) / CHUNK;
         double acc = 0.0;
-        {
-            // four chunks at a time in phases (chunk words, staging map, positions, terms)
-            // with no branch between the loads, so that the gathers of all four go out together;
-            // rows past the list and the padding slot read valid memory and are masked.  The
-            // first four rows are read before the list length arrives (rows below nchunk exist
-            // for every slot).
-            constexpr int CP = 4 / EP;  // chunks per phase
-            uint4 qf[CP];
+        // four chunks at a time in phases (chunk words, staging map, positions, terms)
+        // with no branch between the loads, so that the gathers of all four go out together;
+        // rows past the list and the padding slot read valid memory and are masked.  The
+        // first four rows are read before the list length arrives (rows below nchunk exist
+        // for every slot).
+        constexpr int CP = 4 / EP;  // chunks per phase
+        uint4 qf[CP];
 #pragma unroll
-            for (int j = 0; j < CP; ++j) qf[j] = B.nl[(size_t)min(j, P.nchunk - 1) * S_ + i];
-            for (int c0 = 0; c0 < nch; c0 += CP) {
-                int uj[4], sj[4], wj[4];
-                bool vj[4];
-                uint4 qc[CP];
+        for (int j = 0; j < CP; ++j) qf[j] = B.nl[(size_t)min(j, P.nchunk - 1) * S_ + i];
+        for (int c0 = 0; c0 < nch; c0 += CP) {
+            int uj[4], sj[4], wj[4];
+            bool vj[4];
+            uint4 qc[CP];
 #pragma unroll
-                for (int j = 0; j < CP; ++j)
-                    qc[j] = c0 == 0 ? qf[j] : B.nl[(size_t)min(c0 + j, P.nchunk - 1) * S_ + i];
+            for (int j = 0; j < CP; ++j)
+                qc[j] = c0 == 0 ? qf[j] : B.nl[(size_t)min(c0 + j, P.nchunk - 1) * S_ + i];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int jc = j / EP, x = e + LPP * (j % EP);  // chunk, entry
-                    const uint4 q = qc[jc];
-                    const uint32_t wd = (x < 2) ? q.x : (x < 4) ? q.y : (x < 6) ? q.z : q.w;
-                    int u = (int)((wd >> (16 * (x & 1))) & 0xffffu);
-                    bool ok = c0 + jc < nch;
-                    if (MULTI && xr) {
-                        ok = ok && !(u >> 15);  // excluded pair: no attraction between them
-                        u &= 0x7fff;
+            for (int j = 0; j < 4; ++j) {
+                const int jc = j / EP, x = e + LPP * (j % EP);  // chunk, entry
+                const uint4 q = qc[jc];
+                const uint32_t wd = (x < 2) ? q.x : (x < 4) ? q.y : (x < 6) ? q.z : q.w;
+                int u = (int)((wd >> (16 * (x & 1))) & 0xffffu);
+                bool ok = c0 + jc < nch;
+                if (MULTI && xr) {
+                    ok = ok && !(u >> 15);  // excluded pair: no attraction between them
+                    u &= 0x7fff;
+                }
+                vj[j] = ok && u < total;
+                uj[j] = vj[j] ? u : 0;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                sj[j] = sm[uj[j]];
+                wj[j] = wm[uj[j]];
+            }
+            double xj[4][3];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                for (int a = 0; a < 3; ++a) xj[j][a] = X[3 * sj[j] + a];
+            Real sjv[4];
+            int tj[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                sjv[j] = sA[sj[j]].x;
+                tj[j] = MULTI ? B.type[sj[j]] : 0;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                Real dx = (Real)(xi0 - (xj[j][0] + R.L[0] * (double)unpack_w(wj[j], 0)));
+                Real dy = (Real)(xi1 - (xj[j][1] + R.L[1] * (double)unpack_w(wj[j], 1)));
+                Real dz = (Real)(xi2 - (xj[j][2] + R.L[2] * (double)unpack_w(wj[j], 2)));
+                Real r2 = dx * dx + dy * dy + dz * dz;
+                if (MULTI) {
+                    // s'_ij(n_i) in FP64 by the pair's window; no attraction: E_a = 0
+                    const PairM<Real> &q2 = pm[ti * MAXT + tj[j]];
+                    const R4 qg = q2.geo;
+                    const Real uu = fma(sqrt_r(r2), qg.x, qg.y);
+                    const Real qq = fma(-uu, uu, Real(1));
+                    if (vj[j] && qq > Real(0)) {
+                        const double x1 = R.pair[ti * MAXT + tj[j]].x1;
+                        acc += omega_dd64(n_i, x1, x1 + 1.0) *
+                               (double)(omega_win<Real>(sjv[j], q2.core.w) * (-q2.cnt.w * qq * qq));
                     }
-                    vj[j] = ok && u < total;
-                    uj[j] = vj[j] ? u : 0;
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    sj[j] = sm[uj[j]];
-                    wj[j] = wm[uj[j]];
-                }
-                double xj[4][3];
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    for (int a = 0; a < 3; ++a) xj[j][a] = X[3 * sj[j] + a];
-                Real sjv[4];
-                int tj[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    sjv[j] = sA[sj[j]].x;
-                    tj[j] = MULTI ? B.type[sj[j]] : 0;
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    Real dx = (Real)(xi0 - (xj[j][0] + R.L[0] * (double)unpack_w(wj[j], 0)));
-                    Real dy = (Real)(xi1 - (xj[j][1] + R.L[1] * (double)unpack_w(wj[j], 1)));
-                    Real dz = (Real)(xi2 - (xj[j][2] + R.L[2] * (double)unpack_w(wj[j], 2)));
-                    Real r2 = dx * dx + dy * dy + dz * dz;
-                    if (MULTI) {
-                        // s'_ij(n_i) in FP64 by the pair's window; no attraction: E_a = 0
-                        const PairM<Real> &q2 = pm[ti * MAXT + tj[j]];
-                        const R4 qg = q2.geo;
-                        const Real uu = fma(sqrt_r(r2), qg.x, qg.y);
-                        const Real qq = fma(-uu, uu, Real(1));
-                        if (vj[j] && qq > Real(0)) {
-                            const double x1 = R.pair[ti * MAXT + tj[j]].x1;
-                            acc += omega_dd64(n_i, x1, x1 + 1.0) *
-                                   (double)(omega_win<Real>(sjv[j], q2.core.w) * (-q2.cnt.w * qq * qq));
-                        }
-                    } else {
-                        Real uu = (sqrt_r(r2) - p0.m) * p0.inv_w;
-                        Real qq = Real(1) - uu * uu;
-                        if (vj[j] && qq > Real(0)) acc += (double)(sjv[j] * (-p0.E_a * qq * qq));
-                    }
+                } else {
+                    Real uu = (sqrt_r(r2) - p0.m) * p0.inv_w;
+                    Real qq = Real(1) - uu * uu;
+                    if (vj[j] && qq > Real(0)) acc += (double)(sjv[j] * (-p0.E_a * qq * qq));
                 }
             }
         }
@@ -2454,9 +2443,6 @@ __global__ void k_kick_drift(Buffers B, Launch P, int cur, StepArgs st)
         atomicOr(&B.flags[r], (uint32_t)VBC_FLAG_REBUILD);
 }
 
-// Sum of the per-brick energy/virial partial sums of replica R over its bricks, in a fixed
-// order (strided per thread, then waves, then the wave totals in order); the result is
-// valid in threads 0..7 (one component each).
 // The eight sums of replica R's per-brick partial sums, in an order that does not depend on
 // the workgroup's size (the count pass and the closing reduction run it with different
 // sizes): lane l of the first wave adds bricks l, l + 64, ..., then the wave's lanes are
@@ -2843,8 +2829,8 @@ __device__ __forceinline__ void lcc_union(int32_t *lp, int32_t a, int32_t b)
 
 // Bonds that leave a brick, as (own slot, slot in the neighbouring brick) with the smaller
 // slot first, recorded by the sweep of the bonds in the brick's share of a space that is free
-// between list builds (a resident replica's reference positions are the layout's, another's
-// the list's): up to three per slot.
+// between list builds (xref, or xs of a replica that is stepped in one workgroup and keeps its
+// reference positions in xref): up to three per slot.
 __device__ __forceinline__ int2 *cross_bonds(const Buffers &B, const RepDev &R, int64_t base)
 {
     return (int2 *)((R.resident ? B.xs : B.xref) + 3 * base);
@@ -3345,7 +3331,7 @@ __global__ void __launch_bounds__(DENSE_BLOCK) k_bond_track_dense(Buffers B, Lau
 // whose reserved LDS leaves two workgroups of two waves on a CU (190 us a step), and some
 // replica's list is due in nearly every step.  The steps of such a set run with one workgroup
 // per replica instead: its positions and switching factors stay in LDS, a barrier takes the
-// place of a launch, and one launch does a whole call for all replicas (that set: 20 us a step
+// place of a launch, and one launch does many steps for all replicas (that set: 20 us a step
 // from a uniform start, 65 once some replicas have collapsed into droplets with lists of a
 // hundred neighbours; then one CU's VALU issue on the densest replica is the bound).
 //
@@ -4088,7 +4074,9 @@ size_t lds_bytes_force(const Launch &P)
 // its bricks wait for the first.  The force pass gains from half a round (30,000 particles at
 // density 0.05 27.6 and 26.1 us a step; with none saved, FP64 at 0.3, 60.3 and 61.9), the count
 // pass from one (0.7 saved: 88.6 and 90.1), the list pass, not due in most steps, from two (1.9
-// saved: 49.2 and 51.1).  Laid out for density 1, all passes in one and two launches:
+// saved: 49.2 and 51.1).  The waves a CU can hold follow the kernels' registers: of one type 8
+// per SIMD in the count pass and the bond analyses (the tracker 6), 6 in the FP32 and 5 in the
+// FP64 force pass, 6 in the list build.  Laid out for density 1, all passes in one and two launches:
 // 100,000 particles at 0.05 59.2 and 39.9 (FP64 128 and 62), 400,000 199.6 and 95.1, 200,000
 // at 0.15 72.3 and 60.0; ten steps of twenty tracked systems of 4000 at 0.05 1151 and 766, a
 // tick of a pool of 24 at 0.3 1057 and 872.
