@@ -2355,30 +2355,44 @@ __device__ __forceinline__ void force_brick(const Buffers &B, const Launch &P, i
         // the sums of 64 consecutive particles (a wave's) are added in their order, round after
         // round of the workgroup: the same bits at every workgroup size.  The first round, with
         // which nearly every brick ends, stands by itself (an evaluation of 200,000 particles in
-        // FP64: 175 us, 179 with it in the loop, 176 before)
+        // FP64: 175 us, 179 with it in the loop, 176 before); red holds the sums of as many
+        // rounds as it has places for, so that few bricks meet a further barrier
         const int n_own = __builtin_amdgcn_readfirstlane(S.n_own);  // a scalar: barriers below
         const int wv = threadIdx.x / VBC_WAVE, ln = threadIdx.x % VBC_WAVE, nw = blockDim.x / VBC_WAVE;
         double s = 0.0;
-        auto add = [&]() __attribute__((always_inline)) {
+        auto keep = [&](int at) __attribute__((always_inline)) {
             const double v = wave_sum8(acc);
-            if ((ln & 7) == 0) red[ln >> 3][wv] = v;
-            if (mv) moved = 1;
-            __syncthreads();
+            if ((ln & 7) == 0) red[ln >> 3][at + wv] = v;
+        };
+        auto add = [&](int n) __attribute__((always_inline)) {
             if (threadIdx.x == 1) {
                 // W = W_xx + W_yy + W_zz, summed per wave in the same fixed order
-                for (int w = 0; w < nw; ++w) s += (red[2][w] + red[3][w]) + red[4][w];
+                for (int w = 0; w < n; ++w) s += (red[2][w] + red[3][w]) + red[4][w];
             } else if (threadIdx.x < 8) {
-                for (int w = 0; w < nw; ++w) s += red[threadIdx.x][w];
+                for (int w = 0; w < n; ++w) s += red[threadIdx.x][w];
             }
         };
         if ((int)threadIdx.x < n_own) particle(threadIdx.x);
-        add();
+        if (wv * VBC_WAVE < n_own) keep(0);
+        int at = nw, done = 0;  // places of red given out, sums added
         for (int t0 = blockDim.x; t0 < n_own; t0 += blockDim.x) {
-            for (int k = 0; k < 8; ++k) acc[k] = 0.0;
-            if (t0 + (int)threadIdx.x < n_own) particle(t0 + threadIdx.x);
-            __syncthreads();  // red was read
-            add();
+            if (at + nw > 1024 / VBC_WAVE) {
+                __syncthreads();
+                add(at);
+                __syncthreads();
+                done += at;
+                at = 0;
+            }
+            if (t0 + wv * VBC_WAVE < n_own) {
+                for (int k = 0; k < 8; ++k) acc[k] = 0.0;
+                if (t0 + (int)threadIdx.x < n_own) particle(t0 + threadIdx.x);
+                keep(at);
+            }
+            at += nw;
         }
+        if (mv) moved = 1;
+        __syncthreads();
+        add((n_own + VBC_WAVE - 1) / VBC_WAVE - done);
         if (threadIdx.x < 8) B.part[(size_t)b * 8 + threadIdx.x] = s;
         // a time step's sums: added by the next count pass or the call's closing reduction
         if (st.acc && lb == 0 && threadIdx.x == 0) B.tpend[r] = 1;

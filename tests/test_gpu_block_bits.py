@@ -114,3 +114,28 @@ def test_a_set_block_stays(block):
     assert pool.options()["block"] == block
     pool.step(2, **INTEG)
     pool.check()
+
+
+@pytest.mark.parametrize("precision,brick,n,rho,stage_cap", [("fp32", 5, 4400, 0.9, 4608), ("fp64", 4, 3700, 1.2, 3936)])
+def test_energies_of_very_full_bricks(precision, brick, n, rho, stage_cap):
+    """Bricks of more than 1024 particles (more sums of 64 than the force pass keeps at a time):
+    energy and virial at every workgroup size, in bits, and against the oracle."""
+    import oracle
+    from paper_2609_07842_amd import vbc
+    L, p = W.box_length(n, rho), W.vbc_params(E_a=4.0, f=9.0)
+    x = W.uniform_positions(n, L, 5)
+    nc = int(L / 2.4)
+    c = np.minimum((x * (nc / L)).astype(int), nc - 1) // brick
+    assert np.unique(c, axis=0, return_counts=True)[1].max() > 1024
+    print(f"[full bricks] {precision} cells {nc}", flush=True)
+    s = vbc.System(vbc.replica(n, L, p), precision=precision, brick=brick, block=64, k_max=160, stage_cap=stage_cap)
+    s.set_state(x)
+    out = []
+    for block in (64, 320, 512, 1024):
+        s.tune_set(block=block)
+        out.append(s.force()[2].cpu().numpy()[0].copy())
+    s.check()
+    assert all(np.array_equal(a, out[0]) for a in out)
+    ref = oracle.evaluate(x, L, p)
+    want = np.concatenate([[ref["U"], ref["W"]], ref["Wt"]])
+    assert np.abs(out[0] - want).max() <= (1e-10 if precision == "fp64" else 1e-5) * (np.abs(ref["e"]).sum() + np.abs(ref["Wt"]).max())
