@@ -122,6 +122,16 @@ static void drop_graphs(vbc_handle h)
     h->graphs.clear();
 }
 
+// Free the replaced graphs once nothing on s runs any more.
+static hipError_t free_retired(vbc_handle h, hipStream_t s)
+{
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    for (hipGraphExec_t g : h->retired) (void)hipGraphExecDestroy(g);
+    h->retired.clear();
+    return hipSuccess;
+}
+
 // Record the launch(es) of one kernel class between two events when timing is on.
 template <class Fn>
 static hipError_t timed(vbc_handle h, int kind, hipStream_t s, Fn &&fn)
@@ -1248,6 +1258,7 @@ vbc_status vbc_admit(vbc_handle h, const vbc_replica_desc *d, const double *d_x,
     h->opt.block = Q.block;
     // the graphs of a single-replica handle hold its descriptor
     if (resized || Q.one) {
+        if (h->retired.size() >= 2 * GRAPH_CACHE) VBC_TRY(h, free_retired(h, s), "sync");
         for (auto &g : h->graphs) h->retired.push_back(g.exec);  // other replicas' steps may be running
         h->graphs.clear();
     }
@@ -1534,9 +1545,7 @@ vbc_status vbc_check(vbc_handle h, hipStream_t s, uint32_t *flags_per_replica)
 {
     Range range_("vbc_check");
     if (!h) return fail(VBC_ERR_ARG, "NULL handle");
-    VBC_TRY(h, hipStreamSynchronize(s), "sync");
-    for (hipGraphExec_t g : h->retired) (void)hipGraphExecDestroy(g);
-    h->retired.clear();
+    VBC_TRY(h, free_retired(h, s), "sync");
     std::vector<uint32_t> f(h->P.nrep);
     VBC_TRY(h, hipMemcpy(f.data(), h->B.flags, sizeof(uint32_t) * h->P.nrep, hipMemcpyDeviceToHost),
             "flags readback");

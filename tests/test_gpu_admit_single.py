@@ -35,3 +35,26 @@ def test_admitted_replica_runs_with_its_own_parameters(nsteps, precision):
         h.check()
     for a, b in zip(s.get_state(), fresh.get_state()):
         assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
+
+
+def test_many_admissions():
+    """Replicas that follow one another in one handle without a check in between, each stepped
+    through graphs of its own: the last one's state is that of a fresh handle."""
+    from paper_2609_07842_amd import vbc
+    n, L = 300, W.box_length(300, RHO)
+    desc = lambda k: vbc.replica(n, L, W.vbc_params(E_a=1.0 + 0.1 * k, f=2.0), seed=k)
+    state = lambda k: (W.uniform_positions(n, L, 30 + k), W.maxwell_boltzmann(n, 1.0, 60 + k))
+    s = vbc.System(desc(0), precision="fp32")
+    s._keep_admit = {}
+    s.set_state(*state(0))
+    for k in range(1, 60):
+        s.step(3, **INTEG)
+        vbc.Pool.retire(s, 0)
+        assert vbc.Pool.admit(s, desc(k), *state(k)) == 0
+    fresh = vbc.System(desc(59), precision="fp32")
+    fresh.set_state(*state(59))
+    for h in (s, fresh):
+        h.step(3, **INTEG)
+        h.check()
+    for a, b in zip(s.get_state(), fresh.get_state()):
+        assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
